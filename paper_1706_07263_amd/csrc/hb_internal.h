@@ -127,6 +127,23 @@ constexpr float kMinSkipLog2 = 16.0f;
 // long as its count of such chunks stays within the budget the rest of the
 // tolerance buys (every pixel of the wave then loses at most that mass).
 constexpr float kBandLog2 = 6.0f;
+// Certified depth (MFMA kernel).  The stated bound E on the posterior mean
+// holds for a pixel as soon as its skipped weight is at most E / thb_max of
+// its kept weight (the mean moves by at most thb_max times their ratio).  A
+// wave sums the bounds of the chunks it leaves out, so it may stop at a far
+// smaller depth than the a-priori threshold above, which assumes that every
+// skipped node lies just under it and that the kept weight is 1/2: on the
+// 1080p frames (256 x 256 grid) the certificate needs a depth of 26 to 28.6
+// (10th to 99th percentile of the waves; 25 to 29.4 over six other shapes,
+// grids 64 to 256, levels 0 to 3) where the threshold is 46 and its band 40.
+// The first depth is E / (2 thb_max) in log2 (28.6 by default), which one
+// wave in a hundred fails; a failed wave adds the chunks of the next
+// kDepthStep units.  Super-tiles are left out kSuperMargin units below the
+// chunks' depth (their bound counts for all of their nodes).
+constexpr float kDepthStep = 4.0f;
+constexpr float kSuperMargin = 12.0f;
+constexpr float kMassLog2 = 48.0f;     // unit of the skipped weight: 2^-48
+constexpr float kChunkNodesLog2 = 4.0f;
 struct SkipRule {
     float skip_log2 = kExactSkipLog2, band_log2 = kExactSkipLog2;
     int band_chunks = 0;
@@ -205,6 +222,8 @@ struct PosteriorArgs {
     int split;
     float scale;             // sqrt(log2(e) / (2 sigma^2))
     float skip_log2;         // chunks bounded more than this below the reference are skipped
+    float depth0;            // MFMA kernel: depth of the first pass (skip_log2: the only one)
+    float cert_log2;         // MFMA kernel: largest certified log2 of skipped over kept weight
     float band_log2;         // chunks bounded more than this below it are skipped while the budget lasts
     int band_chunks;         // budget: chunks a wave may skip between band_log2 and skip_log2
     float *gref;             // [n][LL] best probe logit over the whole grid, or null (one split)

@@ -59,6 +59,8 @@ struct hb_plan_s {
     float iref[3] = {1, 1, 1};
     float scale = 1.0f;
     float skip_log2 = kExactSkipLog2;
+    float depth0 = kExactSkipLog2;      // = skip_log2 when nothing is certified
+    float cert_log2 = 0.0f;
     float band_log2 = kExactSkipLog2;   // = skip_log2 when no budget is in use
     int band_chunks = 0;
 
@@ -551,6 +553,8 @@ hb_status_t estimate(hb_plan_s *p, const void *d_frames, int32_t n_frames, const
         pa.split = p->split;
         pa.scale = p->scale;
         pa.skip_log2 = p->skip_log2;
+        pa.depth0 = p->depth0;
+        pa.cert_log2 = p->cert_log2;
         pa.band_log2 = p->band_log2;
         pa.band_chunks = p->band_chunks;
         pa.part = cb.part;
@@ -729,6 +733,15 @@ hb_status_t hb_plan_create(const hb_plan_desc_t *desc, int device, hb_plan_t *ou
     p->skip_log2 = rule.skip_log2;
     p->band_log2 = rule.band_log2;
     p->band_chunks = rule.band_chunks;
+    p->depth0 = p->skip_log2;
+    if (rule.bound > 0.0 && p->split == 1) {
+        // skipped over kept weight that moves a mean by at most the stated
+        // bound (a sixteenth left for rounding); the kernel of a split grid
+        // sees a part of the kept weight only and takes the a-priori threshold
+        const double ratio = rule.bound / desc->thb_max;
+        p->depth0 = (float)std::min<double>(p->skip_log2, std::max<double>(kMinSkipLog2, -std::log2(0.5 * ratio)));
+        p->cert_log2 = (float)std::log2(ratio * (1.0 - 1.0 / 16));
+    }
     p->info.skip_bound = rule.bound;
     p->info.skip_log2 = p->skip_log2;
     p->info.band_log2 = p->band_log2;

@@ -488,6 +488,34 @@ def test_posterior_tolerance_skips_within_its_bound(torch_cuda, tol):
         hbtest.assert_maps_close(out[tol], hbtest.run_oracle(fr[None], "f32", s), f"tolerance {tol}")
 
 
+@pytest.mark.parametrize("gt,gs,levels,illumination", [(32, 32, 1, 0), (64, 45, 0, 1), (130, 128, 2, 0), (256, 256, 1, 1)])
+@pytest.mark.parametrize("tol", [1e-5, 1e-3, 0.1, 1.0])
+def test_certified_skipping_stays_within_its_bound(torch_cuda, gt, gs, levels, illumination, tol):
+    """The MFMA kernel skips as far as the weight it keeps certifies the
+    stated bound.  The frame holds tissue at the corners of the grid, values
+    outside it and clipped, dark and bright pixels, whose posteriors sit on
+    few nodes and whose certificates therefore need further passes."""
+    rng = np.random.default_rng(gt + levels)
+    thb = np.repeat(np.linspace(5.0, 260.0, 64), 64).reshape(64, 64)
+    so2 = np.tile(np.linspace(0.15, 1.0, 64), (64, 1))
+    fr = synth.noisy_frame(*synth.hb_hbo2(thb, so2), synth.spectra(), 91 + gt)
+    fr[rng.integers(0, 64, 12), rng.integers(0, 64, 12)] = 1e-6
+    fr[rng.integers(0, 64, 12), rng.integers(0, 64, 12)] = 1.5
+    s = dict(_settings(levels=levels, grid=gt), grid_thb=gt, grid_so2=gs, illumination=illumination)
+    out = {}
+    for t in (0.0, tol):
+        run = hbtest.GpuRun(64, 64, dict(s, posterior_tolerance=t), grid_split=1)
+        assert run.plan.info()["posterior_kernel"] == "mfma"
+        bound = run.plan.info()["skip_bound"]
+        out[t] = run(fr[None])[:, :2].astype(np.float64)
+        run.close()
+    assert 0 < bound <= tol
+    diff = np.abs(out[tol] - out[0.0]).max()
+    print(f"{gt}x{gs} L{levels} tol {tol}: bound {bound:.3g}, max diff {diff:.3g}")
+    # float32 sums of either kept set round within the FP32 parity tolerance
+    assert diff <= bound + 2e-5
+
+
 @pytest.mark.parametrize("levels", [0, 1, 2])
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("camera", ["default", "shifted"])
