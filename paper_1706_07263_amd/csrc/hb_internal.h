@@ -142,7 +142,7 @@ constexpr float kBandLog2 = 6.0f;
 // chunks' depth (their bound counts for all of their nodes).
 constexpr float kDepthStep = 4.0f;
 constexpr float kSuperMargin = 12.0f;
-constexpr float kMassLog2 = 48.0f;     // unit of the skipped weight: 2^-48
+constexpr float kMassLog2 = 42.0f;     // unit of the skipped weight: 2^-42
 constexpr float kChunkNodesLog2 = 4.0f;
 struct SkipRule {
     float skip_log2 = kExactSkipLog2, band_log2 = kExactSkipLog2;
@@ -175,12 +175,34 @@ inline int super_floats(int side) {
 constexpr int kStripPixels = 2048;
 constexpr int kBlockThreads = 256;
 
-// Pixel blocks of 16 per wave in the posterior kernel (an 8 x 4 tile of LL
-// pixels for two).  Each chunk's 1 KB split operand is loaded once per wave
-// and used for every block, so more blocks cut the vector-memory traffic per
-// pair; fewer blocks give tighter skip boxes (fewer pairs evaluated).  Two
-// measured fastest (one was 10% slower, bound by operand loads).
-constexpr int kPixelBlocks = 2;
+// Tables of the MFMA kernel's tests, derived from the super-tile table:
+//   headers  [super][kHdrFloats]: absolute box lower corner (3), upper corner
+//            (3), Hb and HbO2 of the centre, centre high parts (3), low parts
+//            (3), segment (int bits)
+//   boxes    [chunk][kBoxFloats]: the chunk's absolute box, lower corner (3)
+//            and upper corner (3), rounded outward
+//   probes   split operands (as the chunks') of 16 probes each in absolute
+//            coordinates, probe_slots(side) per super-tile; slots without a
+//            probe have the logit kPadLogit
+// One lane tests one super-tile or chunk, and 64 consecutive entries are one
+// contiguous read.
+constexpr int kHdrFloats = 16;
+constexpr int kBoxFloats = 8;
+inline int probe_shift(int side) { return side <= 8 ? 0 : (side <= 16 ? 2 : 4); }
+inline int probe_slots(int side) { return 1 << probe_shift(side); }   // ceil(side / 8)^2 and more
+
+// LL pixels of one tile of the MFMA kernel (8 x 4, two MFMA blocks of 16).
+// Each chunk's 1 KB split operand is loaded once and used for both blocks;
+// larger tiles would share it further but keep more chunks.
+constexpr int kTilePixels = 32;
+// The super-tiles are dealt to kSegments segments (row + column of the
+// super-tile, modulo the count), each with its own sums, which 1, 2 or 4 waves
+// evaluate: the segments and the order in which they are merged do not depend
+// on the number of waves, so a frame gives the same bits in any launch.  The
+// kept super-tiles form a band, which these diagonals cut evenly: the busiest
+// segment has 1.07 to 1.21 times the mean work over five shapes (1.10 to 1.33
+// with row + 2 column, 2.2 to 3.3 with contiguous quarters).
+constexpr int kSegments = 4;
 
 // Partial moments per LL pixel and grid split:
 //   [0] logit reference, [1] S0, [2] S1 about the anchor, [3] S2 about the anchor,
@@ -228,6 +250,13 @@ struct PosteriorArgs {
     int band_chunks;         // budget: chunks a wave may skip between band_log2 and skip_log2
     float *gref;             // [n][LL] best probe logit over the whole grid, or null (one split)
     float *part;             // [n][split][kPartFields][LL]
+    const float *headers;    // MFMA kernel: test tables (see kHdrFloats)
+    const float *boxes;
+    const void *probes;
+    int probe_shift;         // log2 of the probe slots of a super-tile
+    int supers_per_test;     // 64 / chunks_per_super
+    int inv_chunks;          // ceil(65536 / chunks_per_super): lane / chunks_per_super = lane * this >> 16
+    int list_across;         // MFMA kernel: list kept super-tiles across groups of 64 (else group by group)
     const float *lo;         // [chunk][kLoFloats] coordinate low parts (double-float logits)
     int precise;             // direct kernel: every logit from double-float differences
     unsigned long long *work;  // optional: [0] pairs evaluated (pixel x node), added per wave,

@@ -736,19 +736,46 @@ __device__ __forceinline__ void kahan_add(float &s, float &c, float x) {
     s = t;
 }
 
-// Sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48, each pairwise step exact
-// up to a carried error term (two-sum), the error added at the end.
-__device__ __forceinline__ float lane_sum_rows(float x) {
-    float e = 0.0f;
-#pragma unroll
-    for (int o = 16; o <= 32; o <<= 1) {
-        const float y = __shfl_xor(x, o), ye = __shfl_xor(e, o);
-        float s, err;
-        two_sum(x, y, s, err);
-        x = s;
-        e = (e + ye) + err;
-    }
-    return x + e;
+// Lane exchanges on the VALU (no LDS round trip): a DPP move, and the row
+// swaps of gfx950.  swap_rows16 exchanges the odd 16-lane rows of a with the
+// even rows of b, swap_rows32 the upper half of a with the lower half of b.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ void swap_rows16(float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap_rows32(float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+
+template <bool MAX>
+__device__ __forceinline__ float pick(float a, float b) {
+    return MAX ? fmaxf(a, b) : fminf(a, b);
+}
+// Minimum / maximum over the 16 lanes of a row, every lane gets it.
+template <bool MAX>
+__device__ __forceinline__ float row_reduce(float x) {
+    x = pick<MAX>(x, dpp<0xB1>(x));    // lane ^ 1
+    x = pick<MAX>(x, dpp<0x4E>(x));    // lane ^ 2
+    x = pick<MAX>(x, dpp<0x141>(x));   // the other quad of eight lanes
+    return pick<MAX>(x, dpp<0x140>(x));   // the other eight of the row
+}
+// Maximum over the four lanes l, l ^ 16, l ^ 32, l ^ 48.
+__device__ __forceinline__ float max_rows(float x) {
+    float y = x;
+    swap_rows16(x, y);
+    x = y = fmaxf(x, y);
+    swap_rows32(x, y);
+    return fmaxf(x, y);
+}
+__device__ __forceinline__ float lane_value(float x, int lane) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
 }
 
 __device__ __forceinline__ f32x4 mfma_16x16x32_bf16(bf16x8 a, bf16x8 b, f32x4 c) {
@@ -784,8 +811,8 @@ __device__ __forceinline__ bf16x8 split_pixel_operand(float u, float c, bool coo
 
 
 constexpr int kXcds = 8;   // accelerator complex dies of an MI355X, each with its own L2
-// Workgroups of four waves resident at once: 256 CUs x 4 SIMDs x 6 waves / 4.
-constexpr int kResidentGroups = 256 * 4 * 6 / 4;
+// Waves resident at once: 256 CUs x 4 SIMDs x 6 waves.
+constexpr int kResidentWaves = 256 * 4 * 6;
 constexpr int kOrderSquare = 8;
 
 // A wave takes a compact 8-wide tile of LL pixels (PW / 8 rows), four waves
@@ -806,25 +833,27 @@ __device__ __forceinline__ void square_or(float r, float m, bool sq, float &p, f
     pe = sq ? fmaf(r, r, -rr) : 0.0f;
 }
 
+// Renumbered workgroup.  Workgroups are dealt to the 8 XCDs in turn; each XCD
+// takes a contiguous run of tiles (neighbouring pixels keep overlapping
+// chunks, which then stay in that XCD's L2).  The last n % 8 workgroups keep
+// their numbers.  A launch whose workgroups are all resident at once keeps the
+// plain numbering: its time is that of the slowest XCD, and interleaved tiles
+// spread the frame's costly regions over all eight (measured 1.5% faster for
+// one 1080p frame, slower from two frames on).
+__device__ __forceinline__ int xcd_order(int bid, int n, int resident) {
+    const int per_xcd = n / kXcds;
+    return n > resident && bid < per_xcd * kXcds ? (bid % kXcds) * per_xcd + bid / kXcds : bid;
+}
+
+// Work number `sub` of four vertically stacked tiles of PW pixels (kWaveTileW
+// wide) in group `idx`.
 template <int PW>
-__device__ __forceinline__ WaveWork wave_work(const PosteriorArgs &a) {
+__device__ __forceinline__ WaveWork tile_work(const PosteriorArgs &a, int idx, int sub) {
     constexpr int TH = PW / kWaveTileW;
     WaveWork w;
-    const int wave = threadIdx.x >> 6;
     const int S = a.split;
-    // Workgroups are dealt to the 8 XCDs in turn; renumber them so that each
-    // XCD takes a contiguous run of tiles (neighbouring pixels keep
-    // overlapping chunks, which then stay in that XCD's L2).  The last
-    // gridDim.x % 8 workgroups keep their numbers.  A launch whose
-    // workgroups are all resident at once keeps the plain numbering: its
-    // time is that of the slowest XCD, and interleaved tiles spread the
-    // frame's costly regions over all eight (measured 1.5% faster for one
-    // 1080p frame, slower from two frames on).
-    int bid = blockIdx.x;
-    const int per_xcd = gridDim.x / kXcds;
-    if (gridDim.x > kResidentGroups && bid < per_xcd * kXcds) bid = (bid % kXcds) * per_xcd + bid / kXcds;
-    w.split = bid % S;
-    const int chunk = bid / S;
+    w.split = idx % S;
+    const int chunk = idx / S;
     const int bcols = (a.wl + kWaveTileW - 1) / kWaveTileW;
     const int brows = (a.hl + 4 * TH - 1) / (4 * TH);
     const int per_frame = bcols * brows;
@@ -846,10 +875,10 @@ __device__ __forceinline__ WaveWork wave_work(const PosteriorArgs &a) {
         br = o / wl;
         bc = full * kOrderSquare + o % wl;
     }
-    w.r0 = (band * kOrderSquare + br) * 4 * TH + wave * TH;
+    w.r0 = (band * kOrderSquare + br) * 4 * TH + sub * TH;
     w.c0 = bc * kWaveTileW;
-    w.s0 = (int)((long long)a.n_supers * w.split / S);
-    w.s1 = (int)((long long)a.n_supers * (w.split + 1) / S);
+    w.s0 = S == 1 ? 0 : (int)((long long)a.n_supers * w.split / S);
+    w.s1 = S == 1 ? a.n_supers : (int)((long long)a.n_supers * (w.split + 1) / S);
     return w;
 }
 
@@ -1150,41 +1179,25 @@ __device__ float far_gap_max(const PosteriorArgs &a, const WaveWork &w, const fl
     return mx;
 }
 
-// Fused recomposition for one split and n <= 2: every lane of pixel row lp
-// holds the pixel's complete sums after the lane reduction, so the estimate
-// is anchor + S1 / S0 (what the split merge gives for one split, bit for
-// bit).  The wave then writes the maps of its tile, (4 x 2^n) x (8 x 2^n)
-// pixels in units of V along a row: the unit's estimate is fetched from its
-// pixel's lanes (uniform trip count) before any lane branches.
-template <int PB, int V>
-__device__ __forceinline__ void fused_maps(const PosteriorArgs &a, const WaveWork &w, const float *anc_hb,
-                                           const float *anc_ox, const float *R0, const float *R1,
-                                           const float *R2, int lane) {
-    const int lp = lane & 15, lk = lane >> 4;
+// Fused recomposition for one split and n <= 2: lane l (and l + 32) holds the
+// estimate of the tile's pixel l.  The tile's waves write the maps of its
+// (4 x 2^n) x (8 x 2^n) pixels in units of V along a row: the unit's estimate
+// is fetched from its pixel's lane (uniform trip count) before any lane
+// branches.
+template <int NW, int V>
+__device__ __forceinline__ void fused_maps(const PosteriorArgs &a, const WaveWork &w, float ex, float ey, int wave,
+                                           int lane) {
     const int n = a.levels, B = 1 << n;
-    float ex[PB], ey[PB];
-#pragma unroll
-    for (int b = 0; b < PB; ++b) {
-        ex[b] = anc_hb[b] + R1[b] / R0[b];
-        ey[b] = anc_ox[b] + R2[b] / R0[b];
-        long long p;
-        if (lk == 0 && wave_pixel(a, w, b * 16 + lp, p)) a.est[(size_t)w.f * a.LL + p] = make_float2(ex[b], ey[b]);
-    }
     const int per_row = (kWaveTileW * B) / V;             // units per tile row
-    const int n_units = (16 * PB / kWaveTileW) * B * per_row;
-    const int T = (n_units + 63) / 64;                     // same for every lane
+    const int n_units = (kTilePixels / kWaveTileW) * B * per_row;
+    const int T = (n_units + 64 * NW - 1) / (64 * NW);     // same for every lane
     for (int t = 0; t < T; ++t) {
-        const int u = lane + 64 * t;
+        const int u = lane + 64 * (wave + NW * t);
         const bool live = u < n_units;
         const int y = live ? u / per_row : 0, x = live ? (u - y * per_row) * V : 0;
         const int ty = y >> n, tx = x >> n;
         const int i = ty * kWaveTileW + tx;                 // LL pixel of the tile
-        float2 e = make_float2(0.0f, 0.0f);
-#pragma unroll
-        for (int b = 0; b < PB; ++b) {
-            const float sx = __shfl(ex[b], i & 15), sy = __shfl(ey[b], i & 15);
-            if ((i >> 4) == b) e = make_float2(sx, sy);
-        }
+        const float2 e = make_float2(__shfl(ex, i), __shfl(ey, i));
         const int gr = w.r0 + ty, gc = w.c0 + tx;
         if (!live || gr >= a.hl || gc >= a.wl) continue;
         const size_t o = ((size_t)w.f * a.H + ((size_t)gr << n) + (y & (B - 1))) * a.W + ((size_t)gc << n) +
@@ -1334,54 +1347,217 @@ __device__ __forceinline__ void far_pixel_sums(const PosteriorArgs &a, const Wav
     for (int k = 0; k < 3; ++k) S[k] = x[k] + e[k];
 }
 
-// MFMA kernel: a wave takes PB blocks of 16 LL pixels.  Per super-tile,
-// 16-node chunk and pixel block one v_mfma_f32_16x16x32_bf16 forms the
-// 16 x 16 logits
+// MFMA kernel: NW waves take a tile of 32 LL pixels, two blocks of 16.  Per
+// super-tile, 16-node chunk and pixel block one v_mfma_f32_16x16x32_bf16 forms
+// the 16 x 16 logits
 //   t - m = [v_g, -|v_g|^2, 1] . [2 r, 1, -(|r|^2 + m)]
 // (nodes as rows, pixels as columns) from exact three-part bf16 splits of the
 // FP32 operands: every product except the smallest (u3 v3), in half the
 // cycles of the FP32 16x16x4 MFMA.  The node operand (1 KB per chunk) is
-// loaded once for all PB blocks.  Each lane then holds 1 pixel x the 4
+// loaded once for both blocks.  Each lane then holds 1 pixel x the 4
 // nodes of one chunk row (lane l: pixel l % 16, THb row l / 16, SO2 offsets
 // 0..3) and runs the exponentials and the moments on the VALU.
-// Two pixel blocks per wave (an 8 x 4 tile) at six waves per SIMD (80 VGPRs;
-// spills only inside the far-observation pass) measured fastest on the 1080p
-// workload; WAVES = 4 (88 VGPRs, three operand buffers, wave priority by
-// predicted work) serves launches small enough to be resident at once.  Both
-// evaluate the same chunks in the same order.  DFC: the pixel operand's
-// constant |r|^2 + m summed as a double-float (plans near the precision
-// budget).
-template <int PB, int WAVES, bool DFC>
-__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_posterior(PosteriorArgs a) {
-    constexpr int PW = 16 * PB;
-    constexpr int LPP = 64 / PW;
+//
+// The tile's reference, its chunk tests and its kept chunks are shared out
+// between its waves; what is kept, the segments and their sums are the same
+// for any NW.  DFC: the pixel operand's constant |r|^2 + m summed as a
+// double-float (plans near the precision budget).
+//
+// Bound by VALU issue: 97% busy on sixteen 1080p frames (256 x 256 grid), 14
+// instructions (one MFMA and four exponentials among them) per 256 pairs and
+// about 3000 per tile around them (14250 in all).  Six waves per SIMD (80
+// VGPRs; spills outside the chunk loop only) measured fastest.  Times a call,
+// one wave per tile throughout -> this: 640x480 frame 224 -> 88 us, 1080p
+// frame 223 -> 194, 64x64 frame on a 32 x 32 grid 87 -> 73, sixteen 1080p
+// frames 2391 -> 2308, 1280x1024 pair on a 512 x 512 grid 2999 -> 2784.
+struct KeptSuper {
+    unsigned lo, hi;   // kept chunks of the super-tile, one bit each
+    int si, segment;
+};
+
+template <int NW>
+struct TileShared {
+    KeptSuper kept[64];
+    float total[6][kTilePixels];   // S0, S1, S2 and their compensation, per pixel
+    // several waves: sums of the segments, best probes, skipped weights
+    float part[NW > 1 ? kSegments : 1][6][kTilePixels];
+    float best[NW][kTilePixels];
+    unsigned mass[NW];
+};
+
+// base + n / d with n = nh + nl and d = dh + dl, rounded once.
+__device__ __forceinline__ float plus_quotient(float base, float nh, float nl, float dh, float dl) {
+    const float q = nh / dh;
+    float s, e;
+    two_sum(base, q, s, e);
+    return s + (e + (fmaf(-q, dh, nh) + fmaf(-q, dl, nl)) / dh);
+}
+
+// (hi, lo) += (x, e), the rounding error of the sum carried in lo.
+__device__ __forceinline__ void carry_add(float &hi, float &lo, float x, float e) {
+    float t, r;
+    two_sum(hi, x, t, r);
+    hi = t;
+    lo += r + e;
+}
+
+template <int NW, bool DFC>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(6))) void k_posterior(PosteriorArgs a) {
+    constexpr int PB = kTilePixels / 16;
+    __shared__ TileShared<NW> sh;
     const int lane = threadIdx.x & 63;
+    const int wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int lp = lane & 15, lk = lane >> 4;
-    const WaveWork w = wave_work<PW>(a);
+    const int bid = xcd_order(blockIdx.x, gridDim.x, kResidentWaves / NW);
+    const WaveWork w = tile_work<kTilePixels>(a, bid >> 2, bid & 3);
     // Tiles below the last row of the frame (the workgroup grid rounds the
     // rows up) hold no pixel: nothing to do.
     if (w.r0 >= a.hl) return;
     const float *zf = a.z + (size_t)w.f * 6 * a.LL;
     const float sc = a.scale;
+    for (int i = threadIdx.x; i < 6 * kTilePixels; i += 64 * NW) (&sh.total[0][0])[i] = 0.0f;
 
-    // Per-pixel pass: lane -> pixel lane % PW of the wave tile.
-    const int part = lane / PW;
-    float ph[3], pl[3];
-    {
-        long long p;
-        wave_pixel(a, w, lane % PW, p);
+    // Observations: lane (lp, lk) holds coordinate lk of pixel b*16 + lp
+    // (lk == 3 repeats coordinate 0).
+    float ah[PB], al[PB];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) load_obs(zf, a.LL, p, k, sc, ph[k], pl[k]);
+    for (int b = 0; b < PB; ++b) {
+        long long p;
+        wave_pixel(a, w, b * 16 + lp, p);
+        load_obs(zf, a.LL, p, lk < 3 ? lk : 0, sc, ah[b], al[b]);
     }
-    float zlo[3], zhi[3];
-    wave_obs_box(ph, pl, zlo, zhi);
-    PixelRef ref = pixel_reference<PW, LPP>(a, w, ph, pl, part, zlo, zhi);
+    // Observation box of the tile, widened for rounding.
+    float zbox[6], far2 = 0.0f;
+    {
+        const float x0 = ah[0] + al[0], x1 = ah[1] + al[1];
+        const float lo = row_reduce<false>(fminf(x0, x1)), hi = row_reduce<true>(fmaxf(x0, x1));
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            zbox[k] = lane_value(lo, 16 * k) - kBoxSlack;
+            zbox[3 + k] = lane_value(hi, 16 * k) + kBoxSlack;
+            const float e = fmaxf(-zbox[k], zbox[3 + k]);
+            far2 = fmaf(e, e, far2);
+        }
+    }
+    auto super_bound = [&](int si) {   // -inf past the split's range
+        return si < w.s1 ? box_box_bound(a.headers + (size_t)si * kHdrFloats, zbox) : -INFINITY;
+    };
+    // Pixel operands (the MFMA B operands) of both blocks from their
+    // coordinates r (lane groups lk < 3) and m: c = -(|r|^2 + m), formed over
+    // the pixel's four lanes, is wanted by its lane of group 3 only.
+    auto pixel_operands = [&](const float (&r)[PB], const float (&m)[PB], auto dfc, bf16x8 (&av)[PB]) {
+        float c0, c1;
+        if constexpr (decltype(dfc)::value) {
+            // as a double-float (plans near the precision budget)
+            float p, pe, q, qe;
+            square_or(r[0], m[0], lk < 3, p, pe);
+            square_or(r[1], m[1], lk < 3, q, qe);
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+                if (o == 0) {
+                    swap_rows16(p, q);
+                    swap_rows16(pe, qe);
+                } else {
+                    swap_rows32(p, q);
+                    swap_rows32(pe, qe);
+                }
+                float t, e;
+                two_sum(p, q, t, e);
+                p = q = t;
+                pe = qe = (pe + qe) + e;
+            }
+            c0 = c1 = -(p + pe);
+        } else {
+            float p = lk < 3 ? r[0] * r[0] : m[0], q = lk < 3 ? r[1] * r[1] : m[1];
+            swap_rows16(p, q);   // rows: block 0 of rows 0 + 1, block 1 of rows 0 + 1, then of rows 2 + 3
+            p = q = p + q;
+            swap_rows32(p, q);
+            c0 = c1 = -(p + q);   // rows: block 0, 1, 0, 1
+        }
+        swap_rows16(c0, c1);      // block 0 on every row, block 1 on every row
+        av[0] = split_pixel_operand(2.0f * r[0], c0, lk < 3);
+        av[1] = split_pixel_operand(2.0f * r[1], c1, lk < 3);
+    };
+    const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+
+    // Reference: each pixel's best probe (one node per 8 x 8 patch) over the
+    // split's super-tiles.  The super-tile with the highest bound is probed
+    // first, then those bounded above the tile's lowest best probe: the
+    // result equals a scan of every probe.  The probes' logits come from MFMAs
+    // on split operands in absolute coordinates, 16 probes at once: they round
+    // at the scale of |z|^2 2^-22, which the reference may (every weight is
+    // formed relative to the same m, and the skip tests allow for far2 2^-20).
+    float mup = -INFINITY;   // upper bound of every logit of the split
+    int best = w.s0;
+    for (int g = w.s0; g < w.s1; g += 64) {
+        const float b = super_bound(g + lane);
+        const float r = row_reduce<true>(b);
+        const float top = fmaxf(fmaxf(lane_value(r, 0), lane_value(r, 16)), fmaxf(lane_value(r, 32), lane_value(r, 48)));
+        if (top > mup) {
+            mup = top;
+            best = g + __builtin_ctzll(__builtin_amdgcn_ballot_w64(b == top) | (1ull << 63));
+        }
+    }
+    best = __builtin_amdgcn_readfirstlane(best);
+    float am[PB] = {-INFINITY, -INFINITY};   // reference of pixel b*16 + lp
+    {
+        bf16x8 pv[PB];
+        const float x[PB] = {ah[0] + al[0], ah[1] + al[1]}, none[PB] = {0.0f, 0.0f};
+        pixel_operands(x, none, std::false_type{}, pv);
+        const int shift = 4 - a.probe_shift;   // log2 of the super-tiles of one probe operand
+        auto probe = [&](int blk) {
+            const bf16x8 v = reinterpret_cast<const bf16x8 *>(a.probes)[(size_t)blk * 64 + lane];
+#pragma unroll
+            for (int b = 0; b < PB; ++b) {
+                f32x4 d = mfma_16x16x32_bf16(v, pv[b], zero4);
+                if (a.split > 1) {
+                    // the operand may hold super-tiles of other splits
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int si = (blk << shift) + ((4 * lk + e) >> a.probe_shift);
+                        if (si < w.s0 || si >= w.s1) d[e] = -INFINITY;
+                    }
+                }
+                am[b] = fmaxf(fmaxf(am[b], fmaxf(d[0], d[1])), fmaxf(d[2], d[3]));
+            }
+        };
+        const int first = best >> shift;
+        probe(first);   // every wave
+#pragma unroll
+        for (int b = 0; b < PB; ++b) am[b] = max_rows(am[b]);
+        float lowest = INFINITY;
+#pragma unroll
+        for (int b = 0; b < PB; ++b) lowest = fminf(lowest, am[b] > -INFINITY ? am[b] : INFINITY);
+        lowest = lane_value(row_reduce<false>(lowest), 0);
+        int done = first, turn = 0;
+        for (int g = w.s0; g < w.s1; g += 64) {
+            unsigned long long cand = __builtin_amdgcn_ballot_w64(super_bound(g + lane) > lowest);
+            while (cand) {
+                const int blk = (g + __builtin_ctzll(cand)) >> shift;
+                cand &= cand - 1;
+                if (blk == first || blk == done) continue;
+                done = blk;
+                if (NW == 1 || turn++ % NW == wave) probe(blk);
+            }
+        }
+        // over the pixel's lanes and the waves
+#pragma unroll
+        for (int b = 0; b < PB; ++b) am[b] = max_rows(am[b]);
+        if constexpr (NW > 1) {
+            if (lane < 32) sh.best[wave][lane] = lane < 16 ? am[0] : am[1];
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < NW; ++q)
+#pragma unroll
+                for (int b = 0; b < PB; ++b) am[b] = fmaxf(am[b], sh.best[q][16 * b + lp]);
+        }
+    }
 
     // Skipping.  A chunk (or super-tile) whose logit upper bound lies more
     // than skip_log2 below every pixel's reference has every weight below
     // 2^-skip_log2 (exactly 0 in float32 at kExactSkipLog2, so then leaving
     // it out changes no bit).  The bound is taken between the chunk's box and
-    // the box of the wave's observations (min reference over the wave), one
+    // the box of the tile's observations (min reference over the tile), one
     // chunk per lane.  With a posterior tolerance the first pass keeps only
     // the chunks bounded less than depth0 below the reference; the bounds of
     // those it leaves out add up to a bound on the skipped weight, which is
@@ -1390,47 +1566,40 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(W
     // the chunks of the next kDepthStep units, down to skip_log2.  Sixteen
     // 1080p frames: 9.8% of the pairs instead of 12.1%, 2.82 to 2.50 ms a call;
     // the 1280x1024 pair on a 512 x 512 grid: 3.41 to 2.98 ms.
-    float mmin = ref.m;
-    if (a.gref) {
-        long long p;
-        wave_pixel(a, w, lane % PW, p);
-        mmin = fmaxf(mmin, a.gref[(size_t)w.f * a.LL + p]);
-    }
-    // A pixel without a finite logit (a NaN observation) gets NaN maps
-    // whatever is kept; it must not switch skipping off for its wave.
-    if (!(mmin > -INFINITY)) mmin = INFINITY;
+    const int px = lane & 31;
+    float mmin = INFINITY;
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) mmin = fminf(mmin, __shfl_xor(mmin, o));
+    for (int b = 0; b < PB; ++b) {
+        float m = am[b];
+        if (a.gref) {
+            long long p;
+            wave_pixel(a, w, b * 16 + lp, p);
+            m = fmaxf(m, a.gref[(size_t)w.f * a.LL + p]);
+        }
+        // A pixel without a finite logit (a NaN observation) gets NaN maps
+        // whatever is kept; it must not switch skipping off for its tile.
+        mmin = fminf(mmin, m > -INFINITY ? m : INFINITY);
+    }
+    mmin = lane_value(row_reduce<false>(mmin), 0) - far2 * 0x1p-20f;
     // If some weight could exceed 2^kFarGap relative to the best probe, take
     // the exact maximum over the nodes of the chunks that will be kept (the
     // only weights evaluated); a split far from the posterior usually keeps
     // none, and then the reference needs no refinement.
-    if (__any(!(ref.mup - ref.m <= kFarGap))) ref.m = far_gap_max<PW, LPP>(a, w, ph, pl, part, zlo, zhi, mmin, ref.m);
-
-    // Pixel operand (the MFMA B operand) of block b: lane (lp, lk) holds
-    // coordinate lk of pixel b*16 + lp (lk == 3: the homogeneous 1, and m for
-    // the constant term).
-    float ah[PB], al[PB], am[PB];
-#pragma unroll
-    for (int b = 0; b < PB; ++b) {
+    if (__any(!(mup - am[0] <= kFarGap) || !(mup - am[1] <= kFarGap))) {
         long long p;
-        wave_pixel(a, w, b * 16 + lp, p);
-        load_obs(zf, a.LL, p, lk < 3 ? lk : 0, sc, ah[b], al[b]);
-        am[b] = __shfl(ref.m, b * 16 + lp);
-    }
-    // Result layout: lane (lp, lk) holds pixel b*16 + lp and the four nodes
-    // of chunk row lk; its sums run over those nodes of every kept chunk.
-    // Sums across super-tiles carry Kahan compensation terms K0..K2.
-    float anc_hb[PB], anc_ox[PB], R0[PB], R1[PB], R2[PB], K0[PB], K1[PB], K2[PB];
+        wave_pixel(a, w, px, p);
+        float ph[3], pl[3];
 #pragma unroll
-    for (int b = 0; b < PB; ++b) {
-        anc_hb[b] = __shfl(ref.ahb, b * 16 + lp);
-        anc_ox[b] = __shfl(ref.aox, b * 16 + lp);
-        R0[b] = R1[b] = R2[b] = 0.0f;
-        K0[b] = K1[b] = K2[b] = 0.0f;
+        for (int k = 0; k < 3; ++k) load_obs(zf, a.LL, p, k, sc, ph[k], pl[k]);
+        const float m = far_gap_max<kTilePixels, 2>(a, w, ph, pl, lane >> 5, zbox, zbox + 3, mmin,
+                                                    (px < 16 ? am[0] : am[1]));
+#pragma unroll
+        for (int b = 0; b < PB; ++b) am[b] = __shfl(m, b * 16 + lp);
     }
+    // Anchor of the moments, for the whole tile: the centre of the super-tile
+    // with the highest bound.
+    const float anc_hb = a.headers[(size_t)best * kHdrFloats + 6], anc_ox = a.headers[(size_t)best * kHdrFloats + 7];
 
-    const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
     unsigned executed = 0;   // chunks evaluated by this wave
     // Split operands through a buffer resource: the lane offset stays in a
     // register and the chunk offset is scalar; loads past the table return 0.
@@ -1438,199 +1607,215 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(W
         const_cast<void *>(a.split_ops), (short)0, a.n_supers * a.chunks_per_super * kSplitChunkBytes, kBufferWord3);
     const __amdgpu_buffer_rsrc_t super_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(a.supers), (short)0, a.n_supers * a.super_stride * 4, kBufferWord3);
-    // A super-tile holds at most 64 chunks (side <= 32): one chunk per lane.
-    const int ct = min(lane, a.chunks_per_super - 1);
-    const unsigned long long chunk_lanes =
-        a.chunks_per_super >= 64 ? ~0ull : (1ull << a.chunks_per_super) - 1;
-    const float zbox[6] = {zlo[0], zlo[1], zlo[2], zhi[0], zhi[1], zhi[2]};
+    // Chunk tests: a super-tile holds cps <= 64 chunks, so 64 lanes test
+    // 64 / cps super-tiles at once, lane sub * cps + ci chunk ci of the sub-th.
+    const int cps = a.chunks_per_super, per_test = a.supers_per_test;
+    const int sub = (int)((unsigned)lane * (unsigned)a.inv_chunks >> 16), ci = lane - sub * cps;   // lane / cps
+    const unsigned long long chunk_bits = cps >= 64 ? ~0ull : (1ull << cps) - 1;
+
     // Passes: the chunks whose bound v (relative to mmin) has vlo < v <= vhi
     // are evaluated; a pass that reaches skip_log2 is the last.
     const float nskip = -a.skip_log2;
     float vhi = INFINITY, vlo = -a.depth0;
     for (;;) {
-    const bool last = !(vlo > nskip);
-    const float svlo = fmaxf(nskip, vlo - kSuperMargin);
-    unsigned long long mass = 0;   // this lane's share of the skipped weight, 2^-kMassLog2 per node
-    // Super-tiles are tested one per lane; the kept ones are walked in order.
-    for (int g = w.s0; g < w.s1; g += 64) {
-      float rbox[6];
-      const int sl = g + lane;
-      const float sv = sl < w.s1 ? wave_super_bound(a, sl, zlo, zhi, rbox) - mmin : -INFINITY;
-      unsigned long long smask = __ballot(sv > svlo);
-      if (!last && sl < w.s1 && !(sv > svlo)) mass += (unsigned long long)mass_units(sv) * a.chunks_per_super;
-      if constexpr (WAVES < 6) {
-        // All waves of such a launch start together and the launch lasts as
-        // long as its busiest wave, whose work the count of super-tiles it
-        // keeps predicts: busier waves get the SIMD first (scheduling only).
-        // Thresholds at 1/3, 3/8 and 5/12 of the split's super-tiles; on
-        // 1080p frames with a 256^2 grid waves keeping 5/12 or more average
-        // twice the chunks of the median wave.
-        if (g == w.s0 && vhi == INFINITY) {
-          const int kept = 24 * __popcll(smask), n = w.s1 - w.s0;
-          if (kept >= 10 * n) __builtin_amdgcn_s_setprio(3);
-          else if (kept >= 9 * n) __builtin_amdgcn_s_setprio(2);
-          else if (kept >= 8 * n) __builtin_amdgcn_s_setprio(1);
-        }
-      }
-      while (smask) {
-        const int si = g + __builtin_ctzll(smask);
-        smask &= smask - 1;
-        const float *__restrict__ T = a.supers + (size_t)si * a.super_stride;
-        const float *__restrict__ C0 = T + kSupHdr + kMaxProbes * kProbeFloats;
-        // chunk tests, one chunk per lane (absolute boxes)
-        const float v = box_box_bound(C0 + (size_t)ct * kChunkFloats + 96, zbox) - mmin;
-        const unsigned long long mask = __builtin_amdgcn_ballot_w64(v > vlo && v <= vhi) & chunk_lanes;
-        if (!last && lane < a.chunks_per_super && !(v > vlo)) mass += mass_units(v);
-        if (mask == 0) continue;
-        const int kk = lk < 3 ? lk : 0;
-        const float ch = T[kk], cl = T[3 + kk];
-        bf16x8 av[PB];
-#pragma unroll
-        for (int b = 0; b < PB; ++b) {
-            const float r = (ah[b] - ch) + (al[b] - cl);
-            // |r|^2 + m over the pixel's four lanes (same value on each)
-            if constexpr (DFC) {
-                // as a double-float (plans near the precision budget)
-                float p, pe;
-                square_or(r, am[b], lk < 3, p, pe);
-#pragma unroll
-                for (int o = 16; o <= 32; o <<= 1) {
-                    const float q = __shfl_xor(p, o), qe = __shfl_xor(pe, o);
-                    float s, e;
-                    two_sum(p, q, s, e);
-                    p = s;
-                    pe = (pe + qe) + e;
+        const bool last = !(vlo > nskip);
+        const float svlo = fmaxf(nskip, vlo - kSuperMargin);
+        unsigned mass = 0;   // this lane's share of the skipped weight (saturating), 2^-kMassLog2 per chunk
+        for (int g = w.s0; g < w.s1;) {
+            // Super-tiles, one per lane; the kept ones are listed.
+            int K = 0;
+            while (g < w.s1) {
+                const float sv = super_bound(g + lane) - mmin;
+                const unsigned long long smask = __builtin_amdgcn_ballot_w64(sv > svlo);
+                const int n = __popcll(smask);
+                // the list holds 64; exact and no skipping take the same windows
+                if (K + n > 64 || (K > 0 && !a.list_across)) break;
+                if (!last && (NW == 1 || wave == 0) && g + lane < w.s1 && !(sv > svlo))
+                    mass = __builtin_elementwise_add_sat(mass, mass_units(sv) * (unsigned)cps);
+                const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(smask >> 32),
+                                                           __builtin_amdgcn_mbcnt_lo((unsigned)smask, 0));
+                if (sv > svlo) {   // every wave writes the same values
+                    sh.kept[K + rank].si = g + lane;
+                    sh.kept[K + rank].segment = __float_as_int(a.headers[(size_t)(g + lane) * kHdrFloats + 14]);
                 }
-                av[b] = split_pixel_operand(2.0f * r, -(p + pe), lk < 3);
-            } else {
-                float a2 = lk < 3 ? r * r : am[b];
-                a2 += __shfl_xor(a2, 16);
-                a2 += __shfl_xor(a2, 32);
-                av[b] = split_pixel_operand(2.0f * r, -a2, lk < 3);
+                K += n;
+                g += 64;
             }
-        }
-        float L0[PB], L1[PB], L2[PB];
-        const int s_first = si * a.chunks_per_super;   // first chunk of the super-tile in the split table
-        // byte offset of the first chunk's row coefficients in the super-tile table
-        const int c_first = (si * a.super_stride + kSupHdr + kMaxProbes * kProbeFloats + 104) * 4;
-        // Walk the kept chunks with two operand buffers: the next chunk's
-        // operands are in flight while the current one is evaluated.  The
-        // loads are issued unconditionally (the last chunk is simply loaded
-        // again), so the wait counts match on every path and a wait for the
-        // current chunk never waits for the next one.
-        unsigned long long walk = mask;
-        int tail = 0;
-        auto take = [&](bf16x8 &bv, f32x3 &qm) -> bool {
-            const bool got = walk != 0;
-            tail = got ? __builtin_ctzll(walk | (1ull << 63)) : tail;
-            walk &= walk - 1;
-            bv = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
-                                                split_rsrc, lane * kSplitLaneBytes,
-                                                (s_first + tail) * kSplitChunkBytes, 0));
-            qm = __builtin_bit_cast(f32x3, __builtin_amdgcn_raw_buffer_load_b96(
-                                               super_rsrc, lk * 16, c_first + tail * (kChunkFloats * 4), 0));
-            // keep these loads ahead of the evaluation that follows
-            __builtin_amdgcn_sched_barrier(0);
-            return got;
-        };
-        // Weights of the row's four nodes (SO2 offsets s = 0..3): their sum
-        // W0 and first moment W1 = sum s w_s give the row's Hb moment
-        // through the affine row coefficients, and W0 its THb moment (THb
-        // is constant along the row); HbO2 = THb - Hb after the super-tile.
-        // The first chunk of the super-tile starts the sums.
-        auto eval = [&](const bf16x8 &bv, const f32x3 &qm, auto first) {
-            ++executed;
-#pragma unroll
-            for (int b = 0; b < PB; ++b) {
-                const f32x4 d = mfma_16x16x32_bf16(bv, av[b], zero4);
-                const float w0 = __builtin_amdgcn_exp2f(d[0]), w1 = __builtin_amdgcn_exp2f(d[1]);
-                const float w2 = __builtin_amdgcn_exp2f(d[2]), w3 = __builtin_amdgcn_exp2f(d[3]);
-                const float W0 = (w0 + w1) + (w2 + w3);
-                const float W1 = fmaf(3.0f, w3, fmaf(2.0f, w2, w1));
-                if constexpr (decltype(first)::value) {
-                    L0[b] = W0;
-                    L1[b] = fmaf(qm.x, W0, qm.y * W1);
-                    L2[b] = qm.z * W0;
-                } else {
-                    L0[b] += W0;
-                    L1[b] = fmaf(qm.x, W0, fmaf(qm.y, W1, L1[b]));
-                    L2[b] = fmaf(qm.z, W0, L2[b]);
+            if (K == 0) break;
+            // Chunk tests of the kept super-tiles, 64 chunks at once.
+            for (int k0 = wave * per_test; k0 < K; k0 += NW * per_test) {
+                const int k = k0 + sub;
+                const bool real = sub < per_test && k < K;
+                const int si = sh.kept[real ? k : 0].si;
+                const float v = box_box_bound(a.boxes + ((size_t)si * cps + ci) * kBoxFloats, zbox) - mmin;
+                const unsigned long long kept = __builtin_amdgcn_ballot_w64(real && v > vlo && v <= vhi);
+                if (!last) mass = __builtin_elementwise_add_sat(mass, real && !(v > vlo) ? mass_units(v) : 0u);
+                if (real && ci == 0) {
+                    const unsigned long long bits = kept >> (sub * cps) & chunk_bits;
+                    sh.kept[k].lo = (unsigned)bits;
+                    sh.kept[k].hi = (unsigned)(bits >> 32);
                 }
             }
-        };
-        using First = std::true_type;
-        using Next = std::false_type;
-        // The mask holds at least one chunk: the first take gets it.
-        if constexpr (WAVES >= 6) {
-            bf16x8 bA, bB;
-            f32x3 qA, qB;
-            take(bA, qA);
-            bool more = take(bB, qB);
-            eval(bA, qA, First{});
-            while (more) {
-                const bool gotA = take(bA, qA);
-                eval(bB, qB, Next{});
-                if (!gotA) break;
-                more = take(bB, qB);
-                eval(bA, qA, Next{});
+            __syncthreads();
+            // Segments in turn (which wave sums a segment changes no bit).
+            const KeptSuper own = sh.kept[lane];
+            for (int seg = wave; seg < kSegments; seg += NW) {
+                unsigned long long list =
+                    __builtin_amdgcn_ballot_w64(lane < K && own.segment == seg && (own.lo | own.hi) != 0);
+                if (NW == 1 && list == 0) continue;
+                // Result layout: lane (lp, lk) holds pixel b*16 + lp and the
+                // four nodes of chunk row lk; its sums run over those nodes
+                // of every chunk of the segment, with Kahan compensation
+                // terms K0..K2 across super-tiles.
+                float R0[PB], R1[PB], R2[PB], K0[PB], K1[PB], K2[PB];
+#pragma unroll
+                for (int b = 0; b < PB; ++b) R0[b] = R1[b] = R2[b] = K0[b] = K1[b] = K2[b] = 0.0f;
+                for (; list; list &= list - 1) {
+                    const int k = __builtin_ctzll(list);
+                    unsigned long long walk = (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)own.hi, k) << 32 |
+                                              (unsigned)__builtin_amdgcn_readlane((int)own.lo, k);
+                    const int si = __builtin_amdgcn_readlane(own.si, k);
+                    executed += __popcll(walk);
+                    const int s_first = si * cps;   // first chunk of the super-tile in the split table
+                    // byte offset of the first chunk's row coefficients in the super-tile table
+                    const int c_first = (si * a.super_stride + kSupHdr + kMaxProbes * kProbeFloats + 104) * 4;
+                    // Walk the kept chunks with two operand buffers: the next chunk's
+                    // operands are in flight while the current one is evaluated.  The
+                    // loads are issued unconditionally (the last chunk is simply loaded
+                    // again), so the wait counts match on every path and a wait for the
+                    // current chunk never waits for the next one.
+                    int tail = 0;
+                    auto take = [&](bf16x8 &bv, f32x3 &qm) -> bool {
+                        const bool got = walk != 0;
+                        tail = got ? __builtin_ctzll(walk | (1ull << 63)) : tail;
+                        walk &= walk - 1;
+                        bv = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                                            split_rsrc, lane * kSplitLaneBytes,
+                                                            (s_first + tail) * kSplitChunkBytes, 0));
+                        qm = __builtin_bit_cast(f32x3, __builtin_amdgcn_raw_buffer_load_b96(
+                                                           super_rsrc, lk * 16, c_first + tail * (kChunkFloats * 4), 0));
+                        // keep these loads ahead of the evaluation that follows
+                        __builtin_amdgcn_sched_barrier(0);
+                        return got;
+                    };
+                    bf16x8 bA, bB;
+                    f32x3 qA, qB;
+                    take(bA, qA);   // the mask holds at least one chunk
+                    bool next = take(bB, qB);
+                    const float *__restrict__ H = a.headers + (size_t)si * kHdrFloats;
+                    const float ch = lk == 0 ? H[8] : (lk == 1 ? H[9] : H[10]);
+                    const float cl = lk == 0 ? H[11] : (lk == 1 ? H[12] : H[13]);
+                    bf16x8 av[PB];
+                    const float r[PB] = {(ah[0] - ch) + (al[0] - cl), (ah[1] - ch) + (al[1] - cl)};
+                    pixel_operands(r, am, std::integral_constant<bool, DFC>{}, av);
+                    float L0[PB], L1[PB], L2[PB];
+                    // Weights of the row's four nodes (SO2 offsets s = 0..3): their sum
+                    // W0 and first moment W1 = sum s w_s give the row's Hb moment
+                    // through the affine row coefficients, and W0 its THb moment (THb
+                    // is constant along the row); HbO2 = THb - Hb after the super-tile.
+                    // The first chunk of the super-tile starts the sums.
+                    auto eval = [&](const bf16x8 &bv, const f32x3 &qm, auto first_chunk) {
+#pragma unroll
+                        for (int b = 0; b < PB; ++b) {
+                            const f32x4 d = mfma_16x16x32_bf16(bv, av[b], zero4);
+                            const float w0 = __builtin_amdgcn_exp2f(d[0]), w1 = __builtin_amdgcn_exp2f(d[1]);
+                            const float w2 = __builtin_amdgcn_exp2f(d[2]), w3 = __builtin_amdgcn_exp2f(d[3]);
+                            const float W0 = (w0 + w1) + (w2 + w3);
+                            const float W1 = fmaf(3.0f, w3, fmaf(2.0f, w2, w1));
+                            if constexpr (decltype(first_chunk)::value) {
+                                L0[b] = W0;
+                                L1[b] = fmaf(qm.x, W0, qm.y * W1);
+                                L2[b] = qm.z * W0;
+                            } else {
+                                L0[b] += W0;
+                                L1[b] = fmaf(qm.x, W0, fmaf(qm.y, W1, L1[b]));
+                                L2[b] = fmaf(qm.z, W0, L2[b]);
+                            }
+                        }
+                    };
+                    using First = std::true_type;
+                    using Next = std::false_type;
+                    eval(bA, qA, First{});
+                    while (next) {
+                        const bool got = take(bA, qA);
+                        eval(bB, qB, Next{});
+                        if (!got) break;
+                        next = take(bB, qB);
+                        eval(bA, qA, Next{});
+                    }
+                    const float from_hb = H[6] - anc_hb, from_ox = H[7] - anc_ox;
+#pragma unroll
+                    for (int b = 0; b < PB; ++b) {
+                        kahan_add(R0[b], K0[b], L0[b]);
+                        kahan_add(R1[b], K1[b], fmaf(from_hb, L0[b], L1[b]));
+                        kahan_add(R2[b], K2[b], fmaf(from_ox, L0[b], L2[b] - L1[b]));   // HbO2 = THb - Hb
+                    }
+                }
+                // Sum over the four chunk-row lanes with compensated (two-sum)
+                // steps, both blocks at once: lane l < 32 ends up with pixel l.
+                auto close = [&](float x, float y, int q) {
+                    float t, e, f;
+                    swap_rows16(x, y);
+                    two_sum(x, y, t, e);
+                    x = y = t;
+                    f = e;
+                    swap_rows32(x, y);
+                    swap_rows32(e, f);
+                    float u, v;
+                    two_sum(x, y, u, v);
+                    const float err = (e + f) + v;
+                    if (lane < 32) {
+                        if constexpr (NW == 1) {
+                            float hi = sh.total[q][lane], lo = sh.total[3 + q][lane];
+                            carry_add(hi, lo, u, err);
+                            sh.total[q][lane] = hi;
+                            sh.total[3 + q][lane] = lo;
+                        } else {
+                            sh.part[seg][q][lane] = u;
+                            sh.part[seg][3 + q][lane] = err;
+                        }
+                    }
+                };
+                close(R0[0], R0[1], 0);
+                close(R1[0], R1[1], 1);
+                close(R2[0], R2[1], 2);
             }
-        } else {
-            // Fewer resident waves hide less latency: three buffers, two
-            // chunks' operands in flight.
-            bf16x8 bA, bB, bC;
-            f32x3 qA, qB, qC;
-            take(bA, qA);
-            bool gotB = take(bB, qB);
-            bool gotC = take(bC, qC);
-            eval(bA, qA, First{});
-            while (gotB) {
-                const bool gotA = take(bA, qA);
-                eval(bB, qB, Next{});
-                if (!gotC) break;
-                gotB = take(bB, qB);
-                eval(bC, qC, Next{});
-                if (!gotA) break;
-                gotC = take(bC, qC);
-                eval(bA, qA, Next{});
+            __syncthreads();   // the window's list is free again, its segments are summed
+            if constexpr (NW > 1) {
+                if (threadIdx.x < 3 * kTilePixels) {
+                    const int q = threadIdx.x / kTilePixels, i = threadIdx.x % kTilePixels;
+                    float hi = sh.total[q][i], lo = sh.total[3 + q][i];
+#pragma unroll
+                    for (int t = 0; t < kSegments; ++t) carry_add(hi, lo, sh.part[t][q][i], sh.part[t][3 + q][i]);
+                    sh.total[q][i] = hi;
+                    sh.total[3 + q][i] = lo;
+                }
+                __syncthreads();
             }
         }
-        const float chb = T[6], cox = T[7];
+        if (last) break;
+        // Certificate: the skipped weight, at most 2^skipped relative to mmin for
+        // every pixel of the tile, against the pixel's sum.  A NaN sum certifies
+        // itself: its maps are NaN whatever is kept.
 #pragma unroll
-        for (int b = 0; b < PB; ++b) {
-            kahan_add(R0[b], K0[b], L0[b]);
-            kahan_add(R1[b], K1[b], fmaf(chb - anc_hb[b], L0[b], L1[b]));
-            kahan_add(R2[b], K2[b], fmaf(cox - anc_ox[b], L0[b], L2[b] - L1[b]));   // HbO2 = THb - Hb
+        for (int o = 32; o >= 1; o >>= 1) mass = __builtin_elementwise_add_sat(mass, (unsigned)__shfl_xor((int)mass, o));
+        if constexpr (NW > 1) {
+            if (lane == 0) sh.mass[wave] = mass;
+            __syncthreads();
+            mass = sh.mass[0];
+#pragma unroll
+            for (int q = 1; q < NW; ++q) mass = __builtin_elementwise_add_sat(mass, sh.mass[q]);
         }
-      }
+        const float skipped = __log2f((float)mass) - kMassLog2;
+        const float held = (px < 16 ? am[0] : am[1]) + __log2f(sh.total[0][px] + sh.total[3][px]);
+        if (!__any(skipped > a.cert_log2 + (held - mmin))) break;
+        if constexpr (NW > 1) __syncthreads();   // sums and masses are read before the next pass writes
+        vhi = vlo;
+        vlo = fmaxf(nskip, vlo - kDepthStep);
     }
-    if (last) break;
-    // Certificate: the skipped weight, at most 2^skipped relative to mmin for
-    // every pixel of the wave, against the pixel's sum.  A NaN sum certifies
-    // itself: its maps are NaN whatever is kept.
-    float skipped = (float)mass;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) skipped += __shfl_xor(skipped, o);
-    skipped = __log2f(skipped) - kMassLog2;
-    bool short_of = false;
-#pragma unroll
-    for (int b = 0; b < PB; ++b) {
-        float s0 = R0[b] + __shfl_xor(R0[b], 16);
-        s0 += __shfl_xor(s0, 32);
-        short_of |= skipped > a.cert_log2 + ((am[b] + __log2f(s0)) - mmin);
-    }
-    if (!__any(short_of)) break;
-    vhi = vlo;
-    vlo = fmaxf(nskip, vlo - kDepthStep);
-    }
-
-    // Reduce over the four chunk-row lanes of each pixel with compensated
-    // (two-sum) pairwise steps, then lanes with lk == 0 write.
-#pragma unroll
-    for (int b = 0; b < PB; ++b) {
-        R0[b] = lane_sum_rows(R0[b]);
-        R1[b] = lane_sum_rows(R1[b]);
-        R2[b] = lane_sum_rows(R2[b]);
-    }
+    __syncthreads();
+    float S0 = sh.total[0][px] + sh.total[3][px];
+    const float m = (px < 16 ? am[0] : am[1]);
 
     // Pixels whose observation lies farther than sqrt(far_rho2) (scaled
     // units) from the grid's nodes: the expanded logit's terms grow with that
@@ -1640,88 +1825,73 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(W
     // = -(m + log2 S0), at most the nearest node's; with a split grid, also
     // that of the best probe of the whole grid (-gref): a split whose nodes
     // all lie far from an observation that lies close to others carries a
-    // negligible part of the posterior.
+    // negligible part of the posterior.  The tile's waves take the pixels in
+    // turn.
     unsigned far_pixels = 0;
-    static_assert(PW <= 64, "one mask bit per pixel of the wave");
-    unsigned long long far = 0;
     // Lane indices for what follows, formed here again rather than kept
     // across the main loop.
-    const int lane_e = opaque_v((int)threadIdx.x) & 63;
-    const int lp_e = lane_e & 15, lk_e = lane_e >> 4;
+    const int lane_e = opaque_v((int)threadIdx.x) & 63, px_e = lane_e & 31;
+    long long pe;
+    const bool valid = wave_pixel(a, w, px_e, pe);
+    unsigned long long far = __builtin_amdgcn_ballot_w64(lane_e < 32 && valid && m + __log2f(S0) < -a.far_rho2);
+    if (__builtin_expect(far != 0, 0)) {
+        // The pass reads the kernel's arguments again from the argument segment
+        // (PosteriorArgs is the kernel's only argument): keeping the values it
+        // needs live across the main loop would cost that loop registers.
+        KernArgs *ka = (KernArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+        for (int turn = 0; far != 0; ++turn) {
+            const int q = __builtin_ctzll(far);
+            far &= far - 1;
+            if (NW > 1 && turn % NW != wave) continue;
+            const PosteriorArgs fa = far_args(opaque(ka));
+            long long pq;
+            wave_pixel(fa, w, q, pq);
+            const float *zq = fa.z + (size_t)w.f * 6 * fa.LL;
+            float qh[3], qlo[3];
 #pragma unroll
-    for (int b = 0; b < PB; ++b) {
-        long long p;
-        const bool valid = wave_pixel(a, w, b * 16 + lp_e, p);
-        const float m = __shfl(ref.m, b * 16 + lp_e);
-        far |= (__ballot(lk_e == 0 && valid && m + __log2f(R0[b]) < -a.far_rho2) & 0xffffull) << (16 * b);
-    }
-    // The pass reads the kernel's arguments again from the argument segment
-    // (PosteriorArgs is the kernel's only argument): keeping the values it
-    // needs live across the main loop would cost that loop registers.
-    KernArgs *ka = (KernArgs *)__builtin_amdgcn_kernarg_segment_ptr();
-    while (__builtin_expect(far != 0, 0)) {
-        const PosteriorArgs fa = far_args(opaque(ka));
-        const int q = __builtin_ctzll(far);   // pixel q of the wave: block q / 16, row lane q % 16
-        far &= far - 1;
-        const int qb = q >> 4, ql16 = q & 15;
-        float xa = anc_hb[0], xo = anc_ox[0];
-#pragma unroll
-        for (int b = 1; b < PB; ++b)
-            if (qb == b) {
-                xa = anc_hb[b];
-                xo = anc_ox[b];
+            for (int k = 0; k < 3; ++k) load_obs(zq, fa.LL, pq, k, fa.scale, qh[k], qlo[k]);
+            const float mq = __shfl(m, q);
+            float m_skip = mq;
+            if (fa.gref) {
+                const float g = fa.gref[(size_t)w.f * fa.LL + pq];
+                if (!(g < -fa.far_rho2)) continue;
+                m_skip = fmaxf(m_skip, g);
             }
-        long long pq;
-        wave_pixel(fa, w, q, pq);
-        const float *zq = fa.z + (size_t)w.f * 6 * fa.LL;
-        float qh[3], qlo[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) load_obs(zq, fa.LL, pq, k, fa.scale, qh[k], qlo[k]);
-        const float mq = __shfl(ref.m, q);
-        float m_skip = mq;
-        if (fa.gref) {
-            const float g = fa.gref[(size_t)w.f * fa.LL + pq];
-            if (!(g < -fa.far_rho2)) continue;
-            m_skip = fmaxf(m_skip, g);
+            ++far_pixels;
+            float S[3];
+            far_pixel_sums(fa, w, qh, qlo, m_skip, -mq, anc_hb, anc_ox, S);
+            if (lane_e < 6)   // these replace the pixel's sums
+                sh.total[lane_e][q] = lane_e == 0 ? S[0] : (lane_e == 1 ? S[1] : (lane_e == 2 ? S[2] : 0.0f));
         }
-        ++far_pixels;
-        float S[3];
-        far_pixel_sums(fa, w, qh, qlo, m_skip, -mq, __shfl(xa, ql16), __shfl(xo, ql16), S);
-#pragma unroll
-        for (int b = 0; b < PB; ++b)
-            if (qb == b && lp_e == ql16) {
-                R0[b] = S[0];
-                R1[b] = S[1];
-                R2[b] = S[2];
-            }
+        __syncthreads();
+        S0 = sh.total[0][px_e] + sh.total[3][px_e];
     }
-    if (a.work && lane == 0) {
-        atomicAdd(a.work, (unsigned long long)executed * PW * kChunkNodes);
+    if (a.work && lane_e == 0) {
+        atomicAdd(a.work, (unsigned long long)executed * kTilePixels * kChunkNodes);
         if (far_pixels) atomicAdd(a.work + 1, (unsigned long long)far_pixels);
     }
+    const bool writer = wave == 0 && lane_e < 32 && valid;
     if (a.fuse) {
+        // one split: the estimate is anchor + S1 / S0
+        const float dh = sh.total[0][px_e], dl = sh.total[3][px_e];
+        const float ex = plus_quotient(anc_hb, sh.total[1][px_e], sh.total[4][px_e], dh, dl);
+        const float ey = plus_quotient(anc_ox, sh.total[2][px_e], sh.total[5][px_e], dh, dl);
+        if (writer) a.est[(size_t)w.f * a.LL + pe] = make_float2(ex, ey);
         switch (a.vec) {
-            case 4: fused_maps<PB, 4>(a, w, anc_hb, anc_ox, R0, R1, R2, lane_e); break;
-            case 2: fused_maps<PB, 2>(a, w, anc_hb, anc_ox, R0, R1, R2, lane_e); break;
-            default: fused_maps<PB, 1>(a, w, anc_hb, anc_ox, R0, R1, R2, lane_e); break;
+            case 4: fused_maps<NW, 4>(a, w, ex, ey, wave, lane_e); break;
+            case 2: fused_maps<NW, 2>(a, w, ex, ey, wave, lane_e); break;
+            default: fused_maps<NW, 1>(a, w, ex, ey, wave, lane_e); break;
         }
         return;
     }
-    float *out = a.part + ((size_t)w.f * a.split + w.split) * kPartFields * a.LL;
-#pragma unroll
-    for (int b = 0; b < PB; ++b) {
-        const int src = b * 16 + lp_e;
-        const float m = __shfl(ref.m, src);
-        long long p;
-        const bool valid = wave_pixel(a, w, src, p);
-        if (lk_e == 0 && valid) {
-            out[p] = m;
-            out[a.LL + p] = R0[b];
-            out[2 * a.LL + p] = R1[b];
-            out[3 * a.LL + p] = R2[b];
-            out[4 * a.LL + p] = anc_hb[b];
-            out[5 * a.LL + p] = anc_ox[b];
-        }
+    if (writer) {
+        float *out = a.part + ((size_t)w.f * a.split + w.split) * kPartFields * a.LL;
+        out[pe] = m;
+        out[a.LL + pe] = S0;
+        out[2 * a.LL + pe] = sh.total[1][px_e] + sh.total[4][px_e];
+        out[3 * a.LL + pe] = sh.total[2][px_e] + sh.total[5][px_e];
+        out[4 * a.LL + pe] = anc_hb;
+        out[5 * a.LL + pe] = anc_ox;
     }
 }
 
@@ -1736,7 +1906,7 @@ template <bool PRECISE>
 __global__ __launch_bounds__(kBlockThreads) void k_posterior_direct(PosteriorArgs a) {
     constexpr int PW = 64;
     const int lane = threadIdx.x & 63;
-    const WaveWork w = wave_work<PW>(a);
+    const WaveWork w = tile_work<PW>(a, xcd_order(blockIdx.x, gridDim.x, kResidentWaves / 4), threadIdx.x >> 6);
     if (w.r0 >= a.hl) return;   // a tile below the frame's last row holds no pixel
     const float *zf = a.z + (size_t)w.f * 6 * a.LL;
     long long p;
@@ -1993,27 +2163,43 @@ hipError_t launch_reference(const PosteriorArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
+namespace {
+
+template <int NW>
+void launch_mfma(const PosteriorArgs &a, long long tiles, hipStream_t s) {
+    const dim3 g((unsigned)tiles), blk(64 * NW);
+    if (a.dfc)
+        hipLaunchKernelGGL((k_posterior<NW, true>), g, blk, 0, s, a);
+    else
+        hipLaunchKernelGGL((k_posterior<NW, false>), g, blk, 0, s, a);
+}
+
+}  // namespace
+
 hipError_t launch_posterior(const PosteriorArgs &a, bool mfma, hipStream_t s) {
-    const int th = (mfma ? 16 * kPixelBlocks : 64) / kWaveTileW;
+    const int th = (mfma ? kTilePixels : 64) / kWaveTileW;
     const long long per_frame = (long long)((a.wl + kWaveTileW - 1) / kWaveTileW) * ((a.hl + 4 * th - 1) / (4 * th));
     const long long grid = per_frame * a.n_frames * a.split;
     if (grid <= 0) return hipSuccess;
-    // A launch whose workgroups are all resident at once runs about four
-    // waves per SIMD: the variant built for four keeps more loads in flight
-    // (same arithmetic, same bits).
-    const dim3 g((unsigned)grid), blk(kBlockThreads);
-    if (mfma && grid <= kResidentGroups && a.dfc)
-        hipLaunchKernelGGL((k_posterior<kPixelBlocks, 4, true>), g, blk, 0, s, a);
-    else if (mfma && grid <= kResidentGroups)
-        hipLaunchKernelGGL((k_posterior<kPixelBlocks, 4, false>), g, blk, 0, s, a);
-    else if (mfma && a.dfc)
-        hipLaunchKernelGGL((k_posterior<kPixelBlocks, 6, true>), g, blk, 0, s, a);
-    else if (mfma)
-        hipLaunchKernelGGL((k_posterior<kPixelBlocks, 6, false>), g, blk, 0, s, a);
-    else if (a.precise)
+    if (mfma) {
+        const long long tiles = 4 * grid;
+        // Tiles that would all be resident at once with one wave each: the
+        // launch would last as long as its busiest tile (2.3 times the mean on
+        // 1080p frames), and four waves a tile share that out.  One 640x480
+        // frame (600 tiles, 256 x 256 grid): 221 us a call with one wave, 137
+        // with two, 88 with four; one 1080p frame (4080 tiles): 216, 209 and 194.
+        // More tiles keep the chip full by themselves, and the waves of a tile
+        // repeat its set-up: 9600 tiles (128 x 128 grid) 210, 211 and 228 us,
+        // 20480 tiles 282, 315 and 367.
+        if (tiles <= kResidentWaves)
+            launch_mfma<4>(a, tiles, s);
+        else
+            launch_mfma<1>(a, tiles, s);
+    } else if (a.precise) {
         hipLaunchKernelGGL(k_posterior_direct<true>, dim3((unsigned)grid), dim3(kBlockThreads), 0, s, a);
-    else
+    } else {
         hipLaunchKernelGGL(k_posterior_direct<false>, dim3((unsigned)grid), dim3(kBlockThreads), 0, s, a);
+    }
     return hipGetLastError();
 }
 

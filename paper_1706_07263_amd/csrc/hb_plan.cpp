@@ -45,6 +45,9 @@ struct hb_plan_s {
     float *d_tiles = nullptr;   // super-tile table
     float *d_lo = nullptr;      // low parts of the node coordinates (double-float direct logits)
     void *d_split = nullptr;    // split bf16 A operands of the chunks
+    float *d_tests = nullptr;   // MFMA kernel: headers and boxes of its tests
+    void *d_probes = nullptr;   // MFMA kernel: split bf16 operands of the probes
+    size_t boxes_at = 0;        // floats
     float *d_z = nullptr;
     float2 *d_det = nullptr;
     float *d_part = nullptr;
@@ -158,7 +161,7 @@ int auto_split(const Dims &dm, int n_tiles, int max_batch) {
     // (600 waves) to 3840x2160.  The split is fixed per plan, so a frame gives
     // the same bits in any batch.
     constexpr long long kMinWaves = 256;
-    const long long per_wave = 16LL * kPixelBlocks;
+    const long long per_wave = kTilePixels;
     const long long waves = std::max(1LL, ((long long)max_batch * dm.LL + per_wave - 1) / per_wave);
     int s = 1;
     while (s < 64 && waves * s < kMinWaves) s *= 2;
@@ -181,6 +184,8 @@ void free_plan(hb_plan_s *p) {
     (void)hipFree(p->d_tiles);
     (void)hipFree(p->d_lo);
     (void)hipFree(p->d_split);
+    (void)hipFree(p->d_tests);
+    (void)hipFree(p->d_probes);
     (void)hipFree(p->d_z);
     (void)hipFree(p->d_det);
     (void)hipFree(p->d_part);
@@ -433,34 +438,89 @@ void split3(float x, uint16_t p[3]) {
     p[2] = bf16_nearest(r2);
 }
 
-// Split bf16 A operands of every chunk from the FP32 coordinates and
-// squared-norm entries of the super-tile table (layout in hb_internal.h).
+// Split bf16 A operand of 16 nodes from C, [coordinate or squared-norm
+// entry][node] (layout in hb_internal.h).
+void split_block(const float *C, uint16_t *O) {
+    constexpr int kLaneHalves = kSplitLaneBytes / 2;
+    for (int g = 0; g < 4; ++g)
+        for (int i = 0; i < 16; ++i) {
+            uint16_t *L = O + (size_t)(16 * g + i) * kLaneHalves;
+            uint16_t v[3];
+            split3(C[16 * g + i], v);   // g = 3: the squared-norm entry
+            if (g < 3) {
+                const int order[8] = {0, 1, 0, 2, 1, 0, 2, 1};
+                for (int e = 0; e < 8; ++e) L[e] = v[order[e]];
+            } else {
+                const uint16_t one = bf16_nearest(1.0f);
+                for (int e = 0; e < 3; ++e) {
+                    L[e] = v[e];
+                    L[3 + e] = one;   // picks up the pixel's constant
+                }
+            }
+        }
+}
+
+// Split bf16 A operands of every chunk of the super-tile table.
 void build_split_ops(const std::vector<float> &table, int n_sup, int side, std::vector<uint16_t> &ops) {
     const int stride = super_floats(side);
     const int n_chunks = (side / 4) * (side / 4);
     constexpr int kLaneHalves = kSplitLaneBytes / 2;
     ops.assign((size_t)n_sup * n_chunks * 64 * kLaneHalves, 0);
     for (int si = 0; si < n_sup; ++si)
-        for (int c = 0; c < n_chunks; ++c) {
-            const float *C = &table[(size_t)si * stride + kSupHdr + kMaxProbes * kProbeFloats + (size_t)c * kChunkFloats];
-            uint16_t *O = &ops[((size_t)si * n_chunks + c) * 64 * kLaneHalves];
-            for (int g = 0; g < 4; ++g)
-                for (int i = 0; i < 16; ++i) {
-                    uint16_t *L = O + (size_t)(16 * g + i) * kLaneHalves;
-                    uint16_t v[3];
-                    split3(C[16 * g + i], v);   // g = 3: the squared-norm entry
-                    if (g < 3) {
-                        const int order[8] = {0, 1, 0, 2, 1, 0, 2, 1};
-                        for (int e = 0; e < 8; ++e) L[e] = v[order[e]];
-                    } else {
-                        const uint16_t one = bf16_nearest(1.0f);
-                        for (int e = 0; e < 3; ++e) {
-                            L[e] = v[e];
-                            L[3 + e] = one;   // picks up the pixel's constant
-                        }
-                    }
-                }
+        for (int c = 0; c < n_chunks; ++c)
+            split_block(&table[(size_t)si * stride + kSupHdr + kMaxProbes * kProbeFloats + (size_t)c * kChunkFloats],
+                        &ops[((size_t)si * n_chunks + c) * 64 * kLaneHalves]);
+}
+
+// Test tables of the MFMA kernel (layout in hb_internal.h) from the
+// super-tile table; `out` holds headers and boxes one after the other.
+void build_test_tables(const std::vector<float> &table, int n_sup, int columns, int side, size_t boxes_at,
+                       std::vector<float> &out, std::vector<uint16_t> &probes) {
+    const int stride = super_floats(side), cps = (side / 4) * (side / 4), slots = probe_slots(side);
+    constexpr int kLaneHalves = kSplitLaneBytes / 2;
+    out.assign(boxes_at + (size_t)n_sup * cps * kBoxFloats, 0.0f);
+    const size_t n_blocks = ((size_t)n_sup * slots + 15) / 16;
+    std::vector<float> v(n_blocks * 64, 0.0f);   // [block][coordinate or norm][probe]
+    for (size_t b = 0; b < n_blocks; ++b)
+        for (int i = 0; i < 16; ++i) v[b * 64 + 48 + i] = kPadLogit;
+    for (int si = 0; si < n_sup; ++si) {
+        const float *T = &table[(size_t)si * stride];
+        float *H = &out[(size_t)si * kHdrFloats];
+        for (int k = 0; k < 3; ++k) {
+            H[k] = INFINITY;
+            H[3 + k] = -INFINITY;
+            H[8 + k] = T[k];
+            H[11 + k] = T[3 + k];
         }
+        H[6] = T[6];
+        H[7] = T[7];
+        const int segment = (si % columns + si / columns) % kSegments;
+        std::memcpy(&H[14], &segment, sizeof(int));
+        for (int c = 0; c < cps; ++c) {
+            const float *C = T + kSupHdr + kMaxProbes * kProbeFloats + (size_t)c * kChunkFloats;
+            float *X = &out[boxes_at + ((size_t)si * cps + c) * kBoxFloats];
+            for (int k = 0; k < 3; ++k) {
+                X[k] = C[96 + k];
+                X[3 + k] = C[99 + k];
+                H[k] = std::min(H[k], X[k]);
+                H[3 + k] = std::max(H[3 + k], X[3 + k]);
+            }
+        }
+        int np;
+        std::memcpy(&np, &T[14], sizeof(int));
+        for (int i = 0; i < np; ++i) {
+            const size_t at = (size_t)si * slots + i;
+            double sq = 0;
+            for (int k = 0; k < 3; ++k) {
+                const float x = (float)((double)T[k] + (double)T[3 + k] + (double)T[kSupHdr + i * kProbeFloats + k]);
+                v[at / 16 * 64 + 16 * k + at % 16] = x;
+                sq += (double)x * (double)x;
+            }
+            v[at / 16 * 64 + 48 + at % 16] = (float)-sq;
+        }
+    }
+    probes.assign(n_blocks * 64 * kLaneHalves, 0);
+    for (size_t b = 0; b < n_blocks; ++b) split_block(&v[b * 64], &probes[b * 64 * kLaneHalves]);
 }
 
 // Per-call device buffers of hb_estimate_frames: the plan's own, or carved
@@ -550,6 +610,14 @@ hb_status_t estimate(hb_plan_s *p, const void *d_frames, int32_t n_frames, const
         pa.n_supers = p->n_tiles;
         pa.super_stride = super_floats(p->side);
         pa.chunks_per_super = (p->side / 4) * (p->side / 4);
+        pa.headers = p->d_tests;
+        pa.boxes = p->d_tests + p->boxes_at;
+        pa.probes = p->d_probes;
+        pa.probe_shift = probe_shift(p->side);
+        pa.supers_per_test = 64 / pa.chunks_per_super;
+        pa.inv_chunks = (65536 + pa.chunks_per_super - 1) / pa.chunks_per_super;
+        // exact and no skipping go through the same windows
+        pa.list_across = p->desc.posterior_tolerance > 0 ? 1 : 0;
         pa.split = p->split;
         pa.scale = p->scale;
         pa.skip_log2 = p->skip_log2;
@@ -700,6 +768,12 @@ hb_status_t hb_plan_create(const hb_plan_desc_t *desc, int device, hb_plan_t *ou
     if (st == HB_OK) st = dev_alloc(p, (void **)&p->d_tiles, sizeof(float) * (size_t)p->n_tiles * super_floats(p->side));
     if (st == HB_OK)
         st = dev_alloc(p, &p->d_split, (size_t)kSplitChunkBytes * p->n_tiles * (p->side / 4) * (p->side / 4));
+    {
+        const size_t n = (size_t)p->n_tiles, cps = (size_t)(p->side / 4) * (p->side / 4);
+        p->boxes_at = n * kHdrFloats;
+        if (st == HB_OK) st = dev_alloc(p, (void **)&p->d_tests, sizeof(float) * (p->boxes_at + n * cps * kBoxFloats));
+        if (st == HB_OK) st = dev_alloc(p, &p->d_probes, (n * probe_slots(p->side) + 15) / 16 * kSplitChunkBytes);
+    }
     if (st == HB_OK)
         st = dev_alloc(p, (void **)&p->d_lo, sizeof(float) * kLoFloats * p->n_tiles * (p->side / 4) * (p->side / 4));
     if (st == HB_OK) st = dev_alloc(p, (void **)&p->d_z, sizeof(float) * nb * 6 * LL);
@@ -863,6 +937,12 @@ hb_status_t hb_set_forward_model(hb_plan_t p, const hb_forward_model_t *fm) {
     if (hipMemcpy(p->d_tiles, tiles.data(), sizeof(float) * tiles.size(), hipMemcpyHostToDevice) != hipSuccess)
         return HB_ERR_DEVICE;
     if (hipMemcpy(p->d_lo, lo.data(), sizeof(float) * lo.size(), hipMemcpyHostToDevice) != hipSuccess)
+        return HB_ERR_DEVICE;
+    std::vector<float> tests;
+    std::vector<uint16_t> probes;
+    build_test_tables(tiles, p->n_tiles, (d.grid_so2 + p->side - 1) / p->side, p->side, p->boxes_at, tests, probes);
+    if (hipMemcpy(p->d_tests, tests.data(), sizeof(float) * tests.size(), hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(p->d_probes, probes.data(), sizeof(uint16_t) * probes.size(), hipMemcpyHostToDevice) != hipSuccess)
         return HB_ERR_DEVICE;
     std::vector<uint16_t> split_ops;
     build_split_ops(tiles, p->n_tiles, p->side, split_ops);

@@ -516,6 +516,26 @@ def test_certified_skipping_stays_within_its_bound(torch_cuda, gt, gs, levels, i
     assert diff <= bound + 2e-5
 
 
+@pytest.mark.parametrize("h,w,levels,gt,gs", [(2, 2, 1, 40, 40), (10, 18, 1, 75, 100), (9, 7, 0, 170, 200),
+                                              (12, 40, 2, 300, 280), (24, 16, 2, 33, 260)])
+def test_tile_kernel_edges(torch_cuda, h, w, levels, gt, gs):
+    """Frames smaller than a tile or ragged against it; super-tiles of 1, 4,
+    9, 25 and 64 chunks, ragged against the grid, up to 90 of them (more than
+    one list of 64): no and exact skipping agree bit for bit, a frame gives
+    the same bits alone and in a batch, and the maps match the oracle."""
+    frames = np.stack([synth.single_frame(h, w, config=65, stream=i)[0] for i in range(3)])
+    s = dict(_settings(levels=levels, grid=gt), grid_thb=gt, grid_so2=gs)
+    out = {}
+    for t in (-1.0, 0.0, 1e-6):
+        run = hbtest.GpuRun(w, h, dict(s, posterior_tolerance=t), max_batch=3, grid_split=1)
+        assert run.plan.info()["posterior_kernel"] == "mfma"
+        out[t] = run(frames)
+        assert np.array_equal(run(frames[1:2])[0], out[t][1], equal_nan=True)
+        run.close()
+    assert np.array_equal(out[-1.0], out[0.0], equal_nan=True)
+    hbtest.assert_maps_close(out[1e-6], hbtest.run_oracle(frames, "f32", s), f"{h}x{w} L{levels} {gt}x{gs}")
+
+
 @pytest.mark.parametrize("levels", [0, 1, 2])
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("camera", ["default", "shifted"])
