@@ -176,11 +176,16 @@ constexpr int kStripPixels = 2048;
 constexpr int kBlockThreads = 256;
 
 // Tables of the MFMA kernel's tests, derived from the super-tile table:
+//   axes     3 x 3 rotation (rows: unit vectors) along which the boxes lie:
+//            the principal directions of the differences between neighbouring
+//            nodes, the strongest last.  The nodes form a surface, so boxes
+//            along these axes are thin in one direction (kept chunks 3% fewer
+//            on 1080p frames than with boxes along the channels)
 //   headers  [super][kHdrFloats]: absolute box lower corner (3), upper corner
-//            (3), Hb and HbO2 of the centre, centre high parts (3), low parts
+//            (3) along the axes, Hb and HbO2 of the centre, centre high parts (3), low parts
 //            (3), segment (int bits)
-//   boxes    [chunk][kBoxFloats]: the chunk's absolute box, lower corner (3)
-//            and upper corner (3), rounded outward
+//   boxes    [chunk][kBoxFloats]: the chunk's absolute box along the axes,
+//            lower corner (3) and upper corner (3), rounded outward
 //   probes   split operands (as the chunks') of 16 probes each in absolute
 //            coordinates, probe_slots(side) per super-tile; slots without a
 //            probe have the logit kPadLogit
@@ -191,10 +196,15 @@ constexpr int kBoxFloats = 8;
 inline int probe_shift(int side) { return side <= 8 ? 0 : (side <= 16 ? 2 : 4); }
 inline int probe_slots(int side) { return 1 << probe_shift(side); }   // ceil(side / 8)^2 and more
 
-// LL pixels of one tile of the MFMA kernel (8 x 4, two MFMA blocks of 16).
+// LL pixels of one tile of the MFMA kernel (two MFMA blocks of 16).
 // Each chunk's 1 KB split operand is loaded once and used for both blocks;
 // larger tiles would share it further but keep more chunks.
 constexpr int kTilePixels = 32;
+// A workgroup of the MFMA kernel takes a region of LL pixels, deals them to
+// its tiles by observation and writes the region's maps.
+constexpr int kRegionW = 16, kRegionH = 8;
+constexpr int kRegionPixels = kRegionW * kRegionH;
+constexpr int kRegionTiles = kRegionPixels / kTilePixels;
 // The super-tiles are dealt to kSegments segments (row + column of the
 // super-tile, modulo the count), each with its own sums, which 1, 2 or 4 waves
 // evaluate: the segments and the order in which they are merged do not depend
@@ -250,7 +260,8 @@ struct PosteriorArgs {
     int band_chunks;         // budget: chunks a wave may skip between band_log2 and skip_log2
     float *gref;             // [n][LL] best probe logit over the whole grid, or null (one split)
     float *part;             // [n][split][kPartFields][LL]
-    const float *headers;    // MFMA kernel: test tables (see kHdrFloats)
+    float axes[9];           // MFMA kernel: axes and tables of its tests (see kHdrFloats)
+    const float *headers;
     const float *boxes;
     const void *probes;
     int probe_shift;         // log2 of the probe slots of a super-tile

@@ -815,14 +815,15 @@ constexpr int kXcds = 8;   // accelerator complex dies of an MI355X, each with i
 constexpr int kResidentWaves = 256 * 4 * 6;
 constexpr int kOrderSquare = 8;
 
-// A wave takes a compact 8-wide tile of LL pixels (PW / 8 rows), four waves
-// of a workgroup stack vertically; compact tiles keep the wave's observations
-// close together, which is what the skipping test below relies on.
+// A wave of the direct kernel takes a compact 8-wide tile of LL pixels
+// (PW / 8 rows), four waves of a workgroup stack vertically; compact tiles
+// keep the wave's observations close together, which is what the skipping
+// test below relies on.
 constexpr int kWaveTileW = 8;
 
 struct WaveWork {
     int f, split, s0, s1;
-    int r0, c0;  // wave tile origin in LL pixels
+    int r0, c0;  // origin of the wave's tile (of the workgroup's region) in LL pixels
 };
 
 // (p, pe) = r^2 exactly (product and its FMA residual) if sq, else (m, 0).
@@ -845,17 +846,15 @@ __device__ __forceinline__ int xcd_order(int bid, int n, int resident) {
     return n > resident && bid < per_xcd * kXcds ? (bid % kXcds) * per_xcd + bid / kXcds : bid;
 }
 
-// Work number `sub` of four vertically stacked tiles of PW pixels (kWaveTileW
-// wide) in group `idx`.
-template <int PW>
-__device__ __forceinline__ WaveWork tile_work(const PosteriorArgs &a, int idx, int sub) {
-    constexpr int TH = PW / kWaveTileW;
+// Block number idx of BW x BH LL pixels (and its grid split).
+template <int BW, int BH>
+__device__ __forceinline__ WaveWork block_work(const PosteriorArgs &a, int idx) {
     WaveWork w;
     const int S = a.split;
     w.split = idx % S;
     const int chunk = idx / S;
-    const int bcols = (a.wl + kWaveTileW - 1) / kWaveTileW;
-    const int brows = (a.hl + 4 * TH - 1) / (4 * TH);
+    const int bcols = (a.wl + BW - 1) / BW;
+    const int brows = (a.hl + BH - 1) / BH;
     const int per_frame = bcols * brows;
     w.f = chunk / per_frame;
     const int t = chunk % per_frame;
@@ -875,8 +874,8 @@ __device__ __forceinline__ WaveWork tile_work(const PosteriorArgs &a, int idx, i
         br = o / wl;
         bc = full * kOrderSquare + o % wl;
     }
-    w.r0 = (band * kOrderSquare + br) * 4 * TH + sub * TH;
-    w.c0 = bc * kWaveTileW;
+    w.r0 = (band * kOrderSquare + br) * BH;
+    w.c0 = bc * BW;
     w.s0 = S == 1 ? 0 : (int)((long long)a.n_supers * w.split / S);
     w.s1 = S == 1 ? a.n_supers : (int)((long long)a.n_supers * (w.split + 1) / S);
     return w;
@@ -888,6 +887,11 @@ __device__ __forceinline__ bool wave_pixel(const PosteriorArgs &a, const WaveWor
     const bool valid = r < a.hl && c < a.wl;
     p = (long long)min(r, a.hl - 1) * a.wl + min(c, a.wl - 1);
     return valid;
+}
+
+// LL index of pixel i of the workgroup's region.
+__device__ __forceinline__ long long region_pixel(const PosteriorArgs &a, const WaveWork &w, int i) {
+    return (long long)(w.r0 + i / kRegionW) * a.wl + w.c0 + i % kRegionW;
 }
 
 // Scaled double-float observation of LL pixel p, channel k.
@@ -1138,20 +1142,21 @@ __global__ __launch_bounds__(kBlockThreads) void k_reference(PosteriorArgs a) {
     a.gref[i] = mlo;
 }
 
-// Exact maximum logit over the nodes of the chunks a wave keeps (the same
-// super-tile and chunk tests as the main loop), difference form; each pixel's
-// LPP lanes split every chunk's nodes.  Returns max(current, that maximum).
-template <int PW, int LPP>
+// Exact maximum logit over the nodes of the chunks a wave may keep, difference
+// form; each pixel's LPP lanes split every chunk's nodes.  super_test(si) and
+// chunk_test(si, c) are the bounds of the main loop's own tests (one
+// super-tile or chunk per lane): a chunk that the loop evaluates but this scan
+// leaves out could hold weights that overflow relative to the result.
+// Returns max(current, that maximum).
+template <int PW, int LPP, typename SuperTest, typename ChunkTest>
 __device__ float far_gap_max(const PosteriorArgs &a, const WaveWork &w, const float ph[3], const float pl[3],
-                             int part, const float zlo[3], const float zhi[3], float mmin, float cur) {
+                             int part, SuperTest super_test, ChunkTest chunk_test, float mmin, float cur) {
     const int lane = threadIdx.x & 63;
     const float nskip = -a.skip_log2;
-    const float zbox[6] = {zlo[0], zlo[1], zlo[2], zhi[0], zhi[1], zhi[2]};
     float mx = cur;
     for (int g = w.s0; g < w.s1; g += 64) {
-        float rbox[6];
         const int sl = g + lane;
-        unsigned long long smask = __ballot(sl < w.s1 && wave_super_bound(a, sl, zlo, zhi, rbox) - mmin > nskip);
+        unsigned long long smask = __ballot(sl < w.s1 && super_test(sl) - mmin > nskip);
         while (smask) {
             const int si = g + __builtin_ctzll(smask);
             smask &= smask - 1;
@@ -1161,8 +1166,8 @@ __device__ float far_gap_max(const PosteriorArgs &a, const WaveWork &w, const fl
             const float *__restrict__ C0 = T + kSupHdr + kMaxProbes * kProbeFloats;
             for (int cg = 0; cg < a.chunks_per_super; cg += 64) {
                 const int ct = min(cg + lane, a.chunks_per_super - 1);
-                unsigned long long mask = __ballot(cg + lane < a.chunks_per_super &&
-                                                   box_box_bound(C0 + (size_t)ct * kChunkFloats + 96, zbox) - mmin > nskip);
+                unsigned long long mask =
+                    __ballot(cg + lane < a.chunks_per_super && chunk_test(si, ct) - mmin > nskip);
                 while (mask) {
                     const float *__restrict__ C = C0 + (size_t)(cg + __builtin_ctzll(mask)) * kChunkFloats;
                     mask &= mask - 1;
@@ -1179,32 +1184,35 @@ __device__ float far_gap_max(const PosteriorArgs &a, const WaveWork &w, const fl
     return mx;
 }
 
-// Fused recomposition for one split and n <= 2: lane l (and l + 32) holds the
-// estimate of the tile's pixel l.  The tile's waves write the maps of its
-// (4 x 2^n) x (8 x 2^n) pixels in units of V along a row: the unit's estimate
-// is fetched from its pixel's lane (uniform trip count) before any lane
-// branches.
-template <int NW, int V>
-__device__ __forceinline__ void fused_maps(const PosteriorArgs &a, const WaveWork &w, float ex, float ey, int wave,
-                                           int lane) {
+// Fused recomposition for one split and n <= 2, in units of V pixels along a
+// row, from the estimates of the region's pixels: the maps of the whole region,
+// (8 x 2^n) x (16 x 2^n) pixels, or (RT == 1) those of the 32 pixels of one tile.
+template <int RT, int V>
+__device__ __forceinline__ void fused_maps(const PosteriorArgs &a, const WaveWork &w, const float2 *est,
+                                           const int *tile_slot, int tile_valid) {
+    constexpr int kLogV = V == 4 ? 2 : (V == 2 ? 1 : 0);
     const int n = a.levels, B = 1 << n;
-    const int per_row = (kWaveTileW * B) / V;             // units per tile row
-    const int n_units = (kTilePixels / kWaveTileW) * B * per_row;
-    const int T = (n_units + 64 * NW - 1) / (64 * NW);     // same for every lane
-    for (int t = 0; t < T; ++t) {
-        const int u = lane + 64 * (wave + NW * t);
-        const bool live = u < n_units;
-        const int y = live ? u / per_row : 0, x = live ? (u - y * per_row) * V : 0;
-        const int ty = y >> n, tx = x >> n;
-        const int i = ty * kWaveTileW + tx;                 // LL pixel of the tile
-        const float2 e = make_float2(__shfl(ex, i), __shfl(ey, i));
-        const int gr = w.r0 + ty, gc = w.c0 + tx;
-        if (!live || gr >= a.hl || gc >= a.wl) continue;
-        const size_t o = ((size_t)w.f * a.H + ((size_t)gr << n) + (y & (B - 1))) * a.W + ((size_t)gc << n) +
-                         (x & (B - 1));
+    const int n_units = ((RT == 1 ? tile_valid : kRegionPixels) << 2 * n) >> kLogV;
+    for (int u = threadIdx.x; u < n_units; u += blockDim.x) {
+        int i, y, x;   // pixel of the region, offset in its block
+        if constexpr (RT == 1) {
+            const int o = u & ((1 << (2 * n - kLogV)) - 1);
+            i = tile_slot[u >> (2 * n - kLogV)];
+            y = o >> (n - kLogV);
+            x = (o << kLogV) & (B - 1);
+        } else {
+            const int row_shift = 4 + n - kLogV;   // log2 of the units of a region row
+            const int Y = u >> row_shift, X = (u << kLogV) & ((kRegionW << n) - 1);
+            i = (Y >> n) * kRegionW + (X >> n);
+            y = Y & (B - 1);
+            x = X & (B - 1);
+        }
+        const int gr = w.r0 + i / kRegionW, gc = w.c0 + i % kRegionW;
+        if (gr >= a.hl || gc >= a.wl) continue;
+        const size_t o = ((size_t)w.f * a.H + ((size_t)gr << n) + y) * a.W + ((size_t)gc << n) + x;
         float2 dp[V];
         load_detail<V>(a.det, o, dp);
-        write_maps<V>(a.hb, a.hbo2, a.thb, a.so2, a.thb_eps, o, e, dp);
+        write_maps<V>(a.hb, a.hbo2, a.thb, a.so2, a.thb_eps, o, est[i], dp);
     }
 }
 
@@ -1347,7 +1355,8 @@ __device__ __forceinline__ void far_pixel_sums(const PosteriorArgs &a, const Wav
     for (int k = 0; k < 3; ++k) S[k] = x[k] + e[k];
 }
 
-// MFMA kernel: NW waves take a tile of 32 LL pixels, two blocks of 16.  Per
+// MFMA kernel: NW waves take a tile of 32 LL pixels, two blocks of 16; a
+// workgroup takes RT tiles of a region of 128 pixels (all four, or one).  Per
 // super-tile, 16-node chunk and pixel block one v_mfma_f32_16x16x32_bf16 forms
 // the 16 x 16 logits
 //   t - m = [v_g, -|v_g|^2, 1] . [2 r, 1, -(|r|^2 + m)]
@@ -1360,16 +1369,18 @@ __device__ __forceinline__ void far_pixel_sums(const PosteriorArgs &a, const Wav
 //
 // The tile's reference, its chunk tests and its kept chunks are shared out
 // between its waves; what is kept, the segments and their sums are the same
-// for any NW.  DFC: the pixel operand's constant |r|^2 + m summed as a
+// for any NW and RT.  DFC: the pixel operand's constant |r|^2 + m summed as a
 // double-float (plans near the precision budget).
 //
-// Bound by VALU issue: 97% busy on sixteen 1080p frames (256 x 256 grid), 14
+// Bound by VALU issue: 96% busy on sixteen 1080p frames (256 x 256 grid), 14
 // instructions (one MFMA and four exponentials among them) per 256 pairs and
-// about 3000 per tile around them (14250 in all).  Six waves per SIMD (80
-// VGPRs; spills outside the chunk loop only) measured fastest.  Times a call,
-// one wave per tile throughout -> this: 640x480 frame 224 -> 88 us, 1080p
-// frame 223 -> 194, 64x64 frame on a 32 x 32 grid 87 -> 73, sixteen 1080p
-// frames 2391 -> 2308, 1280x1024 pair on a 512 x 512 grid 2999 -> 2784.
+// about 3100 per tile around them (12460 in all).  Six waves per SIMD (80
+// VGPRs; spills outside the chunk loop only).  Times a call with tiles of 8 x 4
+// neighbours and boxes along the channels -> tiles of like observations and
+// boxes along the nodes' axes: sixteen 1080p frames 2274 -> 1976 us, 1280x1024
+// pair on a 512 x 512 grid 2794 -> 2470, 1280x1024 frame at level 0 with the
+// illumination term 1198 -> 1049, sixteen 320x240 frames 205 -> 165, one
+// 640x480 frame 85 -> 72.
 struct KeptSuper {
     unsigned lo, hi;   // kept chunks of the super-tile, one bit each
     int si, segment;
@@ -1384,6 +1395,29 @@ struct TileShared {
     float best[NW][kTilePixels];
     unsigned mass[NW];
 };
+
+template <int NW, int RT>
+struct RegionShared {
+    TileShared<NW> tile[RT];
+    float obs[6][kRegionPixels];        // scaled observation, high and low parts
+    float rot[3][kRegionPixels];        // the same along the boxes' axes
+    unsigned key[kRegionPixels];
+    int rank[kRegionPixels];
+    int slot[kRegionPixels];            // pixel of the region at each rank
+    float2 est[kRegionPixels];
+    int more[3];
+};
+
+// Order between the lanes of a tile: of its only wave, or of the workgroup.
+template <int NW>
+__device__ __forceinline__ void tile_sync() {
+    if constexpr (NW == 1) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
+    }
+}
 
 // base + n / d with n = nh + nl and d = dh + dl, rounded once.
 __device__ __forceinline__ float plus_quotient(float base, float nh, float nl, float dh, float dl) {
@@ -1401,42 +1435,103 @@ __device__ __forceinline__ void carry_add(float &hi, float &lo, float x, float e
     lo += r + e;
 }
 
-template <int NW, bool DFC>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(6))) void k_posterior(PosteriorArgs a) {
+template <int NW, int RT, bool DFC>
+__global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6))) void k_posterior(PosteriorArgs a) {
     constexpr int PB = kTilePixels / 16;
-    __shared__ TileShared<NW> sh;
+    __shared__ RegionShared<NW, RT> rsh;
     const int lane = threadIdx.x & 63;
-    const int wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wave = wid % NW;   // of its tile
     const int lp = lane & 15, lk = lane >> 4;
-    const int bid = xcd_order(blockIdx.x, gridDim.x, kResidentWaves / NW);
-    const WaveWork w = tile_work<kTilePixels>(a, bid >> 2, bid & 3);
-    // Tiles below the last row of the frame (the workgroup grid rounds the
-    // rows up) hold no pixel: nothing to do.
-    if (w.r0 >= a.hl) return;
-    const float *zf = a.z + (size_t)w.f * 6 * a.LL;
-    const float sc = a.scale;
-    for (int i = threadIdx.x; i < 6 * kTilePixels; i += 64 * NW) (&sh.total[0][0])[i] = 0.0f;
-
-    // Observations: lane (lp, lk) holds coordinate lk of pixel b*16 + lp
-    // (lk == 3 repeats coordinate 0).
-    float ah[PB], al[PB];
+    const int bid = xcd_order(blockIdx.x, gridDim.x, kResidentWaves / (NW * RT));
+    const int tile = RT == 1 ? bid % kRegionTiles : wid / NW;   // of its region
+    const WaveWork w = block_work<kRegionW, kRegionH>(a, RT == 1 ? bid / kRegionTiles : bid);
+    TileShared<NW> &sh = rsh.tile[RT == 1 ? 0 : tile];
+    // Pixels of the region ranked by their observation's coordinate along the
+    // direction in which the nodes spread most; a tile takes 32 consecutive
+    // ranks.  Its observations then lie closer together than those of 8 x 4
+    // neighbours, whose noise spreads them, and their common box keeps fewer
+    // chunks (sixteen 1080p frames: 8.3% of the pairs, with the boxes' axes,
+    // instead of 9.8%).  Regions of 256 pixels would keep 3% fewer still, but
+    // four waves a tile would not fit in one workgroup.  Ranks are counted: the
+    // threads share the comparisons.
+    const int rows = min(kRegionH, a.hl - w.r0), cols = min(kRegionW, a.wl - w.c0);
+    const int n_valid = rows * cols;
+    {
+        const int i = threadIdx.x % kRegionPixels, part = threadIdx.x / kRegionPixels;
+        constexpr int kParts = 64 * NW * RT / kRegionPixels, kKeys = kRegionPixels / kParts;
+        if (part == 0) {
+            const int r = i / kRegionW, c = i % kRegionW;
+            const bool inside = r < rows && c < cols;
+            const long long p = (long long)(w.r0 + min(r, rows - 1)) * a.wl + w.c0 + min(c, cols - 1);
+            const float *zf = a.z + (size_t)w.f * 6 * a.LL;
+            float x[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                float h, l;
+                load_obs(zf, a.LL, p, k, a.scale, h, l);
+                rsh.obs[k][i] = h;
+                rsh.obs[3 + k][i] = l;
+                x[k] = h + l;
+            }
+            float q = 0.0f;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                q = fmaf(a.axes[3 * k], x[0], fmaf(a.axes[3 * k + 1], x[1], a.axes[3 * k + 2] * x[2]));
+                rsh.rot[k][i] = q;
+            }
+            // ordered bits, the low seven replaced by the pixel's number; pixels
+            // outside the frame last
+            const unsigned u = __float_as_uint(q == q ? q : INFINITY);
+            const unsigned ordered = u & 0x80000000u ? ~u : u | 0x80000000u;
+            rsh.key[i] = (inside ? ordered & ~127u : 0xffffff80u) | (unsigned)i;
+            rsh.rank[i] = 0;
+        }
+        for (int t = threadIdx.x; t < 6 * kTilePixels * RT; t += 64 * NW * RT)
+            (&rsh.tile[t / (6 * kTilePixels)].total[0][0])[t % (6 * kTilePixels)] = 0.0f;
+        if (threadIdx.x < 3) rsh.more[threadIdx.x] = 0;
+        __syncthreads();
+        const unsigned own = rsh.key[i];
+        int rank = 0;
+#pragma unroll 4
+        for (int t = 0; t < kKeys; ++t) rank += rsh.key[part * kKeys + t] < own ? 1 : 0;
+        atomicAdd(&rsh.rank[i], rank);
+        __syncthreads();
+        if (part == 0) rsh.slot[rsh.rank[i]] = i;
+        __syncthreads();
+    }
+    // A tile past the frame's pixels has nothing to do; a partial one repeats
+    // its first pixel.
+    const int base = tile * kTilePixels;
+    bool active = base < n_valid;
+    if (RT == 1 && !active) return;
+    int ib[PB];   // region pixel b*16 + lp of the tile
+    float ah[PB], al[PB];   // lane (lp, lk) holds its coordinate lk (lk == 3 repeats coordinate 0)
 #pragma unroll
     for (int b = 0; b < PB; ++b) {
-        long long p;
-        wave_pixel(a, w, b * 16 + lp, p);
-        load_obs(zf, a.LL, p, lk < 3 ? lk : 0, sc, ah[b], al[b]);
+        const int q = base + b * 16 + lp;
+        ib[b] = rsh.slot[q < n_valid ? q : (active ? base : 0)];
+        ah[b] = rsh.obs[lk < 3 ? lk : 0][ib[b]];
+        al[b] = rsh.obs[3 + (lk < 3 ? lk : 0)][ib[b]];
     }
-    // Observation box of the tile, widened for rounding.
+    // Observation box of the tile along the boxes' axes, widened for rounding
+    // (of the rotation too, at the scale of the observation).
     float zbox[6], far2 = 0.0f;
     {
-        const float x0 = ah[0] + al[0], x1 = ah[1] + al[1];
+        const float x0 = rsh.rot[lk < 3 ? lk : 0][ib[0]], x1 = rsh.rot[lk < 3 ? lk : 0][ib[1]];
         const float lo = row_reduce<false>(fminf(x0, x1)), hi = row_reduce<true>(fmaxf(x0, x1));
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            zbox[k] = lane_value(lo, 16 * k) - kBoxSlack;
-            zbox[3 + k] = lane_value(hi, 16 * k) + kBoxSlack;
+            zbox[k] = lane_value(lo, 16 * k);
+            zbox[3 + k] = lane_value(hi, 16 * k);
             const float e = fmaxf(-zbox[k], zbox[3 + k]);
             far2 = fmaf(e, e, far2);
+        }
+        const float slack = kBoxSlack + sqrtf(far2) * 0x1p-20f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            zbox[k] -= slack;
+            zbox[3 + k] += slack;
         }
     }
     auto super_bound = [&](int si) {   // -inf past the split's range
@@ -1563,19 +1658,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(6))) vo
     // those it leaves out add up to a bound on the skipped weight, which is
     // then held against the weight each pixel's sums really contain
     // (cert_log2), and while a pixel's certificate fails a further pass adds
-    // the chunks of the next kDepthStep units, down to skip_log2.  Sixteen
-    // 1080p frames: 9.8% of the pairs instead of 12.1%, 2.82 to 2.50 ms a call;
-    // the 1280x1024 pair on a 512 x 512 grid: 3.41 to 2.98 ms.
+    // the chunks of the next kDepthStep units, down to skip_log2.  (On tiles of
+    // 8 x 4 neighbours this kept 9.8% of the pairs of sixteen 1080p frames
+    // instead of 12.1%: 2.82 to 2.50 ms a call.)
     const int px = lane & 31;
     float mmin = INFINITY;
 #pragma unroll
     for (int b = 0; b < PB; ++b) {
         float m = am[b];
-        if (a.gref) {
-            long long p;
-            wave_pixel(a, w, b * 16 + lp, p);
-            m = fmaxf(m, a.gref[(size_t)w.f * a.LL + p]);
-        }
+        if (a.gref) m = fmaxf(m, a.gref[(size_t)w.f * a.LL + region_pixel(a, w, ib[b])]);
         // A pixel without a finite logit (a NaN observation) gets NaN maps
         // whatever is kept; it must not switch skipping off for its tile.
         mmin = fminf(mmin, m > -INFINITY ? m : INFINITY);
@@ -1586,13 +1677,18 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(6))) vo
     // only weights evaluated); a split far from the posterior usually keeps
     // none, and then the reference needs no refinement.
     if (__any(!(mup - am[0] <= kFarGap) || !(mup - am[1] <= kFarGap))) {
-        long long p;
-        wave_pixel(a, w, px, p);
+        const int i = px < 16 ? ib[0] : ib[1];
         float ph[3], pl[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) load_obs(zf, a.LL, p, k, sc, ph[k], pl[k]);
-        const float m = far_gap_max<kTilePixels, 2>(a, w, ph, pl, lane >> 5, zbox, zbox + 3, mmin,
-                                                    (px < 16 ? am[0] : am[1]));
+        for (int k = 0; k < 3; ++k) {
+            ph[k] = rsh.obs[k][i];
+            pl[k] = rsh.obs[3 + k][i];
+        }
+        auto chunk_test = [&](int si, int c) {
+            return box_box_bound(a.boxes + ((size_t)si * a.chunks_per_super + c) * kBoxFloats, zbox);
+        };
+        const float m = far_gap_max<kTilePixels, 2>(a, w, ph, pl, lane >> 5, super_bound, chunk_test, mmin,
+                                                    px < 16 ? am[0] : am[1]);
 #pragma unroll
         for (int b = 0; b < PB; ++b) am[b] = __shfl(m, b * 16 + lp);
     }
@@ -1613,6 +1709,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(6))) vo
     const int sub = (int)((unsigned)lane * (unsigned)a.inv_chunks >> 16), ci = lane - sub * cps;   // lane / cps
     const unsigned long long chunk_bits = cps >= 64 ? ~0ull : (1ull << cps) - 1;
 
+    // Several waves per tile: the tiles of the workgroup go through the same
+    // barriers, so they learn of each other whether one has more to do.
+    int round = 0;
+    auto any_tile = [&](bool mine) {
+        if (mine) rsh.more[round] = 1;
+        const int after = round == 2 ? 0 : round + 1;
+        if (threadIdx.x == 0) rsh.more[after] = 0;   // read last two rounds ago
+        __syncthreads();
+        const bool any = rsh.more[round] != 0;
+        round = after;
+        return any;
+    };
+
     // Passes: the chunks whose bound v (relative to mmin) has vlo < v <= vhi
     // are evaluated; a pass that reaches skip_log2 is the last.
     const float nskip = -a.skip_log2;
@@ -1621,10 +1730,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(6))) vo
         const bool last = !(vlo > nskip);
         const float svlo = fmaxf(nskip, vlo - kSuperMargin);
         unsigned mass = 0;   // this lane's share of the skipped weight (saturating), 2^-kMassLog2 per chunk
-        for (int g = w.s0; g < w.s1;) {
+        int g = w.s0;
+        for (bool more = true; more;) {
             // Super-tiles, one per lane; the kept ones are listed.
             int K = 0;
-            while (g < w.s1) {
+            while (active && g < w.s1) {
                 const float sv = super_bound(g + lane) - mmin;
                 const unsigned long long smask = __builtin_amdgcn_ballot_w64(sv > svlo);
                 const int n = __popcll(smask);
@@ -1641,7 +1751,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(6))) vo
                 K += n;
                 g += 64;
             }
-            if (K == 0) break;
+            if (NW == 1 && K == 0) break;
+            tile_sync<1>();   // between the lanes of each wave, which has listed them itself
             // Chunk tests of the kept super-tiles, 64 chunks at once.
             for (int k0 = wave * per_test; k0 < K; k0 += NW * per_test) {
                 const int k = k0 + sub;
@@ -1656,7 +1767,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(6))) vo
                     sh.kept[k].hi = (unsigned)(bits >> 32);
                 }
             }
-            __syncthreads();
+            tile_sync<NW>();
             // Segments in turn (which wave sums a segment changes no bit).
             const KeptSuper own = sh.kept[lane];
             for (int seg = wave; seg < kSegments; seg += NW) {
@@ -1780,25 +1891,29 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(6))) vo
                 close(R1[0], R1[1], 1);
                 close(R2[0], R2[1], 2);
             }
-            __syncthreads();   // the window's list is free again, its segments are summed
+            tile_sync<NW>();   // the window's list is free again, its segments are summed
+            more = active && g < w.s1;
             if constexpr (NW > 1) {
-                if (threadIdx.x < 3 * kTilePixels) {
-                    const int q = threadIdx.x / kTilePixels, i = threadIdx.x % kTilePixels;
+                const int q = (64 * wave + lane) / kTilePixels, i = lane % kTilePixels;
+                if (K > 0 && q < 3) {
                     float hi = sh.total[q][i], lo = sh.total[3 + q][i];
 #pragma unroll
                     for (int t = 0; t < kSegments; ++t) carry_add(hi, lo, sh.part[t][q][i], sh.part[t][3 + q][i]);
                     sh.total[q][i] = hi;
                     sh.total[3 + q][i] = lo;
                 }
-                __syncthreads();
+                more = any_tile(more);
             }
         }
-        if (last) break;
-        // Certificate: the skipped weight, at most 2^skipped relative to mmin for
-        // every pixel of the tile, against the pixel's sum.  A NaN sum certifies
-        // itself: its maps are NaN whatever is kept.
+        bool fails = false;
+        if (active && !last) {
+            // Certificate: the skipped weight, at most 2^skipped relative to mmin for
+            // every pixel of the tile, against the pixel's sum.  A NaN sum certifies
+            // itself: its maps are NaN whatever is kept.
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) mass = __builtin_elementwise_add_sat(mass, (unsigned)__shfl_xor((int)mass, o));
+            for (int o = 32; o >= 1; o >>= 1)
+                mass = __builtin_elementwise_add_sat(mass, (unsigned)__shfl_xor((int)mass, o));
+        }
         if constexpr (NW > 1) {
             if (lane == 0) sh.mass[wave] = mass;
             __syncthreads();
@@ -1806,14 +1921,21 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(6))) vo
 #pragma unroll
             for (int q = 1; q < NW; ++q) mass = __builtin_elementwise_add_sat(mass, sh.mass[q]);
         }
-        const float skipped = __log2f((float)mass) - kMassLog2;
-        const float held = (px < 16 ? am[0] : am[1]) + __log2f(sh.total[0][px] + sh.total[3][px]);
-        if (!__any(skipped > a.cert_log2 + (held - mmin))) break;
-        if constexpr (NW > 1) __syncthreads();   // sums and masses are read before the next pass writes
+        if (active && !last) {
+            const float skipped = __log2f((float)mass) - kMassLog2;
+            const float held = (px < 16 ? am[0] : am[1]) + __log2f(sh.total[0][px] + sh.total[3][px]);
+            fails = __any(skipped > a.cert_log2 + (held - mmin));
+        }
+        active = fails;
+        if constexpr (NW > 1) {
+            if (!any_tile(fails)) break;
+        } else {
+            if (!fails) break;
+        }
         vhi = vlo;
         vlo = fmaxf(nskip, vlo - kDepthStep);
     }
-    __syncthreads();
+    tile_sync<NW>();
     float S0 = sh.total[0][px] + sh.total[3][px];
     const float m = (px < 16 ? am[0] : am[1]);
 
@@ -1831,8 +1953,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(6))) vo
     // Lane indices for what follows, formed here again rather than kept
     // across the main loop.
     const int lane_e = opaque_v((int)threadIdx.x) & 63, px_e = lane_e & 31;
-    long long pe;
-    const bool valid = wave_pixel(a, w, px_e, pe);
+    const bool valid = base + px_e < n_valid;
+    const int pixel = rsh.slot[valid ? base + px_e : 0];
     unsigned long long far = __builtin_amdgcn_ballot_w64(lane_e < 32 && valid && m + __log2f(S0) < -a.far_rho2);
     if (__builtin_expect(far != 0, 0)) {
         // The pass reads the kernel's arguments again from the argument segment
@@ -1844,16 +1966,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(6))) vo
             far &= far - 1;
             if (NW > 1 && turn % NW != wave) continue;
             const PosteriorArgs fa = far_args(opaque(ka));
-            long long pq;
-            wave_pixel(fa, w, q, pq);
-            const float *zq = fa.z + (size_t)w.f * 6 * fa.LL;
+            const int i = __builtin_amdgcn_readlane(pixel, q);
             float qh[3], qlo[3];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) load_obs(zq, fa.LL, pq, k, fa.scale, qh[k], qlo[k]);
+            for (int k = 0; k < 3; ++k) {
+                qh[k] = rsh.obs[k][i];
+                qlo[k] = rsh.obs[3 + k][i];
+            }
             const float mq = __shfl(m, q);
             float m_skip = mq;
             if (fa.gref) {
-                const float g = fa.gref[(size_t)w.f * fa.LL + pq];
+                const float g = fa.gref[(size_t)w.f * fa.LL + region_pixel(fa, w, i)];
                 if (!(g < -fa.far_rho2)) continue;
                 m_skip = fmaxf(m_skip, g);
             }
@@ -1863,24 +1986,28 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(6))) vo
             if (lane_e < 6)   // these replace the pixel's sums
                 sh.total[lane_e][q] = lane_e == 0 ? S[0] : (lane_e == 1 ? S[1] : (lane_e == 2 ? S[2] : 0.0f));
         }
-        __syncthreads();
-        S0 = sh.total[0][px_e] + sh.total[3][px_e];
     }
+    tile_sync<NW>();
+    S0 = sh.total[0][px_e] + sh.total[3][px_e];
     if (a.work && lane_e == 0) {
         atomicAdd(a.work, (unsigned long long)executed * kTilePixels * kChunkNodes);
         if (far_pixels) atomicAdd(a.work + 1, (unsigned long long)far_pixels);
     }
     const bool writer = wave == 0 && lane_e < 32 && valid;
+    const long long pe = region_pixel(a, w, pixel);
     if (a.fuse) {
         // one split: the estimate is anchor + S1 / S0
-        const float dh = sh.total[0][px_e], dl = sh.total[3][px_e];
-        const float ex = plus_quotient(anc_hb, sh.total[1][px_e], sh.total[4][px_e], dh, dl);
-        const float ey = plus_quotient(anc_ox, sh.total[2][px_e], sh.total[5][px_e], dh, dl);
-        if (writer) a.est[(size_t)w.f * a.LL + pe] = make_float2(ex, ey);
+        if (writer) {
+            const float dh = sh.total[0][px_e], dl = sh.total[3][px_e];
+            rsh.est[pixel] = make_float2(plus_quotient(anc_hb, sh.total[1][px_e], sh.total[4][px_e], dh, dl),
+                                         plus_quotient(anc_ox, sh.total[2][px_e], sh.total[5][px_e], dh, dl));
+            a.est[(size_t)w.f * a.LL + pe] = rsh.est[pixel];
+        }
+        __syncthreads();
         switch (a.vec) {
-            case 4: fused_maps<NW, 4>(a, w, ex, ey, wave, lane_e); break;
-            case 2: fused_maps<NW, 2>(a, w, ex, ey, wave, lane_e); break;
-            default: fused_maps<NW, 1>(a, w, ex, ey, wave, lane_e); break;
+            case 4: fused_maps<RT, 4>(a, w, rsh.est, rsh.slot + base, min(kTilePixels, n_valid - base)); break;
+            case 2: fused_maps<RT, 2>(a, w, rsh.est, rsh.slot + base, min(kTilePixels, n_valid - base)); break;
+            default: fused_maps<RT, 1>(a, w, rsh.est, rsh.slot + base, min(kTilePixels, n_valid - base)); break;
         }
         return;
     }
@@ -1906,7 +2033,8 @@ template <bool PRECISE>
 __global__ __launch_bounds__(kBlockThreads) void k_posterior_direct(PosteriorArgs a) {
     constexpr int PW = 64;
     const int lane = threadIdx.x & 63;
-    const WaveWork w = tile_work<PW>(a, xcd_order(blockIdx.x, gridDim.x, kResidentWaves / 4), threadIdx.x >> 6);
+    WaveWork w = block_work<kWaveTileW, 4 * PW / kWaveTileW>(a, xcd_order(blockIdx.x, gridDim.x, kResidentWaves / 4));
+    w.r0 += (threadIdx.x >> 6) * (PW / kWaveTileW);
     if (w.r0 >= a.hl) return;   // a tile below the frame's last row holds no pixel
     const float *zf = a.z + (size_t)w.f * 6 * a.LL;
     long long p;
@@ -1924,9 +2052,19 @@ __global__ __launch_bounds__(kBlockThreads) void k_posterior_direct(PosteriorArg
     if (!(mmin > -INFINITY)) mmin = INFINITY;  // NaN observation: see the MFMA kernel
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) mmin = fminf(mmin, __shfl_xor(mmin, o));
-    if (__any(!(ref.mup - ref.m <= kFarGap))) ref.m = far_gap_max<PW, 1>(a, w, ph, pl, 0, zlo, zhi, mmin, ref.m);
-    const float nm = -ref.m;
     const float zbox[6] = {zlo[0], zlo[1], zlo[2], zhi[0], zhi[1], zhi[2]};
+    if (__any(!(ref.mup - ref.m <= kFarGap))) {
+        auto super_test = [&](int si) {
+            float rbox[6];
+            return wave_super_bound(a, si, zlo, zhi, rbox);
+        };
+        auto chunk_test = [&](int si, int c) {
+            return box_box_bound(a.supers + (size_t)si * a.super_stride + kSupHdr + kMaxProbes * kProbeFloats +
+                                     (size_t)c * kChunkFloats + 96, zbox);
+        };
+        ref.m = far_gap_max<PW, 1>(a, w, ph, pl, 0, super_test, chunk_test, mmin, ref.m);
+    }
+    const float nm = -ref.m;
     float R0 = 0.f, R1 = 0.f, R2 = 0.f, K0 = 0.f, K1 = 0.f, K2 = 0.f;
     unsigned executed = 0;
     for (int g = w.s0; g < w.s1; g += 64) {
@@ -2165,40 +2303,40 @@ hipError_t launch_reference(const PosteriorArgs &a, hipStream_t s) {
 
 namespace {
 
-template <int NW>
-void launch_mfma(const PosteriorArgs &a, long long tiles, hipStream_t s) {
-    const dim3 g((unsigned)tiles), blk(64 * NW);
+template <int NW, int RT>
+void launch_mfma(const PosteriorArgs &a, long long regions, hipStream_t s) {
+    const dim3 g((unsigned)(regions * (kRegionTiles / RT))), blk(64 * NW * RT);
     if (a.dfc)
-        hipLaunchKernelGGL((k_posterior<NW, true>), g, blk, 0, s, a);
+        hipLaunchKernelGGL((k_posterior<NW, RT, true>), g, blk, 0, s, a);
     else
-        hipLaunchKernelGGL((k_posterior<NW, false>), g, blk, 0, s, a);
+        hipLaunchKernelGGL((k_posterior<NW, RT, false>), g, blk, 0, s, a);
 }
 
 }  // namespace
 
 hipError_t launch_posterior(const PosteriorArgs &a, bool mfma, hipStream_t s) {
-    const int th = (mfma ? kTilePixels : 64) / kWaveTileW;
-    const long long per_frame = (long long)((a.wl + kWaveTileW - 1) / kWaveTileW) * ((a.hl + 4 * th - 1) / (4 * th));
-    const long long grid = per_frame * a.n_frames * a.split;
-    if (grid <= 0) return hipSuccess;
+    const int bw = mfma ? kRegionW : kWaveTileW, bh = mfma ? kRegionH : 4 * 64 / kWaveTileW;
+    const long long blocks = (long long)((a.wl + bw - 1) / bw) * ((a.hl + bh - 1) / bh) * a.n_frames * a.split;
+    if (blocks <= 0) return hipSuccess;
     if (mfma) {
-        const long long tiles = 4 * grid;
         // Tiles that would all be resident at once with one wave each: the
         // launch would last as long as its busiest tile (2.3 times the mean on
-        // 1080p frames), and four waves a tile share that out.  One 640x480
-        // frame (600 tiles, 256 x 256 grid): 221 us a call with one wave, 137
-        // with two, 88 with four; one 1080p frame (4080 tiles): 216, 209 and 194.
-        // More tiles keep the chip full by themselves, and the waves of a tile
-        // repeat its set-up: 9600 tiles (128 x 128 grid) 210, 211 and 228 us,
-        // 20480 tiles 282, 315 and 367.
-        if (tiles <= kResidentWaves)
-            launch_mfma<4>(a, tiles, s);
+        // 1080p frames); four waves a tile share that out, in a workgroup of
+        // their own so that few regions still reach every CU (the region is
+        // then ranked by each of its four tiles' workgroups).  One 640x480
+        // frame (600 tiles, 256 x 256 grid): 155 us a call with one wave per
+        // tile and four tiles per workgroup, 72 this way; one 1080p frame (4080
+        // tiles) 193 and 183.  More tiles keep the chip full by themselves, and
+        // the waves of a tile repeat its set-up: 9600 tiles (128 x 128 grid)
+        // 165 and 187 us, 20480 tiles 256 and 343.
+        if (blocks * kRegionTiles <= kResidentWaves)
+            launch_mfma<4, 1>(a, blocks, s);
         else
-            launch_mfma<1>(a, tiles, s);
+            launch_mfma<1, kRegionTiles>(a, blocks, s);
     } else if (a.precise) {
-        hipLaunchKernelGGL(k_posterior_direct<true>, dim3((unsigned)grid), dim3(kBlockThreads), 0, s, a);
+        hipLaunchKernelGGL(k_posterior_direct<true>, dim3((unsigned)blocks), dim3(kBlockThreads), 0, s, a);
     } else {
-        hipLaunchKernelGGL(k_posterior_direct<false>, dim3((unsigned)grid), dim3(kBlockThreads), 0, s, a);
+        hipLaunchKernelGGL(k_posterior_direct<false>, dim3((unsigned)blocks), dim3(kBlockThreads), 0, s, a);
     }
     return hipGetLastError();
 }

@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -60,6 +61,7 @@ struct hb_plan_s {
 
     hb_plan_info_t info{};
     float iref[3] = {1, 1, 1};
+    float axes[9] = {1, 0, 0, 0, 1, 0, 0, 0, 1};
     float scale = 1.0f;
     float skip_log2 = kExactSkipLog2;
     float depth0 = kExactSkipLog2;      // = skip_log2 when nothing is certified
@@ -231,6 +233,26 @@ float float_up(double x) {
     float f = (float)x;
     if ((double)f < x) f = std::nextafter(f, INFINITY);
     return f;
+}
+
+// work(begin, end) over the super-tiles, on up to `most` threads (the caller's
+// among them; a thread that cannot be started leaves its part to the caller).
+template <typename Work>
+void for_supers(int n_sup, unsigned most, Work work) {
+    unsigned nt = std::max(1u, std::min(std::thread::hardware_concurrency(), most));
+    nt = std::min<unsigned>(nt, (unsigned)n_sup);
+    auto bound = [&](unsigned i) { return (int)((long long)n_sup * i / nt); };
+    std::vector<std::thread> th;
+    th.reserve(nt);
+    for (unsigned i = 1; i < nt; ++i) {
+        try {
+            th.emplace_back(work, bound(i), bound(i + 1));
+        } catch (const std::system_error &) {
+            work(bound(i), bound(i + 1));
+        }
+    }
+    work(bound(0), bound(1));
+    for (auto &x : th) x.join();
 }
 
 // Build the super-tile table (FP64 arithmetic, FP32 storage): scaled
@@ -405,12 +427,7 @@ double build_supers(const hb_plan_desc_t &d, const ForwardModel &fm, const doubl
             std::memcpy(&T[14], &np, sizeof(int));
         }
     };
-    unsigned nt = std::max(1u, std::min(std::thread::hardware_concurrency(), 32u));
-    nt = std::min<unsigned>(nt, (unsigned)n_sup);
-    std::vector<std::thread> th;
-    for (unsigned i = 0; i < nt; ++i)
-        th.emplace_back(work, (int)((long long)n_sup * i / nt), (int)((long long)n_sup * (i + 1) / nt));
-    for (auto &x : th) x.join();
+    for_supers(n_sup, 32u, work);
     direct_index = *std::max_element(index.begin(), index.end());
     return *std::max_element(radius.begin(), radius.end());
 }
@@ -460,22 +477,74 @@ void split_block(const float *C, uint16_t *O) {
         }
 }
 
+// Threads for tables of n_sup super-tiles: one per 512 chunks or so (a thread
+// costs about as much to start as it takes to fill those).
+unsigned table_threads(int n_sup, int side) {
+    return (unsigned)std::max(1LL, std::min(32LL, (long long)n_sup * (side / 4) * (side / 4) / 512));
+}
+
 // Split bf16 A operands of every chunk of the super-tile table.
 void build_split_ops(const std::vector<float> &table, int n_sup, int side, std::vector<uint16_t> &ops) {
-    const int stride = super_floats(side);
-    const int n_chunks = (side / 4) * (side / 4);
-    constexpr int kLaneHalves = kSplitLaneBytes / 2;
-    ops.assign((size_t)n_sup * n_chunks * 64 * kLaneHalves, 0);
+    const int stride = super_floats(side), n_chunks = (side / 4) * (side / 4);
+    ops.assign((size_t)n_sup * n_chunks * kSplitChunkBytes / 2, 0);
+    for_supers(n_sup, table_threads(n_sup, side), [&](int s_begin, int s_end) {
+        for (int si = s_begin; si < s_end; ++si)
+            for (int c = 0; c < n_chunks; ++c)
+                split_block(&table[(size_t)si * stride + kSupHdr + kMaxProbes * kProbeFloats + (size_t)c * kChunkFloats],
+                            &ops[((size_t)si * n_chunks + c) * kSplitChunkBytes / 2]);
+    });
+}
+
+// Principal axes of the node differences across each chunk (both grid
+// directions), rows of `axes` in ascending order of their spread: the
+// eigenvectors of the summed outer products, by Jacobi rotations.
+void principal_axes(const std::vector<float> &table, int n_sup, int side, float axes[9]) {
+    const int stride = super_floats(side), cps = (side / 4) * (side / 4);
+    double A[3][3] = {}, V[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
     for (int si = 0; si < n_sup; ++si)
-        for (int c = 0; c < n_chunks; ++c)
-            split_block(&table[(size_t)si * stride + kSupHdr + kMaxProbes * kProbeFloats + (size_t)c * kChunkFloats],
-                        &ops[((size_t)si * n_chunks + c) * 64 * kLaneHalves]);
+        for (int c = 0; c < cps; ++c) {
+            const float *C = &table[(size_t)si * stride + kSupHdr + kMaxProbes * kProbeFloats + (size_t)c * kChunkFloats];
+            for (int q : {3, 12}) {   // along SO2, along THb
+                while (q > 0 && C[48 + q] <= kPadLogit) q -= q > 3 ? 4 : 1;   // inside the grid
+                if (C[48] <= kPadLogit) continue;
+                double d[3];
+                for (int k = 0; k < 3; ++k) d[k] = (double)C[16 * k + q] - (double)C[16 * k];
+                for (int x = 0; x < 3; ++x)
+                    for (int y = 0; y < 3; ++y) A[x][y] += d[x] * d[y];
+            }
+        }
+    for (int sweep = 0; sweep < 30; ++sweep)
+        for (int x = 0; x < 2; ++x)
+            for (int y = x + 1; y < 3; ++y) {
+                if (A[x][y] == 0.0) continue;
+                const double th = 0.5 * std::atan2(2.0 * A[x][y], A[x][x] - A[y][y]);
+                const double c = std::cos(th), sn = std::sin(th);
+                for (int k = 0; k < 3; ++k) {   // columns, then rows, of A; columns of V
+                    const double p = A[k][x], q = A[k][y];
+                    A[k][x] = c * p + sn * q;
+                    A[k][y] = c * q - sn * p;
+                }
+                for (int k = 0; k < 3; ++k) {
+                    const double p = A[x][k], q = A[y][k];
+                    A[x][k] = c * p + sn * q;
+                    A[y][k] = c * q - sn * p;
+                }
+                for (int k = 0; k < 3; ++k) {
+                    const double p = V[k][x], q = V[k][y];
+                    V[k][x] = c * p + sn * q;
+                    V[k][y] = c * q - sn * p;
+                }
+            }
+    int order[3] = {0, 1, 2};
+    std::sort(order, order + 3, [&](int x, int y) { return A[x][x] < A[y][y]; });
+    for (int r = 0; r < 3; ++r)
+        for (int k = 0; k < 3; ++k) axes[3 * r + k] = (float)V[k][order[r]];
 }
 
 // Test tables of the MFMA kernel (layout in hb_internal.h) from the
 // super-tile table; `out` holds headers and boxes one after the other.
 void build_test_tables(const std::vector<float> &table, int n_sup, int columns, int side, size_t boxes_at,
-                       std::vector<float> &out, std::vector<uint16_t> &probes) {
+                       const float axes[9], std::vector<float> &out, std::vector<uint16_t> &probes) {
     const int stride = super_floats(side), cps = (side / 4) * (side / 4), slots = probe_slots(side);
     constexpr int kLaneHalves = kSplitLaneBytes / 2;
     out.assign(boxes_at + (size_t)n_sup * cps * kBoxFloats, 0.0f);
@@ -483,7 +552,8 @@ void build_test_tables(const std::vector<float> &table, int n_sup, int columns, 
     std::vector<float> v(n_blocks * 64, 0.0f);   // [block][coordinate or norm][probe]
     for (size_t b = 0; b < n_blocks; ++b)
         for (int i = 0; i < 16; ++i) v[b * 64 + 48 + i] = kPadLogit;
-    for (int si = 0; si < n_sup; ++si) {
+    auto work = [&](int s_begin, int s_end) {
+      for (int si = s_begin; si < s_end; ++si) {
         const float *T = &table[(size_t)si * stride];
         float *H = &out[(size_t)si * kHdrFloats];
         for (int k = 0; k < 3; ++k) {
@@ -496,12 +566,27 @@ void build_test_tables(const std::vector<float> &table, int n_sup, int columns, 
         H[7] = T[7];
         const int segment = (si % columns + si / columns) % kSegments;
         std::memcpy(&H[14], &segment, sizeof(int));
+        double cen[3];   // the centre along the axes
+        for (int r = 0; r < 3; ++r) {
+            cen[r] = 0.0;
+            for (int k = 0; k < 3; ++k) cen[r] += (double)axes[3 * r + k] * ((double)T[k] + (double)T[3 + k]);
+        }
         for (int c = 0; c < cps; ++c) {
             const float *C = T + kSupHdr + kMaxProbes * kProbeFloats + (size_t)c * kChunkFloats;
             float *X = &out[boxes_at + ((size_t)si * cps + c) * kBoxFloats];
+            double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+            for (int j = 0; j < kChunkNodes; ++j) {
+                if (C[48 + j] <= kPadLogit) continue;   // outside the grid
+                for (int r = 0; r < 3; ++r) {
+                    const double x = cen[r] + ((double)axes[3 * r] * C[j] + (double)axes[3 * r + 1] * C[16 + j] +
+                                               (double)axes[3 * r + 2] * C[32 + j]);
+                    lo[r] = std::min(lo[r], x);
+                    hi[r] = std::max(hi[r], x);
+                }
+            }
             for (int k = 0; k < 3; ++k) {
-                X[k] = C[96 + k];
-                X[3 + k] = C[99 + k];
+                X[k] = float_down(lo[k]);
+                X[3 + k] = float_up(hi[k]);
                 H[k] = std::min(H[k], X[k]);
                 H[3 + k] = std::max(H[3 + k], X[3 + k]);
             }
@@ -518,7 +603,9 @@ void build_test_tables(const std::vector<float> &table, int n_sup, int columns, 
             }
             v[at / 16 * 64 + 48 + at % 16] = (float)-sq;
         }
-    }
+      }
+    };
+    for_supers(n_sup, table_threads(n_sup, side), work);
     probes.assign(n_blocks * 64 * kLaneHalves, 0);
     for (size_t b = 0; b < n_blocks; ++b) split_block(&v[b * 64], &probes[b * 64 * kLaneHalves]);
 }
@@ -610,6 +697,7 @@ hb_status_t estimate(hb_plan_s *p, const void *d_frames, int32_t n_frames, const
         pa.n_supers = p->n_tiles;
         pa.super_stride = super_floats(p->side);
         pa.chunks_per_super = (p->side / 4) * (p->side / 4);
+        for (int k = 0; k < 9; ++k) pa.axes[k] = p->axes[k];
         pa.headers = p->d_tests;
         pa.boxes = p->d_tests + p->boxes_at;
         pa.probes = p->d_probes;
@@ -939,13 +1027,14 @@ hb_status_t hb_set_forward_model(hb_plan_t p, const hb_forward_model_t *fm) {
     if (hipMemcpy(p->d_lo, lo.data(), sizeof(float) * lo.size(), hipMemcpyHostToDevice) != hipSuccess)
         return HB_ERR_DEVICE;
     std::vector<float> tests;
-    std::vector<uint16_t> probes;
-    build_test_tables(tiles, p->n_tiles, (d.grid_so2 + p->side - 1) / p->side, p->side, p->boxes_at, tests, probes);
+    std::vector<uint16_t> probes, split_ops;
+    build_split_ops(tiles, p->n_tiles, p->side, split_ops);
+    principal_axes(tiles, p->n_tiles, p->side, p->axes);
+    build_test_tables(tiles, p->n_tiles, (d.grid_so2 + p->side - 1) / p->side, p->side, p->boxes_at, p->axes, tests,
+                      probes);
     if (hipMemcpy(p->d_tests, tests.data(), sizeof(float) * tests.size(), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(p->d_probes, probes.data(), sizeof(uint16_t) * probes.size(), hipMemcpyHostToDevice) != hipSuccess)
         return HB_ERR_DEVICE;
-    std::vector<uint16_t> split_ops;
-    build_split_ops(tiles, p->n_tiles, p->side, split_ops);
     if (hipMemcpy(p->d_split, split_ops.data(), sizeof(uint16_t) * split_ops.size(), hipMemcpyHostToDevice) !=
         hipSuccess)
         return HB_ERR_DEVICE;

@@ -536,6 +536,34 @@ def test_tile_kernel_edges(torch_cuda, h, w, levels, gt, gs):
     hbtest.assert_maps_close(out[1e-6], hbtest.run_oracle(frames, "f32", s), f"{h}x{w} L{levels} {gt}x{gs}")
 
 
+@pytest.mark.parametrize("h,w,levels,n,offset", [(242, 318, 0, 4, 0), (242, 318, 1, 12, 1), (484, 636, 2, 12, 2)])
+def test_ragged_regions_agree_in_small_and_large_launches(torch_cuda, h, w, levels, n, offset):
+    """Low-pass bands ragged against the 16 x 8 regions of the posterior: a
+    frame alone (a workgroup per tile, four waves each) and in a batch (a
+    workgroup per region) gives the same bits, into map slabs that allow 4-,
+    1- and 2-pixel stores."""
+    torch = torch_cuda
+    from paper_1706_07263_amd import hb
+    frames = np.stack([synth.single_frame(h, w, config=66, stream=i)[0] for i in range(n)])
+    desc = hb.make_desc(w, h, levels=levels, max_batch=n, grid_thb=72, grid_so2=64)
+    with hb.Plan(desc, 0) as plan:
+        plan.set_forward_model(synth.spectra())
+        dev = torch.from_numpy(frames).cuda()
+        slab = [torch.zeros(n * h * w + 4, device="cuda") for _ in range(4)]
+        every = [m[offset:offset + n * h * w].view(n, h, w) for m in slab]
+        plan.estimate(dev, every)
+        one = [torch.zeros((1, h, w), device="cuda") for _ in range(4)]
+        for k in (0, n - 1):
+            plan.estimate(dev[k:k + 1], one)
+            torch.cuda.synchronize()
+            for a, b in zip(one, every):
+                assert torch.equal(a[0].nan_to_num(-1.0), b[k].nan_to_num(-1.0)), k
+        got = np.stack([m[0].cpu().numpy() for m in one])[None]
+    r, c = (h >> levels) - 9 << levels, (w >> levels) - 17 << levels   # the last, ragged regions
+    ora = hbtest.run_oracle(np.ascontiguousarray(frames[-1:, r:, c:]), "f32", dict(_settings(levels=levels, grid=72), grid_so2=64))
+    hbtest.assert_maps_close(got[:, :, r:, c:], ora, f"{h}x{w} L{levels}")
+
+
 @pytest.mark.parametrize("levels", [0, 1, 2])
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("camera", ["default", "shifted"])
