@@ -79,7 +79,8 @@ typedef struct {
     double thb_eps;             /* SO2 is NaN where THb <= thb_eps (uM)                    */
     int32_t lowpass;            /* hb_lowpass_t                                            */
     int32_t grid_split;         /* posterior grid split across workgroups; 0 = automatic
-                                   (sized so that max_batch frames fill the GPU)         */
+                                   (one for the MFMA kernel; for the direct kernels sized so
+                                   that max_batch frames fill the GPU)                    */
     int32_t illumination;       /* 1: the low-pass posterior integrates out an unknown
                                    per-pixel log offset b*(1,1,1) under a flat prior
                                    (the constant attenuation term for global illumination,

@@ -27,7 +27,8 @@ struct hb_plan_s {
     hb_plan_desc_t desc{};
     int device = 0;
     Dims dims{};
-    int split = 1;
+    int split = 1;              // grid split in use
+    int max_split = 1;          // that the buffers are sized for
     int side = 8;
     float far_rho2 = INFINITY;  // MFMA kernel: squared room for far observations (scaled units)
     double radius = 0;        // largest super-tile radius, scaled units
@@ -155,16 +156,19 @@ SkipRule skip_rule(double G, double thb_max, double tol, int split) {
     return r;
 }
 
+// Automatic split for the direct kernels: one unless a full batch gives fewer
+// than kMinWaves waves of 32 pixels.  With skipping, a split adds a reference
+// pass, a global-reference kernel and the merge kernel, and far splits still
+// pay their per-wave set-up.  The split is fixed per plan, so a frame gives
+// the same bits in any batch.  The MFMA kernel always takes one: it shares a
+// tile between four waves, certifies its skip depth on the pixel's whole sum
+// (which a split does not see) and writes the maps itself.  Measured a call,
+// the former automatic split against one: 64x64 at one level, 32 x 32 grid 77
+// and 28 us, 512 x 512 grid 1845 and 529; 64x64 at two levels, 256 x 256 grid
+// 236 and 147; 16x16 at no level, 1024 x 1024 grid (8 tiles) 3101 and 2560.
 int auto_split(const Dims &dm, int n_tiles, int max_batch) {
-    // One split unless a full batch gives fewer than kMinWaves waves.  With
-    // skipping, a split adds a reference pass, a global-reference kernel and
-    // the merge kernel, and far splits still pay their per-wave set-up:
-    // measured per frame at batch 1, one split was fastest from 640x480
-    // (600 waves) to 3840x2160.  The split is fixed per plan, so a frame gives
-    // the same bits in any batch.
     constexpr long long kMinWaves = 256;
-    const long long per_wave = kTilePixels;
-    const long long waves = std::max(1LL, ((long long)max_batch * dm.LL + per_wave - 1) / per_wave);
+    const long long waves = std::max(1LL, ((long long)max_batch * dm.LL + 31) / 32);
     int s = 1;
     while (s < 64 && waves * s < kMinWaves) s *= 2;
     return std::max(1, std::min(s, n_tiles));
@@ -197,6 +201,30 @@ void free_plan(hb_plan_s *p) {
     for (hipEvent_t e : p->events) (void)hipEventDestroy(e);
     if (p->done) (void)hipEventDestroy(p->done);
     delete p;
+}
+
+// The grid split in use and the skip thresholds, which depend on it.
+void set_split(hb_plan_s *p, int split) {
+    const hb_plan_desc_t &d = p->desc;
+    p->split = split;
+    p->info.grid_split = split;
+    const SkipRule rule = skip_rule((double)p->n_nodes, d.thb_max, d.posterior_tolerance, split);
+    p->skip_log2 = rule.skip_log2;
+    p->band_log2 = rule.band_log2;
+    p->band_chunks = rule.band_chunks;
+    p->depth0 = p->skip_log2;
+    if (rule.bound > 0.0 && split == 1) {
+        // skipped over kept weight that moves a mean by at most the stated
+        // bound (a sixteenth left for rounding); the kernel of a split grid
+        // sees a part of the kept weight only and takes the a-priori threshold
+        const double ratio = rule.bound / d.thb_max;
+        p->depth0 = (float)std::min<double>(p->skip_log2, std::max<double>(kMinSkipLog2, -std::log2(0.5 * ratio)));
+        p->cert_log2 = (float)std::log2(ratio * (1.0 - 1.0 / 16));
+    }
+    p->info.skip_bound = rule.bound;
+    p->info.skip_log2 = p->skip_log2;
+    p->info.band_log2 = p->band_log2;
+    p->info.band_chunks = p->band_chunks;
 }
 
 hb_status_t set_device(int dev) {
@@ -846,7 +874,8 @@ hb_status_t hb_plan_create(const hb_plan_desc_t *desc, int device, hb_plan_t *ou
     const int nsa = (desc->grid_thb + p->side - 1) / p->side, nss = (desc->grid_so2 + p->side - 1) / p->side;
     p->n_tiles = nsa * nss;
     p->n_nodes = (long long)desc->grid_thb * desc->grid_so2;
-    p->split = desc->grid_split > 0 ? std::min(desc->grid_split, p->n_tiles) : auto_split(p->dims, p->n_tiles, desc->max_batch);
+    p->max_split = desc->grid_split > 0 ? std::min(desc->grid_split, p->n_tiles)
+                                        : auto_split(p->dims, p->n_tiles, desc->max_batch);
 
     const size_t nb = (size_t)desc->max_batch;
     const size_t LL = (size_t)p->dims.LL;
@@ -867,8 +896,8 @@ hb_status_t hb_plan_create(const hb_plan_desc_t *desc, int device, hb_plan_t *ou
     if (st == HB_OK) st = dev_alloc(p, (void **)&p->d_z, sizeof(float) * nb * 6 * LL);
     if (st == HB_OK) st = dev_alloc(p, (void **)&p->d_det, sizeof(float2) * nb * HW);
     if (st == HB_OK && desc->lowpass == HB_LOWPASS_BAYES)
-        st = dev_alloc(p, (void **)&p->d_part, sizeof(float) * nb * p->split * kPartFields * LL);
-    if (st == HB_OK && desc->lowpass == HB_LOWPASS_BAYES && p->split > 1)
+        st = dev_alloc(p, (void **)&p->d_part, sizeof(float) * nb * p->max_split * kPartFields * LL);
+    if (st == HB_OK && desc->lowpass == HB_LOWPASS_BAYES && p->max_split > 1)
         st = dev_alloc(p, (void **)&p->d_gref, sizeof(float) * nb * LL);
     if (st == HB_OK) st = dev_alloc(p, (void **)&p->d_est, sizeof(float2) * nb * LL);
     if (st == HB_OK) st = dev_alloc(p, (void **)&p->d_work, 2 * sizeof(unsigned long long));
@@ -888,26 +917,9 @@ hb_status_t hb_plan_create(const hb_plan_desc_t *desc, int device, hb_plan_t *ou
         (void)hipGetLastError();
         p->scratch = nullptr;
     }
-    p->info.grid_split = p->split;
     p->info.n_tiles = p->n_tiles;
     p->info.n_nodes = p->n_nodes;
-    const SkipRule rule = skip_rule((double)p->n_nodes, desc->thb_max, desc->posterior_tolerance, p->split);
-    p->skip_log2 = rule.skip_log2;
-    p->band_log2 = rule.band_log2;
-    p->band_chunks = rule.band_chunks;
-    p->depth0 = p->skip_log2;
-    if (rule.bound > 0.0 && p->split == 1) {
-        // skipped over kept weight that moves a mean by at most the stated
-        // bound (a sixteenth left for rounding); the kernel of a split grid
-        // sees a part of the kept weight only and takes the a-priori threshold
-        const double ratio = rule.bound / desc->thb_max;
-        p->depth0 = (float)std::min<double>(p->skip_log2, std::max<double>(kMinSkipLog2, -std::log2(0.5 * ratio)));
-        p->cert_log2 = (float)std::log2(ratio * (1.0 - 1.0 / 16));
-    }
-    p->info.skip_bound = rule.bound;
-    p->info.skip_log2 = p->skip_log2;
-    p->info.band_log2 = p->band_log2;
-    p->info.band_chunks = p->band_chunks;
+    set_split(p, p->max_split);
     *out = p;
     return HB_OK;
 }
@@ -1022,6 +1034,7 @@ hb_status_t hb_set_forward_model(hb_plan_t p, const hb_forward_model_t *fm) {
         p->info.far_room = INFINITY;
     p->far_rho2 = std::isfinite(p->info.far_room) ? (float)(p->info.far_room * p->info.far_room) : INFINITY;
     p->info.posterior_kernel = p->use_mfma ? 0 : (p->precise ? 2 : 1);
+    set_split(p, d.grid_split == 0 && p->use_mfma ? 1 : p->max_split);
     if (hipMemcpy(p->d_tiles, tiles.data(), sizeof(float) * tiles.size(), hipMemcpyHostToDevice) != hipSuccess)
         return HB_ERR_DEVICE;
     if (hipMemcpy(p->d_lo, lo.data(), sizeof(float) * lo.size(), hipMemcpyHostToDevice) != hipSuccess)
@@ -1063,7 +1076,7 @@ hb_status_t hb_estimate_frames(hb_plan_t p, const void *d_frames, int32_t n_fram
                                void *stream) {
     const hb_status_t st = check_call(p, d_frames, n_frames, d_out);
     if (st != HB_OK || n_frames == 0) return st;
-    const CallBuffers cb{p->d_z, p->d_det, p->d_part, p->d_gref, p->d_est};
+    const CallBuffers cb{p->d_z, p->d_det, p->d_part, p->split > 1 ? p->d_gref : nullptr, p->d_est};
     return estimate(p, d_frames, n_frames, d_out, (hipStream_t)stream, cb, true);
 }
 
