@@ -106,6 +106,67 @@ HB_HD void ln_ratio_df(float R, float I, float &hi, float &lo) {
     df_add(hi, lo, fmaf(ef, LN2_LO, 2.0f * sl + tail + qlo_rel));
 }
 
+// (hi, lo) += (x, e), the rounding error of the sum carried in lo.
+HB_HD void carry_add(float &hi, float &lo, float x, float e) {
+#pragma clang fp contract(off)
+    float t, r;
+    two_sum(hi, x, t, r);
+    hi = t;
+    lo += r + e;
+}
+
+// (mh + ml) . (xh + xl) over three terms, rounded once: the leading products
+// and their sums carry their rounding errors (products by FMA).
+HB_HD float dot_df(const float *mh, const float *ml, const float xh[3], const float xl[3]) {
+#pragma clang fp contract(off)
+    float hi = mh[0] * xh[0];
+    float lo = fmaf(mh[0], xh[0], -hi) + fmaf(mh[0], xl[0], ml[0] * xh[0]);
+    for (int k = 1; k < 3; ++k) {
+        const float p = mh[k] * xh[k];
+        carry_add(hi, lo, p, fmaf(mh[k], xh[k], -p) + fmaf(mh[k], xl[k], ml[k] * xh[k]));
+    }
+    return hi + lo;
+}
+
+// ln I as a double-float for positive, finite float32 I, absolute error below
+// 9e-10 for I in [1e-4, 2] (9e-11 rms; measured against long double over 2e7
+// values): steps 2 and 3 of ln_ratio_df for I itself, the division by 2 + f as
+// a product with an approximate reciprocal whose error the low part takes up.
+HB_HD void ln_df(float I, float &hi, float &lo) {
+#pragma clang fp contract(off)
+    int e;
+    float m = frexpf(I, &e);
+    if (m < 0.70710678f) {
+        m *= 2.0f;
+        e -= 1;
+    }
+    const float f = m - 1.0f;   // exact
+    float dh, dl;
+    fast_two_sum(2.0f, f, dh, dl);
+#if defined(__HIP_DEVICE_COMPILE__)
+    const float rc = __builtin_amdgcn_rcpf(dh);
+#else
+    const float rc = 1.0f / dh;
+#endif
+    const float sh = f * rc;
+    const float sl = (fmaf(-sh, dh, f) - sh * dl) * rc;
+    const float s2 = sh * sh;
+    float p = 2.0f / 15.0f;
+    p = fmaf(p, s2, 2.0f / 13.0f);
+    p = fmaf(p, s2, 2.0f / 11.0f);
+    p = fmaf(p, s2, 2.0f / 9.0f);
+    p = fmaf(p, s2, 2.0f / 7.0f);
+    p = fmaf(p, s2, 2.0f / 5.0f);
+    p = fmaf(p, s2, 2.0f / 3.0f);
+    const float tail = fmaf(s2 * sh, p, 2.0f * s2 * sl);
+    const float LN2_HI = 0.693145751953125f;
+    const float LN2_LO = 1.4286068203094172e-06f;
+    const float ef = (float)e;
+    float s, r;
+    two_sum(ef * LN2_HI, 2.0f * sh, s, r);
+    fast_two_sum(s, r + fmaf(ef, LN2_LO, 2.0f * sl + tail), hi, lo);
+}
+
 #undef HB_HD
 
 }  // namespace hb

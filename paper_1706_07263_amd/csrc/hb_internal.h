@@ -104,8 +104,8 @@ constexpr double kDirectFarBudget = 1000.0;
 // frames, up to 7.3e-5 uM at |M|inf = 1.13e3 uM per unit log-attenuation and
 // 1.1-1.2e-4 uM at 1.4e3-3.1e3 (two levels).  Plans whose |M|inf exceeds
 // kK1PrecisionBudget, and every plan with three or more levels, run K1 with
-// double-float log-ratios, Haar cascade and Tikhonov apply (4x the ALU work:
-// kept off the default camera, |M|inf = 1.05e3).
+// double-float logs, block means and Tikhonov apply (more ALU work: kept off
+// the default camera, |M|inf = 1.05e3).
 constexpr double kK1PrecisionBudget = 1100.0;
 // Low parts of a chunk's node coordinates (3 coordinates x 16 nodes).
 constexpr int kLoFloats = 48;
@@ -234,11 +234,12 @@ struct HaarArgs {
     int dtype;
     float floor;
     float iref[3];           // float32 reference intensities exp(-mu_ref)
+    float ln_iref[6];        // their natural logs as double-floats: high parts, low parts
     const float *M;          // device, 6 floats (FP32 Tikhonov operator)
     float *z;                // [n][6][LL]: high parts R,G,B then low parts
     float2 *det;             // [n][H][W] spatial detail part (inverse Haar of the details)
     int project;             // project z onto the plane orthogonal to (1,1,1)
-    int df;                  // double-float log-ratios, Haar and Tikhonov (always from three levels on)
+    int df;                  // double-float logs, means and Tikhonov (always from three levels on)
 };
 
 struct PosteriorArgs {

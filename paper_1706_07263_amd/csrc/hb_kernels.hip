@@ -4,7 +4,9 @@
 //   K1  k_log_haar_reg<n>   log-attenuation, n-level 2D Haar, Tikhonov on the
 //                           directional coefficients and the inverse Haar of
 //                           that detail part, one block per thread (n <= 2)
-//       k_log_haar          the same in LDS-staged strips (any n)  (Eq. 1-2, 4, 5)
+//       k_log_haar          the same in LDS-staged strips (unaligned frames)
+//       k_log_haar_df       log-attenuation, block means and detail part in
+//                           double-float (any n)          (Eq. 1-2, 4, 5)
 //   K2a k_reference         best probe over the whole grid (split grids only)
 //   K2  k_posterior         posterior mean over the THb x SO2 grid on the
 //                           low-pass band (MFMA logits); with one split it
@@ -121,6 +123,18 @@ __device__ __forceinline__ void load4(const uint16_t *p, float v[4]) {
     v[3] = __uint_as_float(x.y & 0xffff0000u);
 }
 
+// z less its mean over the channels, as double-floats.
+__device__ __forceinline__ void remove_channel_mean(float zh[3], float zl[3]) {
+    float sh = zh[0], sl = zl[0];
+    df_add2(sh, sl, zh[1], zl[1]);
+    df_add2(sh, sl, zh[2], zl[2]);
+    // (sh + sl) / 3: the remainder of the leading quotient is exact by FMA
+    const float mh = sh * (1.0f / 3.0f);
+    const float ml = (fmaf(-3.0f, mh, sh) + sl) * (1.0f / 3.0f);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) df_add2(zh[k], zl[k], -mh, -ml);
+}
+
 struct StripPos {
     int f, br, blk0, nb, ncols, Wt, row0, col0, B;
 };
@@ -170,15 +184,8 @@ __device__ __forceinline__ float neg_log_ratio(float I, float R, float rinv) {
 // u equal those of y = -ln I (they differ by a per-block constant); the block
 // mean of y is recovered as -ln(R/I_ref) + mean(u) relative to the plan's
 // reference intensity I_ref.
-//
-// DF (three levels or more): u and the Haar cascade are double-floats (the
-// low parts in s_i once the intensities are used) and the Tikhonov operator
-// is applied with M as a double-float.  With float32 u, the rounding of u,
-// which grows with the block, reaches the maps through |M| (1e3 to 2e3 uM
-// per unit) at up to 1.3e-4 uM for three levels; the double-float form
-// leaves the rounding of the Tikhonov results and of the inverse Haar.
 // ---------------------------------------------------------------------------
-template <typename T, bool DF>
+template <typename T>
 __global__ __launch_bounds__(kBlockThreads) void k_log_haar(const T *__restrict__ frames, HaarArgs a) {
     __shared__ float s_i[3][kStripPixels];
     __shared__ float s_u[3][kStripPixels];
@@ -252,18 +259,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar(const T *__restrict_
             for (int c = tid; c < ncols; c += kBlockThreads) {
                 const float I = s_i[k][r * Wt + c];
                 const float R = (n > 0) ? s_r[k][c >> n] : I;
-                if constexpr (DF) {
-                    // with no level u = 0 exactly, and s_i keeps the intensity
-                    // that step 5 then reads as the block reference
-                    float uh = 0.0f, ul = 0.0f;
-                    if (n > 0) {
-                        ln_ratio_df(R, I, uh, ul);   // ln(R / I) = -ln(I / R)
-                        s_i[k][r * Wt + c] = ul;
-                    }
-                    s_u[k][r * Wt + c] = uh;
-                } else {
-                    s_u[k][r * Wt + c] = neg_log_ratio(I, R, 1.0f / R);
-                }
+                s_u[k][r * Wt + c] = neg_log_ratio(I, R, 1.0f / R);
             }
     __syncthreads();
 
@@ -277,36 +273,12 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar(const T *__restrict_
                 const int cg = q / 3, k = q - 3 * cg, c = cg * g2;
                 float *u = s_u[k];
                 const int i0 = r * Wt + c, i1 = i0 + h, i2 = (r + h) * Wt + c, i3 = i2 + h;
-                if constexpr (DF) {
-                    const float *ul = s_i[k];
-                    float ah = u[i0], al = ul[i0], bh = u[i2], bl = ul[i2];
-                    float ch = ah, cl = al, dh = bh, dl = bl;
-                    df_add2(ah, al, u[i1], ul[i1]);     // w0 + w1
-                    df_add2(bh, bl, u[i3], ul[i3]);     // w2 + w3
-                    df_add2(ch, cl, -u[i1], -ul[i1]);   // w0 - w1
-                    df_add2(dh, dl, -u[i3], -ul[i3]);   // w2 - w3
-                    float llh = ah, lll = al, d1h = ah, d1l = al, d2h = ch, d2l = cl, d3h = ch, d3l = cl;
-                    df_add2(llh, lll, bh, bl);
-                    df_add2(d1h, d1l, -bh, -bl);
-                    df_add2(d2h, d2l, -dh, -dl);
-                    df_add2(d3h, d3l, dh, dl);
-                    float *vl = s_i[k];
-                    u[i0] = 0.5f * llh;
-                    vl[i0] = 0.5f * lll;
-                    u[i2] = 0.5f * d1h;
-                    vl[i2] = 0.5f * d1l;
-                    u[i3] = 0.5f * d2h;
-                    vl[i3] = 0.5f * d2l;
-                    u[i1] = 0.5f * d3h;
-                    vl[i1] = 0.5f * d3l;
-                } else {
-                    const float w0 = u[i0], w1 = u[i1];
-                    const float w2 = u[i2], w3 = u[i3];
-                    u[i0] = 0.5f * ((w0 + w1) + (w2 + w3));
-                    u[i2] = 0.5f * ((w0 + w1) - (w2 + w3));
-                    u[i3] = 0.5f * ((w0 - w1) - (w2 - w3));
-                    u[i1] = 0.5f * ((w0 - w1) + (w2 - w3));
-                }
+                const float w0 = u[i0], w1 = u[i1];
+                const float w2 = u[i2], w3 = u[i3];
+                u[i0] = 0.5f * ((w0 + w1) + (w2 + w3));
+                u[i2] = 0.5f * ((w0 + w1) - (w2 + w3));
+                u[i3] = 0.5f * ((w0 - w1) - (w2 - w3));
+                u[i1] = 0.5f * ((w0 - w1) + (w2 - w3));
             }
         __syncthreads();
     }
@@ -322,10 +294,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar(const T *__restrict_
             const float R = (n > 0) ? s_r[k][j] : s_i[k][j];
             float zh, zl;
             ln_ratio_df(a.iref[k], R, zh, zl);
-            if constexpr (DF)
-                df_add2(zh, zl, s_u[k][j << n] * invB, n > 0 ? s_i[k][j << n] * invB : 0.0f);
-            else
-                df_add(zh, zl, s_u[k][j << n] * invB);
+            df_add(zh, zl, s_u[k][j << n] * invB);
             const size_t o = (size_t)s.br * d.wl + s.blk0 + j;
             a.z[((size_t)s.f * 6 + k) * d.LL + o] = zh;
             a.z[((size_t)s.f * 6 + 3 + k) * d.LL + o] = zl;
@@ -336,20 +305,11 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar(const T *__restrict_
             for (int k = 0; k < 3; ++k) {
                 const float R = (n > 0) ? s_r[k][j] : s_i[k][j];
                 ln_ratio_df(a.iref[k], R, zh[k], zl[k]);
-                if constexpr (DF)
-                    df_add2(zh[k], zl[k], s_u[k][j << n] * invB, n > 0 ? s_i[k][j << n] * invB : 0.0f);
-                else
-                    df_add(zh[k], zl[k], s_u[k][j << n] * invB);
+                df_add(zh[k], zl[k], s_u[k][j << n] * invB);
             }
-            float sh = zh[0], sl = zl[0];
-            df_add2(sh, sl, zh[1], zl[1]);
-            df_add2(sh, sl, zh[2], zl[2]);
-            // (sh + sl) / 3: the remainder of the leading quotient is exact by FMA
-            const float mh = sh * (1.0f / 3.0f);
-            const float ml = (fmaf(-3.0f, mh, sh) + sl) * (1.0f / 3.0f);
+            remove_channel_mean(zh, zl);
             const size_t o = (size_t)s.br * d.wl + s.blk0 + j;
             for (int k = 0; k < 3; ++k) {
-                df_add2(zh[k], zl[k], -mh, -ml);
                 a.z[((size_t)s.f * 6 + k) * d.LL + o] = zh[k];
                 a.z[((size_t)s.f * 6 + 3 + k) * d.LL + o] = zl[k];
             }
@@ -366,22 +326,8 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar(const T *__restrict_
             float ox = 0.0f, oy = 0.0f;
             if (((r | c) & (B - 1)) != 0) {
                 const float d0 = s_u[0][r * Wt + c], d1 = s_u[1][r * Wt + c], d2 = s_u[2][r * Wt + c];
-                if constexpr (DF) {
-                    // every low part is read before this thread overwrites its element
-                    const float e0 = s_i[0][r * Wt + c], e1 = s_i[1][r * Wt + c], e2 = s_i[2][r * Wt + c];
-                    float xh = 0.0f, xl = 0.0f, yh = 0.0f, yl = 0.0f;
-                    df_mul_add(xh, xl, m0, a.M[8], d0, e0);
-                    df_mul_add(xh, xl, m1, a.M[9], d1, e1);
-                    df_mul_add(xh, xl, m2, a.M[10], d2, e2);
-                    df_mul_add(yh, yl, m3, a.M[11], d0, e0);
-                    df_mul_add(yh, yl, m4, a.M[12], d1, e1);
-                    df_mul_add(yh, yl, m5, a.M[13], d2, e2);
-                    ox = xh + xl;
-                    oy = yh + yl;
-                } else {
-                    ox = fmaf(m0, d0, fmaf(m1, d1, m2 * d2));
-                    oy = fmaf(m3, d0, fmaf(m4, d1, m5 * d2));
-                }
+                ox = fmaf(m0, d0, fmaf(m1, d1, m2 * d2));
+                oy = fmaf(m3, d0, fmaf(m4, d1, m5 * d2));
             }
             s_i[0][r * Wt + c] = ox;
             s_i[1][r * Wt + c] = oy;
@@ -476,15 +422,13 @@ __device__ __forceinline__ void store_row(float2 *p, const float2 *o) {
     }
 }
 
-template <typename T, int N, bool DF>
+template <typename T, int N>
 __global__ __launch_bounds__(kBlockThreads) void k_log_haar_reg(const T *__restrict__ frames, HaarArgs a) {
     constexpr int BW = 1 << N, NP = BW * BW;
     const Dims &d = a.d;
-    const long long idx = (long long)blockIdx.x * kBlockThreads + threadIdx.x;
-    if (idx >= (long long)a.n_frames * d.LL) return;
-    const int f = (int)(idx / d.LL);
-    const long long q = idx - (long long)f * d.LL;
-    const int br = (int)(q / d.wl), bc = (int)(q - (long long)br * d.wl);
+    const unsigned q = blockIdx.x * kBlockThreads + threadIdx.x, f = blockIdx.y;   // block of frame f
+    if (q >= (unsigned)d.LL) return;
+    const int br = (int)(q / (unsigned)d.wl), bc = (int)(q - (unsigned)br * (unsigned)d.wl);
     const int row0 = br << N, col0 = bc << N;
     const T *__restrict__ base = frames + ((size_t)f * d.H * d.W + (size_t)row0 * d.W + col0) * 3;
 
@@ -523,19 +467,11 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar_reg(const T *__restr
     }
 
     // 3. Log-ratio to the block mean; 4. Haar in place (window * H, Eq. 1-2).
-    //    DF: u, the cascade and (step 6) the Tikhonov apply as double-floats
-    //    (low parts in ul), as in the strip kernel.
-    float ul[3][NP];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         const float rinv = 1.0f / R[k];
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            if constexpr (DF)
-                ln_ratio_df(R[k], I[k][i], u[k][i], ul[k][i]);   // ln(R / I) = -ln(I / R)
-            else
-                u[k][i] = neg_log_ratio(I[k][i], R[k], rinv);
-        }
+        for (int i = 0; i < NP; ++i) u[k][i] = neg_log_ratio(I[k][i], R[k], rinv);
 #pragma unroll
         for (int l = 1; l <= N; ++l) {
             const int h = 1 << (l - 1), g2 = 2 * h;
@@ -544,34 +480,12 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar_reg(const T *__restr
 #pragma unroll
                 for (int c = 0; c < BW; c += g2) {
                     const int i0 = r * BW + c, i1 = i0 + h, i2 = (r + h) * BW + c, i3 = i2 + h;
-                    if constexpr (DF) {
-                        float ah = u[k][i0], al = ul[k][i0], bh = u[k][i2], bl = ul[k][i2];
-                        float ch = ah, cl = al, dh = bh, dl = bl;
-                        df_add2(ah, al, u[k][i1], ul[k][i1]);     // w0 + w1
-                        df_add2(bh, bl, u[k][i3], ul[k][i3]);     // w2 + w3
-                        df_add2(ch, cl, -u[k][i1], -ul[k][i1]);   // w0 - w1
-                        df_add2(dh, dl, -u[k][i3], -ul[k][i3]);   // w2 - w3
-                        float llh = ah, lll = al, d1h = ah, d1l = al, d2h = ch, d2l = cl, d3h = ch, d3l = cl;
-                        df_add2(llh, lll, bh, bl);
-                        df_add2(d1h, d1l, -bh, -bl);
-                        df_add2(d2h, d2l, -dh, -dl);
-                        df_add2(d3h, d3l, dh, dl);
-                        u[k][i0] = 0.5f * llh;
-                        ul[k][i0] = 0.5f * lll;
-                        u[k][i2] = 0.5f * d1h;
-                        ul[k][i2] = 0.5f * d1l;
-                        u[k][i3] = 0.5f * d2h;
-                        ul[k][i3] = 0.5f * d2l;
-                        u[k][i1] = 0.5f * d3h;
-                        ul[k][i1] = 0.5f * d3l;
-                    } else {
-                        const float w0 = u[k][i0], w1 = u[k][i1];
-                        const float w2 = u[k][i2], w3 = u[k][i3];
-                        u[k][i0] = 0.5f * ((w0 + w1) + (w2 + w3));
-                        u[k][i2] = 0.5f * ((w0 + w1) - (w2 + w3));
-                        u[k][i3] = 0.5f * ((w0 - w1) - (w2 - w3));
-                        u[k][i1] = 0.5f * ((w0 - w1) + (w2 - w3));
-                    }
+                    const float w0 = u[k][i0], w1 = u[k][i1];
+                    const float w2 = u[k][i2], w3 = u[k][i3];
+                    u[k][i0] = 0.5f * ((w0 + w1) + (w2 + w3));
+                    u[k][i2] = 0.5f * ((w0 + w1) - (w2 + w3));
+                    u[k][i3] = 0.5f * ((w0 - w1) - (w2 - w3));
+                    u[k][i1] = 0.5f * ((w0 - w1) + (w2 - w3));
                 }
         }
     }
@@ -582,20 +496,9 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar_reg(const T *__restr
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         ln_ratio_df(a.iref[k], R[k], zh[k], zl[k]);
-        if constexpr (DF)
-            df_add2(zh[k], zl[k], u[k][0] * invB, ul[k][0] * invB);
-        else
-            df_add(zh[k], zl[k], u[k][0] * invB);
+        df_add(zh[k], zl[k], u[k][0] * invB);
     }
-    if (a.project) {
-        float sh = zh[0], sl = zl[0];
-        df_add2(sh, sl, zh[1], zl[1]);
-        df_add2(sh, sl, zh[2], zl[2]);
-        const float mh = sh * (1.0f / 3.0f);
-        const float ml = (fmaf(-3.0f, mh, sh) + sl) * (1.0f / 3.0f);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) df_add2(zh[k], zl[k], -mh, -ml);
-    }
+    if (a.project) remove_channel_mean(zh, zl);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         a.z[((size_t)f * 6 + k) * d.LL + q] = zh[k];
@@ -611,20 +514,8 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar_reg(const T *__restr
         o[0][i] = o[1][i] = 0.0f;
         if (i != 0) {
             const float d0 = u[0][i], d1 = u[1][i], d2 = u[2][i];
-            if constexpr (DF) {
-                float xh = 0.0f, xl = 0.0f, yh = 0.0f, yl = 0.0f;
-                df_mul_add(xh, xl, m0, a.M[8], d0, ul[0][i]);
-                df_mul_add(xh, xl, m1, a.M[9], d1, ul[1][i]);
-                df_mul_add(xh, xl, m2, a.M[10], d2, ul[2][i]);
-                df_mul_add(yh, yl, m3, a.M[11], d0, ul[0][i]);
-                df_mul_add(yh, yl, m4, a.M[12], d1, ul[1][i]);
-                df_mul_add(yh, yl, m5, a.M[13], d2, ul[2][i]);
-                o[0][i] = xh + xl;
-                o[1][i] = yh + yl;
-            } else {
-                o[0][i] = fmaf(m0, d0, fmaf(m1, d1, m2 * d2));
-                o[1][i] = fmaf(m3, d0, fmaf(m4, d1, m5 * d2));
-            }
+            o[0][i] = fmaf(m0, d0, fmaf(m1, d1, m2 * d2));
+            o[1][i] = fmaf(m3, d0, fmaf(m4, d1, m5 * d2));
         }
     }
 #pragma unroll
@@ -649,6 +540,117 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar_reg(const T *__restr
         float2 row[BW];
 #pragma unroll
         for (int c = 0; c < BW; ++c) row[c] = make_float2(o[0][r * BW + c], o[1][r * BW + c]);
+        store_row<BW>(a.det + ((size_t)f * d.H + row0 + r) * d.W + col0, row);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// K1, double-float variant (three or more levels, or |M| above
+// kK1PrecisionBudget).  With float32 log-ratios their rounding, which grows
+// with the block, reaches the maps through |M| (1e3 to 2e3 uM per unit) at up
+// to 1.3e-4 uM for three levels; here the log-attenuations, their block mean
+// and the Tikhonov apply are double-floats and each detail value is rounded
+// once.  The Haar transform is orthonormal, so what the Tikhonov operator M
+// makes of the directional coefficients recomposes to M (y - block mean of y):
+// neither the transform nor its inverse has to be formed.
+//
+// One thread takes a 4 x 4 sub-block (the block itself up to two levels); the
+// 4^(N - 2) threads of a block are neighbouring lanes in Z order and sum their
+// means by lane exchanges (every lane gets the same bits).  VEC: the frames
+// pointer is aligned to BW stored values.  Bound by VALU issue (about 180
+// operations per pixel; 135 registers, three waves per SIMD): four 1920x1080
+// frames at three levels 64 us; the strips in LDS with a double-float Haar
+// cascade that this replaces took 212.
+// ---------------------------------------------------------------------------
+template <typename T, int N, bool VEC>
+__global__ __launch_bounds__(kBlockThreads) void k_log_haar_df(const T *__restrict__ frames, HaarArgs a) {
+    constexpr int SB = N < 2 ? N : 2, BW = 1 << SB, UP = N - SB;
+    const Dims &d = a.d;
+    const unsigned idx = blockIdx.x * kBlockThreads + threadIdx.x, f = blockIdx.y;
+    const unsigned q = idx >> (2 * UP);            // block of frame f
+    if (q >= (unsigned)d.LL) return;               // all lanes of a block or none
+    const int sub = (int)(idx & ((1 << (2 * UP)) - 1));
+    int sr = 0, sc = 0;   // Z order: even bits column, odd bits row
+#pragma unroll
+    for (int l = 0; l < UP; ++l) {
+        sc |= (sub >> (2 * l) & 1) << l;
+        sr |= (sub >> (2 * l + 1) & 1) << l;
+    }
+    const int br = (int)(q / (unsigned)d.wl), bc = (int)(q - (unsigned)br * (unsigned)d.wl);
+    const int row0 = (br << N) + (sr << SB), col0 = (bc << N) + (sc << SB);
+    const T *__restrict__ base = frames + ((size_t)f * d.H * d.W + (size_t)row0 * d.W + col0) * 3;
+
+    // Loads (all issued first), clamp, ln I.  h[r][3 c + k] + l[r][3 c + k].
+    float h[BW][3 * BW], l[BW][3 * BW];
+#pragma unroll
+    for (int r = 0; r < BW; ++r)
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const T *p = base + (size_t)r * d.W * 3 + t * BW;
+            if constexpr (VEC)
+                load_run<T, BW>(p, &h[r][t * BW]);
+            else
+#pragma unroll
+                for (int e = 0; e < BW; ++e) h[r][t * BW + e] = load_px(p, e);
+        }
+    // Block mean of ln I: sums with the rounding errors carried.
+    float mh[3], ml[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        mh[k] = ml[k] = 0.0f;
+#pragma unroll
+        for (int r = 0; r < BW; ++r)
+#pragma unroll
+            for (int c = 0; c < BW; ++c) {
+                const float x = h[r][3 * c + k];
+                ln_df((x < a.floor) ? a.floor : x, h[r][3 * c + k], l[r][3 * c + k]);   // NaN stays NaN
+                carry_add(mh[k], ml[k], h[r][3 * c + k], l[r][3 * c + k]);
+            }
+#pragma unroll
+        for (int o = 1; o < 1 << (2 * UP); o <<= 1) {
+            const float xh = __shfl_xor(mh[k], o), xl = __shfl_xor(ml[k], o);
+            float s, e;
+            two_sum(mh[k], xh, s, e);
+            mh[k] = s;
+            ml[k] = (ml[k] + xl) + e;
+        }
+        const float inv = 1.0f / (float)(1 << (2 * N));   // exact
+        fast_two_sum(mh[k] * inv, ml[k] * inv, mh[k], ml[k]);
+    }
+
+    // Centred low-pass observation z = ln I_ref - mean ln I, optionally
+    // without its mean over the channels (illumination term).
+    if (sub == 0) {
+        float zh[3], zl[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            zh[k] = a.ln_iref[k];
+            zl[k] = a.ln_iref[3 + k];
+            df_add2(zh[k], zl[k], -mh[k], -ml[k]);
+        }
+        if (a.project) remove_channel_mean(zh, zl);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            a.z[((size_t)f * 6 + k) * d.LL + q] = zh[k];
+            a.z[((size_t)f * 6 + 3 + k) * d.LL + q] = zl[k];
+        }
+    }
+
+    // Detail part M (y - mean y) = M (mean ln I - ln I), each value a
+    // compensated dot product.
+#pragma unroll
+    for (int r = 0; r < BW; ++r) {
+        float2 row[BW];
+#pragma unroll
+        for (int c = 0; c < BW; ++c) {
+            float dh[3], dl[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                two_sum(mh[k], -h[r][3 * c + k], dh[k], dl[k]);
+                dl[k] += ml[k] - l[r][3 * c + k];
+            }
+            row[c] = make_float2(dot_df(a.M, a.M + 8, dh, dl), dot_df(a.M + 3, a.M + 11, dh, dl));
+        }
         store_row<BW>(a.det + ((size_t)f * d.H + row0 + r) * d.W + col0, row);
     }
 }
@@ -1184,7 +1186,7 @@ __device__ float far_gap_max(const PosteriorArgs &a, const WaveWork &w, const fl
     return mx;
 }
 
-// Fused recomposition for one split and n <= 2, in units of V pixels along a
+// Fused recomposition for one split and n <= 3, in units of V pixels along a
 // row, from the estimates of the region's pixels: the maps of the whole region,
 // (8 x 2^n) x (16 x 2^n) pixels, or (RT == 1) those of the 32 pixels of one tile.
 template <int RT, int V>
@@ -1425,14 +1427,6 @@ __device__ __forceinline__ float plus_quotient(float base, float nh, float nl, f
     float s, e;
     two_sum(base, q, s, e);
     return s + (e + (fmaf(-q, dh, nh) + fmaf(-q, dl, nl)) / dh);
-}
-
-// (hi, lo) += (x, e), the rounding error of the sum carried in lo.
-__device__ __forceinline__ void carry_add(float &hi, float &lo, float x, float e) {
-    float t, r;
-    two_sum(hi, x, t, r);
-    hi = t;
-    lo += r + e;
 }
 
 template <int NW, int RT, bool DFC>
@@ -2220,13 +2214,11 @@ template <int V>
 __global__ __launch_bounds__(kBlockThreads) void k_recompose(RecomposeArgs a) {
     const Dims &d = a.d;
     const int n = d.levels, B = 1 << n;
-    const long long idx = (long long)blockIdx.x * kBlockThreads + threadIdx.x;
-    if (idx >= (long long)a.n_frames * d.LL * B) return;
-    const long long blk = idx >> n;
+    const unsigned idx = blockIdx.x * kBlockThreads + threadIdx.x, f = blockIdx.y;
+    const unsigned q = idx >> n;   // block of frame f
+    if (q >= (unsigned)d.LL) return;
     const int r = (int)(idx & (B - 1));
-    const int f = (int)(blk / d.LL);
-    const long long q = blk - (long long)f * d.LL;
-    const int br = (int)(q / d.wl), bc = (int)(q - (long long)br * d.wl);
+    const int br = (int)(q / (unsigned)d.wl), bc = (int)(q - (unsigned)br * (unsigned)d.wl);
     const float2 e = lowpass_estimate(a, f, q);
     if (r == 0) a.est[(size_t)f * d.LL + q] = e;
     const size_t row = ((size_t)f * d.H + ((size_t)br << n) + r) * d.W + ((size_t)bc << n);
@@ -2247,35 +2239,45 @@ hipError_t launch_tikhonov_fp64(const double *d_in, double *d_out, float *d_mf, 
 namespace {
 
 template <typename T, int N>
-void launch_reg(const void *frames, const HaarArgs &b, long long blocks, hipStream_t s) {
-    if (b.df)
-        hipLaunchKernelGGL((k_log_haar_reg<T, N, true>), dim3((unsigned)blocks), dim3(kBlockThreads), 0, s,
+void launch_df(const void *frames, const HaarArgs &b, bool aligned, hipStream_t s) {
+    constexpr int kPerBlock = 1 << (2 * (N < 2 ? 0 : N - 2));   // threads
+    const dim3 blocks((unsigned)((b.d.LL * kPerBlock + kBlockThreads - 1) / kBlockThreads), (unsigned)b.n_frames);
+    if (aligned)
+        hipLaunchKernelGGL((k_log_haar_df<T, N, true>), blocks, dim3(kBlockThreads), 0, s,
                            (const T *)frames, b);
     else
-        hipLaunchKernelGGL((k_log_haar_reg<T, N, false>), dim3((unsigned)blocks), dim3(kBlockThreads), 0, s,
+        hipLaunchKernelGGL((k_log_haar_df<T, N, false>), blocks, dim3(kBlockThreads), 0, s,
                            (const T *)frames, b);
 }
 
 template <typename T>
 void launch_k1(const void *frames, const HaarArgs &b, hipStream_t s) {
     const int n = b.d.levels;
-    const bool aligned = ((uintptr_t)frames % ((size_t)(1 << n) * sizeof(T))) == 0;
-    HaarArgs c = b;
-    c.vec4 = ((uintptr_t)frames % (4 * sizeof(T))) == 0;
-    if (n <= 2 && aligned) {
-        const long long blocks = ((long long)b.n_frames * b.d.LL + kBlockThreads - 1) / kBlockThreads;
-        if (n == 0) launch_reg<T, 0>(frames, b, blocks, s);
-        else if (n == 1) launch_reg<T, 1>(frames, b, blocks, s);
-        else launch_reg<T, 2>(frames, b, blocks, s);
-    } else {
-        const long long grid = (long long)b.n_frames * b.d.hl * b.d.strips_per_row;
-        // Up to two levels the strip kernel keeps the register kernel's bits.
-        if (n >= 3 || b.df)
-            hipLaunchKernelGGL((k_log_haar<T, true>), dim3((unsigned)grid), dim3(kBlockThreads), 0, s,
-                               (const T *)frames, c);
+    // rows start at multiples of the vector, so the pointer decides
+    const bool aligned = ((uintptr_t)frames % ((size_t)(1 << (n < 2 ? n : 2)) * sizeof(T))) == 0;
+    if (n >= 3 || b.df) {
+        switch (n) {
+            case 0: launch_df<T, 0>(frames, b, aligned, s); break;
+            case 1: launch_df<T, 1>(frames, b, aligned, s); break;
+            case 2: launch_df<T, 2>(frames, b, aligned, s); break;
+            case 3: launch_df<T, 3>(frames, b, aligned, s); break;
+            case 4: launch_df<T, 4>(frames, b, aligned, s); break;
+            default: launch_df<T, 5>(frames, b, aligned, s); break;
+        }
+    } else if (aligned) {
+        const dim3 g((unsigned)((b.d.LL + kBlockThreads - 1) / kBlockThreads), (unsigned)b.n_frames), t(kBlockThreads);
+        if (n == 0)
+            hipLaunchKernelGGL((k_log_haar_reg<T, 0>), g, t, 0, s, (const T *)frames, b);
+        else if (n == 1)
+            hipLaunchKernelGGL((k_log_haar_reg<T, 1>), g, t, 0, s, (const T *)frames, b);
         else
-            hipLaunchKernelGGL((k_log_haar<T, false>), dim3((unsigned)grid), dim3(kBlockThreads), 0, s,
-                               (const T *)frames, c);
+            hipLaunchKernelGGL((k_log_haar_reg<T, 2>), g, t, 0, s, (const T *)frames, b);
+    } else {
+        // the strip kernel keeps the register kernel's bits
+        HaarArgs c = b;
+        c.vec4 = ((uintptr_t)frames % (4 * sizeof(T))) == 0;
+        const long long grid = (long long)b.n_frames * b.d.hl * b.d.strips_per_row;
+        hipLaunchKernelGGL((k_log_haar<T>), dim3((unsigned)grid), dim3(kBlockThreads), 0, s, (const T *)frames, c);
     }
 }
 
@@ -2346,7 +2348,7 @@ hipError_t launch_recompose(int n_frames, const RecomposeArgs &a, hipStream_t s)
     RecomposeArgs b = a;
     b.n_frames = n_frames;
     const int B = 1 << a.d.levels;
-    const long long blocks = ((long long)n_frames * a.d.LL * B + kBlockThreads - 1) / kBlockThreads;
+    const dim3 blocks((unsigned)((a.d.LL * B + kBlockThreads - 1) / kBlockThreads), (unsigned)n_frames);
     // widest vector the block width and every map pointer allow
     auto fits = [&](int v) {
         if (B % v) return false;
@@ -2355,11 +2357,11 @@ hipError_t launch_recompose(int n_frames, const RecomposeArgs &a, hipStream_t s)
         return true;
     };
     if (fits(4))
-        hipLaunchKernelGGL(k_recompose<4>, dim3((unsigned)blocks), dim3(kBlockThreads), 0, s, b);
+        hipLaunchKernelGGL(k_recompose<4>, blocks, dim3(kBlockThreads), 0, s, b);
     else if (fits(2))
-        hipLaunchKernelGGL(k_recompose<2>, dim3((unsigned)blocks), dim3(kBlockThreads), 0, s, b);
+        hipLaunchKernelGGL(k_recompose<2>, blocks, dim3(kBlockThreads), 0, s, b);
     else
-        hipLaunchKernelGGL(k_recompose<1>, dim3((unsigned)blocks), dim3(kBlockThreads), 0, s, b);
+        hipLaunchKernelGGL(k_recompose<1>, blocks, dim3(kBlockThreads), 0, s, b);
     return hipGetLastError();
 }
 

@@ -703,6 +703,10 @@ hb_status_t estimate(hb_plan_s *p, const void *d_frames, int32_t n_frames, const
     ha.dtype = p->desc.frame_dtype;
     ha.floor = (float)p->desc.intensity_floor;
     for (int k = 0; k < 3; ++k) ha.iref[k] = p->iref[k];
+    for (int k = 0; k < 3; ++k) {
+        ha.ln_iref[k] = (float)-p->info.mu_ref[k];
+        ha.ln_iref[3 + k] = (float)(-p->info.mu_ref[k] - (double)ha.ln_iref[k]);
+    }
     ha.M = p->d_mf;
     ha.z = cb.z;
     ha.det = cb.det;
@@ -752,8 +756,9 @@ hb_status_t estimate(hb_plan_s *p, const void *d_frames, int32_t n_frames, const
             pa.gref = cb.gref;
             if (launch_reference(pa, s) != hipSuccess) return HB_ERR_DEVICE;
         }
-        // One split, MFMA kernel, n <= 2: the posterior writes the maps.
-        fused = p->use_mfma && p->split == 1 && p->dims.levels <= 2;
+        // One split, MFMA kernel, n <= 3: the posterior writes the maps (from
+        // four levels on its few workgroups would write large regions).
+        fused = p->use_mfma && p->split == 1 && p->dims.levels <= 3;
         if (fused) {
             const int B = 1 << p->dims.levels;
             auto fits = [&](int v) {

@@ -601,6 +601,38 @@ def test_register_and_strip_haar_kernels_agree_bitwise(torch_cuda, levels, dtype
     run.close()
 
 
+@pytest.mark.parametrize("h,w,levels", [(8, 8, 3), (40, 1304, 3), (48, 272, 4), (96, 160, 5)])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+def test_double_float_haar_kernel(torch_cuda, h, w, levels, dtype):
+    """Three to five levels: 4, 16 and 64 lanes share a block, the last
+    workgroup is partial and several frames follow one another.  Frames whose
+    pointer is off the vector width give the same bits; the detail part has
+    block mean zero and the maps match the oracle."""
+    torch = torch_cuda
+    frames = np.stack([synth.single_frame(h, w, config=78, stream=i, dtype=dtype)[0] for i in range(2)])
+    s = _settings(levels=levels, grid=64)
+    run = hbtest.GpuRun(w, h, s, dtype=dtype, max_batch=2)
+    host = frames.view(np.int16) if dtype == "bf16" else frames
+    flat = torch.from_numpy(np.ascontiguousarray(host).reshape(-1))
+    padded = torch.empty(flat.numel() + 1, dtype=flat.dtype, device="cuda")
+    padded[1:] = flat.cuda()
+    outs = []
+    for src in (flat.cuda().view(frames.shape), padded[1:].view(frames.shape)):
+        maps = [torch.full((2, h, w), float("nan"), device="cuda") for _ in range(4)]
+        run.plan.estimate(src, maps)
+        torch.cuda.synchronize()
+        outs.append((np.stack([m.cpu().numpy() for m in maps]), run.debug(run.hb.HB_DEBUG_LOWPASS_OBS, 1),
+                     run.debug(run.hb.HB_DEBUG_DETAILS, 1)))
+    for x, y in zip(outs[0], outs[1]):
+        assert np.array_equal(x, y, equal_nan=True)
+    B = 1 << levels
+    means = outs[0][2].astype(np.float64).reshape(h // B, B, w // B, B, 2).mean(axis=(1, 3))
+    # each of the block's values is within half a float32 ulp (2^-18 for |x| < 64) of one with mean zero
+    assert np.abs(means).max() <= 2.0 ** -18
+    hbtest.assert_maps_close(outs[0][0].transpose(1, 0, 2, 3), hbtest.run_oracle(frames, dtype, s), f"{h}x{w} L{levels} {dtype}")
+    run.close()
+
+
 @pytest.mark.parametrize("h,w,levels,split,offset", [
     (64, 96, 2, 1, 0),      # one split: the posterior kernel writes the maps
     (40, 72, 2, 1, 0),      # ragged wave tiles
