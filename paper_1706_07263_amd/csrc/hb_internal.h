@@ -238,6 +238,13 @@ struct HaarArgs {
     const float *M;          // device, 6 floats (FP32 Tikhonov operator)
     float *z;                // [n][6][LL]: high parts R,G,B then low parts
     float2 *det;             // [n][H][W] spatial detail part (inverse Haar of the details)
+    // Linear low-pass estimator: write the estimate and the maps too (z, det
+    // and est may then be null: not wanted).
+    int maps;
+    float2 *est;             // [n][LL] low-pass estimate
+    int vec;                 // pixels per map store: 1, 2 or 4 (pointer alignment)
+    float thb_eps;
+    float *hb, *hbo2, *thb, *so2;
     int project;             // project z onto the plane orthogonal to (1,1,1)
     int df;                  // double-float logs, means and Tikhonov (always from three levels on)
 };
@@ -314,6 +321,17 @@ hipError_t static_scratch(int device, void **ptr);
 // Launchers (hb_kernels.hip).  They only enqueue work.
 hipError_t launch_tikhonov_fp64(const double *d_in, double *d_out, float *d_mf, hipStream_t s);
 hipError_t launch_log_haar(const void *frames, int n_frames, const HaarArgs &a, hipStream_t s);
+// Vector loads of frames: block rows start at multiples of the vector, so the
+// pointer decides.
+inline bool vector_frames(const void *frames, const HaarArgs &a) {
+    const size_t item = a.dtype == HB_F32 ? 4 : 2;
+    return (uintptr_t)frames % (((size_t)1 << (a.d.levels < 2 ? a.d.levels : 2)) * item) == 0;
+}
+// Whether K1 takes these frames block by block (HaarArgs::maps is possible)
+// rather than in strips.
+inline bool log_haar_takes_blocks(const void *frames, const HaarArgs &a) {
+    return a.d.levels >= 3 || a.df || vector_frames(frames, a);
+}
 hipError_t launch_reference(const PosteriorArgs &a, hipStream_t s);
 hipError_t launch_posterior(const PosteriorArgs &a, bool mfma, hipStream_t s);
 hipError_t launch_recompose(int n_frames, const RecomposeArgs &a, hipStream_t s);

@@ -357,6 +357,50 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar(const T *__restrict_
                 make_float2(s_i[0][r * Wt + c], s_i[1][r * Wt + c]);
 }
 
+// Maps of V consecutive pixels (offset o) from their detail part and the
+// block's low-pass estimate e; vector stores when V > 1 (the host checks the
+// alignment of the map pointers).  Null maps are skipped.
+template <int V>
+__device__ __forceinline__ void write_maps(float *mhb, float *mox, float *mth, float *mso, float thb_eps, size_t o,
+                                           float2 e, const float2 *dp) {
+    float hb[V], ox[V], th[V], so[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        hb[i] = e.x + dp[i].x;
+        ox[i] = e.y + dp[i].y;
+        th[i] = hb[i] + ox[i];
+        so[i] = (th[i] > thb_eps) ? ox[i] / th[i] : __builtin_nanf("");
+    }
+    // streaming stores (non-temporal): the maps are not read again here
+    auto put = [&](float *m, const float *v) {
+        if (!m) return;
+        if constexpr (V == 4) {
+            __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, reinterpret_cast<f32x4 *>(m + o));
+        } else if constexpr (V == 2) {
+            __builtin_nontemporal_store(f32x2{v[0], v[1]}, reinterpret_cast<f32x2 *>(m + o));
+        } else {
+            __builtin_nontemporal_store(v[0], m + o);
+        }
+    };
+    put(mhb, hb);
+    put(mox, ox);
+    put(mth, th);
+    put(mso, so);
+}
+
+// Linear low-pass estimate offset + M z with M, the offset and z as
+// double-floats: the terms are about |M| |z| (~1e3 uM) while the estimate is
+// tens of uM.
+__device__ __forceinline__ float2 linear_estimate(const float *M, const float zh[3], const float zl[3]) {
+    float hh = M[6], hl = M[14], oh = M[7], ol = M[15];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        df_mul_add(hh, hl, M[k], M[8 + k], zh[k], zl[k]);
+        df_mul_add(oh, ol, M[3 + k], M[11 + k], zh[k], zl[k]);
+    }
+    return make_float2(hh + hl, oh + ol);
+}
+
 // ---------------------------------------------------------------------------
 // K1, register variant for n <= 2: one thread per 2^n x 2^n block, the block
 // held in registers (no LDS, no barriers), the strip kernel's arithmetic in
@@ -422,7 +466,30 @@ __device__ __forceinline__ void store_row(float2 *p, const float2 *o) {
     }
 }
 
-template <typename T, int N>
+// BW pixels of a block row at offset o: the detail part, and with the linear
+// low-pass estimator (MAPS) the four maps from it and the block's estimate e,
+// in stores of a.vec pixels.
+template <int BW, bool MAPS>
+__device__ __forceinline__ void put_row(const HaarArgs &a, size_t o, const float2 *row, float2 e) {
+    if (!MAPS || a.det) store_row<BW>(a.det + o, row);
+    if constexpr (MAPS) {
+        if (BW == 4 && a.vec == 4) {
+            write_maps<4>(a.hb, a.hbo2, a.thb, a.so2, a.thb_eps, o, e, row);
+        } else if (BW >= 2 && a.vec >= 2) {
+#pragma unroll
+            for (int c = 0; c + 2 <= BW; c += 2) write_maps<2>(a.hb, a.hbo2, a.thb, a.so2, a.thb_eps, o + c, e, row + c);
+        } else {
+#pragma unroll
+            for (int c = 0; c < BW; ++c) write_maps<1>(a.hb, a.hbo2, a.thb, a.so2, a.thb_eps, o + c, e, row + c);
+        }
+    }
+}
+
+// MAPS (linear low-pass estimator, no posterior): the estimate and the maps
+// too, so that neither the detail part nor the observation is read again.
+// Bound by HBM: sixteen 1920x1080 FP32 frames 254 us at 38 bytes a pixel, 5.0
+// TB/s (a plain copy reaches 5.1); K1 and the maps kernel took 287 for 47.
+template <typename T, int N, bool MAPS>
 __global__ __launch_bounds__(kBlockThreads) void k_log_haar_reg(const T *__restrict__ frames, HaarArgs a) {
     constexpr int BW = 1 << N, NP = BW * BW;
     const Dims &d = a.d;
@@ -499,10 +566,16 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar_reg(const T *__restr
         df_add(zh[k], zl[k], u[k][0] * invB);
     }
     if (a.project) remove_channel_mean(zh, zl);
+    if (!MAPS || a.z)
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        a.z[((size_t)f * 6 + k) * d.LL + q] = zh[k];
-        a.z[((size_t)f * 6 + 3 + k) * d.LL + q] = zl[k];
+        for (int k = 0; k < 3; ++k) {
+            a.z[((size_t)f * 6 + k) * d.LL + q] = zh[k];
+            a.z[((size_t)f * 6 + 3 + k) * d.LL + q] = zl[k];
+        }
+    float2 e = make_float2(0.0f, 0.0f);
+    if constexpr (MAPS) {
+        e = linear_estimate(a.M, zh, zl);
+        if (a.est) a.est[(size_t)f * d.LL + q] = e;
     }
 
     // 6. Tikhonov on the directional coefficients (low-pass slot 0); 7. the
@@ -540,7 +613,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar_reg(const T *__restr
         float2 row[BW];
 #pragma unroll
         for (int c = 0; c < BW; ++c) row[c] = make_float2(o[0][r * BW + c], o[1][r * BW + c]);
-        store_row<BW>(a.det + ((size_t)f * d.H + row0 + r) * d.W + col0, row);
+        put_row<BW, MAPS>(a, ((size_t)f * d.H + row0 + r) * d.W + col0, row, e);
     }
 }
 
@@ -562,7 +635,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar_reg(const T *__restr
 // frames at three levels 64 us; the strips in LDS with a double-float Haar
 // cascade that this replaces took 212.
 // ---------------------------------------------------------------------------
-template <typename T, int N, bool VEC>
+template <typename T, int N, bool VEC, bool MAPS>
 __global__ __launch_bounds__(kBlockThreads) void k_log_haar_df(const T *__restrict__ frames, HaarArgs a) {
     constexpr int SB = N < 2 ? N : 2, BW = 1 << SB, UP = N - SB;
     const Dims &d = a.d;
@@ -620,7 +693,8 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar_df(const T *__restri
 
     // Centred low-pass observation z = ln I_ref - mean ln I, optionally
     // without its mean over the channels (illumination term).
-    if (sub == 0) {
+    float2 e = make_float2(0.0f, 0.0f);
+    if (MAPS || sub == 0) {
         float zh[3], zl[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
@@ -629,10 +703,15 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar_df(const T *__restri
             df_add2(zh[k], zl[k], -mh[k], -ml[k]);
         }
         if (a.project) remove_channel_mean(zh, zl);
+        if (sub == 0 && (!MAPS || a.z))
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            a.z[((size_t)f * 6 + k) * d.LL + q] = zh[k];
-            a.z[((size_t)f * 6 + 3 + k) * d.LL + q] = zl[k];
+            for (int k = 0; k < 3; ++k) {
+                a.z[((size_t)f * 6 + k) * d.LL + q] = zh[k];
+                a.z[((size_t)f * 6 + 3 + k) * d.LL + q] = zl[k];
+            }
+        if constexpr (MAPS) {
+            e = linear_estimate(a.M, zh, zl);
+            if (sub == 0 && a.est) a.est[(size_t)f * d.LL + q] = e;
         }
     }
 
@@ -651,39 +730,8 @@ __global__ __launch_bounds__(kBlockThreads) void k_log_haar_df(const T *__restri
             }
             row[c] = make_float2(dot_df(a.M, a.M + 8, dh, dl), dot_df(a.M + 3, a.M + 11, dh, dl));
         }
-        store_row<BW>(a.det + ((size_t)f * d.H + row0 + r) * d.W + col0, row);
+        put_row<BW, MAPS>(a, ((size_t)f * d.H + row0 + r) * d.W + col0, row, e);
     }
-}
-
-// Maps of V consecutive pixels (offset o) from their detail part and the
-// block's low-pass estimate e; vector stores when V > 1 (the host checks the
-// alignment of the map pointers).  Null maps are skipped.
-template <int V>
-__device__ __forceinline__ void write_maps(float *mhb, float *mox, float *mth, float *mso, float thb_eps, size_t o,
-                                           float2 e, const float2 *dp) {
-    float hb[V], ox[V], th[V], so[V];
-#pragma unroll
-    for (int i = 0; i < V; ++i) {
-        hb[i] = e.x + dp[i].x;
-        ox[i] = e.y + dp[i].y;
-        th[i] = hb[i] + ox[i];
-        so[i] = (th[i] > thb_eps) ? ox[i] / th[i] : __builtin_nanf("");
-    }
-    // streaming stores (non-temporal): the maps are not read again here
-    auto put = [&](float *m, const float *v) {
-        if (!m) return;
-        if constexpr (V == 4) {
-            __builtin_nontemporal_store(f32x4{v[0], v[1], v[2], v[3]}, reinterpret_cast<f32x4 *>(m + o));
-        } else if constexpr (V == 2) {
-            __builtin_nontemporal_store(f32x2{v[0], v[1]}, reinterpret_cast<f32x2 *>(m + o));
-        } else {
-            __builtin_nontemporal_store(v[0], m + o);
-        }
-    };
-    put(mhb, hb);
-    put(mox, ox);
-    put(mth, th);
-    put(mso, so);
 }
 
 // V consecutive detail-part values from offset o (streaming loads).
@@ -2176,19 +2224,10 @@ __global__ __launch_bounds__(kBlockThreads) void k_posterior_direct(PosteriorArg
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float2 lowpass_estimate(const RecomposeArgs &a, int f, long long q) {
     if (a.lowpass == HB_LOWPASS_TIKHONOV) {
-        // offset + M z with M, the offset and z as double-floats: the terms
-        // are about |M| |z| (~1e3 uM) while the estimate is tens of uM.
         const long long LL = a.d.LL;
-        const float *zf = a.z + (size_t)f * 6 * LL;
-        const float *M = a.M;
-        float hh = M[6], hl = M[14], oh = M[7], ol = M[15];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const float zh = zf[k * LL + q], zl = zf[(3 + k) * LL + q];
-            df_mul_add(hh, hl, M[k], M[8 + k], zh, zl);
-            df_mul_add(oh, ol, M[3 + k], M[11 + k], zh, zl);
-        }
-        return make_float2(hh + hl, oh + ol);
+        const float *zf = a.z + (size_t)f * 6 * LL + q;
+        const float zh[3] = {zf[0], zf[LL], zf[2 * LL]}, zl[3] = {zf[3 * LL], zf[4 * LL], zf[5 * LL]};
+        return linear_estimate(a.M, zh, zl);
     }
     const long long LL = a.d.LL;
     const float *P = a.part + (size_t)f * a.split * kPartFields * LL + q;
@@ -2238,40 +2277,42 @@ hipError_t launch_tikhonov_fp64(const double *d_in, double *d_out, float *d_mf, 
 
 namespace {
 
-template <typename T, int N>
+template <typename T, int N, bool MAPS>
 void launch_df(const void *frames, const HaarArgs &b, bool aligned, hipStream_t s) {
     constexpr int kPerBlock = 1 << (2 * (N < 2 ? 0 : N - 2));   // threads
-    const dim3 blocks((unsigned)((b.d.LL * kPerBlock + kBlockThreads - 1) / kBlockThreads), (unsigned)b.n_frames);
+    const dim3 g((unsigned)((b.d.LL * kPerBlock + kBlockThreads - 1) / kBlockThreads), (unsigned)b.n_frames);
     if (aligned)
-        hipLaunchKernelGGL((k_log_haar_df<T, N, true>), blocks, dim3(kBlockThreads), 0, s,
-                           (const T *)frames, b);
+        hipLaunchKernelGGL((k_log_haar_df<T, N, true, MAPS>), g, dim3(kBlockThreads), 0, s, (const T *)frames, b);
     else
-        hipLaunchKernelGGL((k_log_haar_df<T, N, false>), blocks, dim3(kBlockThreads), 0, s,
-                           (const T *)frames, b);
+        hipLaunchKernelGGL((k_log_haar_df<T, N, false, MAPS>), g, dim3(kBlockThreads), 0, s, (const T *)frames, b);
+}
+
+template <typename T, int N, bool MAPS>
+void launch_reg(const void *frames, const HaarArgs &b, hipStream_t s) {
+    const dim3 g((unsigned)((b.d.LL + kBlockThreads - 1) / kBlockThreads), (unsigned)b.n_frames);
+    hipLaunchKernelGGL((k_log_haar_reg<T, N, MAPS>), g, dim3(kBlockThreads), 0, s, (const T *)frames, b);
+}
+
+template <typename T, bool MAPS>
+void launch_blocks(const void *frames, const HaarArgs &b, bool aligned, hipStream_t s) {
+    const bool df = b.d.levels >= 3 || b.df;
+    switch (b.d.levels) {
+        case 0: df ? launch_df<T, 0, MAPS>(frames, b, aligned, s) : launch_reg<T, 0, MAPS>(frames, b, s); break;
+        case 1: df ? launch_df<T, 1, MAPS>(frames, b, aligned, s) : launch_reg<T, 1, MAPS>(frames, b, s); break;
+        case 2: df ? launch_df<T, 2, MAPS>(frames, b, aligned, s) : launch_reg<T, 2, MAPS>(frames, b, s); break;
+        case 3: launch_df<T, 3, MAPS>(frames, b, aligned, s); break;
+        case 4: launch_df<T, 4, MAPS>(frames, b, aligned, s); break;
+        default: launch_df<T, 5, MAPS>(frames, b, aligned, s); break;
+    }
 }
 
 template <typename T>
 void launch_k1(const void *frames, const HaarArgs &b, hipStream_t s) {
-    const int n = b.d.levels;
-    // rows start at multiples of the vector, so the pointer decides
-    const bool aligned = ((uintptr_t)frames % ((size_t)(1 << (n < 2 ? n : 2)) * sizeof(T))) == 0;
-    if (n >= 3 || b.df) {
-        switch (n) {
-            case 0: launch_df<T, 0>(frames, b, aligned, s); break;
-            case 1: launch_df<T, 1>(frames, b, aligned, s); break;
-            case 2: launch_df<T, 2>(frames, b, aligned, s); break;
-            case 3: launch_df<T, 3>(frames, b, aligned, s); break;
-            case 4: launch_df<T, 4>(frames, b, aligned, s); break;
-            default: launch_df<T, 5>(frames, b, aligned, s); break;
-        }
-    } else if (aligned) {
-        const dim3 g((unsigned)((b.d.LL + kBlockThreads - 1) / kBlockThreads), (unsigned)b.n_frames), t(kBlockThreads);
-        if (n == 0)
-            hipLaunchKernelGGL((k_log_haar_reg<T, 0>), g, t, 0, s, (const T *)frames, b);
-        else if (n == 1)
-            hipLaunchKernelGGL((k_log_haar_reg<T, 1>), g, t, 0, s, (const T *)frames, b);
-        else
-            hipLaunchKernelGGL((k_log_haar_reg<T, 2>), g, t, 0, s, (const T *)frames, b);
+    const bool aligned = vector_frames(frames, b);
+    if (b.maps) {
+        launch_blocks<T, true>(frames, b, aligned, s);
+    } else if (log_haar_takes_blocks(frames, b)) {
+        launch_blocks<T, false>(frames, b, aligned, s);
     } else {
         // the strip kernel keeps the register kernel's bits
         HaarArgs c = b;

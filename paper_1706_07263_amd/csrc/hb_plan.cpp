@@ -646,6 +646,7 @@ struct CallBuffers {
     float *part;    // [n][split][kPartFields][LL] posterior partials (Bayesian low-pass)
     float *gref;    // [n][LL] global posterior reference (split grids), else null
     float2 *est;    // [n][LL] low-pass estimate
+    bool kept;      // hb_debug_copy shows them after the call
 };
 
 // Argument and state checks shared by both estimate calls (nothing launched).
@@ -712,11 +713,36 @@ hb_status_t estimate(hb_plan_s *p, const void *d_frames, int32_t n_frames, const
     ha.det = cb.det;
     ha.project = p->desc.illumination && p->desc.lowpass == HB_LOWPASS_BAYES;
     ha.df = p->k1_df;
+    const int B = 1 << p->dims.levels;
+    auto fits = [&](int v) {   // map stores of v pixels
+        if (B % v) return false;
+        for (const float *m : {d_out->hb, d_out->hbo2, d_out->thb, d_out->so2})
+            if (m && ((uintptr_t)m % (sizeof(float) * v)) != 0) return false;
+        return true;
+    };
+    const int vec = fits(4) ? 4 : (fits(2) ? 2 : 1);
+    // Linear low-pass estimator: K1 writes the maps.  A call whose
+    // intermediate buffers nobody sees leaves them unwritten.
+    bool fused = false;
+    if (p->desc.lowpass == HB_LOWPASS_TIKHONOV && log_haar_takes_blocks(d_frames, ha)) {
+        fused = true;
+        ha.maps = 1;
+        ha.est = cb.est;
+        if (!cb.kept) {
+            ha.z = nullptr;
+            ha.det = ha.est = nullptr;
+        }
+        ha.vec = vec;
+        ha.thb_eps = (float)p->desc.thb_eps;
+        ha.hb = d_out->hb;
+        ha.hbo2 = d_out->hbo2;
+        ha.thb = d_out->thb;
+        ha.so2 = d_out->so2;
+    }
 
     if (mark(0) != hipSuccess) return HB_ERR_DEVICE;
     if (launch_log_haar(d_frames, n_frames, ha, s) != hipSuccess) return HB_ERR_DEVICE;
     if (mark(1) != hipSuccess) return HB_ERR_DEVICE;
-    bool fused = false;
     if (p->desc.lowpass == HB_LOWPASS_BAYES) {
         PosteriorArgs pa{};
         pa.LL = p->dims.LL;
@@ -760,15 +786,8 @@ hb_status_t estimate(hb_plan_s *p, const void *d_frames, int32_t n_frames, const
         // four levels on its few workgroups would write large regions).
         fused = p->use_mfma && p->split == 1 && p->dims.levels <= 3;
         if (fused) {
-            const int B = 1 << p->dims.levels;
-            auto fits = [&](int v) {
-                if (B % v) return false;
-                for (const float *m : {d_out->hb, d_out->hbo2, d_out->thb, d_out->so2})
-                    if (m && ((uintptr_t)m % (sizeof(float) * v)) != 0) return false;
-                return true;
-            };
             pa.fuse = 1;
-            pa.vec = fits(4) ? 4 : (fits(2) ? 2 : 1);
+            pa.vec = vec;
             pa.levels = p->dims.levels;
             pa.H = p->dims.H;
             pa.W = p->dims.W;
@@ -1081,7 +1100,7 @@ hb_status_t hb_estimate_frames(hb_plan_t p, const void *d_frames, int32_t n_fram
                                void *stream) {
     const hb_status_t st = check_call(p, d_frames, n_frames, d_out);
     if (st != HB_OK || n_frames == 0) return st;
-    const CallBuffers cb{p->d_z, p->d_det, p->d_part, p->split > 1 ? p->d_gref : nullptr, p->d_est};
+    const CallBuffers cb{p->d_z, p->d_det, p->d_part, p->split > 1 ? p->d_gref : nullptr, p->d_est, true};
     return estimate(p, d_frames, n_frames, d_out, (hipStream_t)stream, cb, true);
 }
 

@@ -633,6 +633,45 @@ def test_double_float_haar_kernel(torch_cuda, h, w, levels, dtype):
     run.close()
 
 
+@pytest.mark.parametrize("h,w,levels,camera", [(33, 19, 0, "default"), (34, 30, 1, "default"), (36, 44, 2, "default"),
+                                               (36, 44, 2, "shifted"), (40, 72, 3, "default"), (64, 96, 5, "default")])
+def test_linear_maps_from_k1(torch_cuda, h, w, levels, camera):
+    """With the linear low-pass estimator K1 writes the maps itself; frames off
+    the vector width at up to two levels go through strips and the maps
+    kernel instead, and the allocation-free call writes no intermediate
+    buffers.  All give the same bits for any store width, leave a map that
+    was not asked for alone, and match the oracle."""
+    from paper_1706_07263_amd import hb
+    torch = torch_cuda
+    sp = synth.spectra() if camera == "default" else synth.alt_spectra(camera)
+    fr = np.stack([synth.single_frame(h, w, config=79, stream=i, sp=sp)[0] for i in range(2)])
+    s = _settings(levels=levels, grid=32)
+    run = hbtest.GpuRun(w, h, s, max_batch=2, lowpass=1, sp=sp)
+    flat = torch.from_numpy(fr.reshape(-1)).cuda()
+    padded = torch.empty(flat.numel() + 1, device="cuda")
+    padded[1:] = flat
+    want = None
+    for src in (flat.view(fr.shape), padded[1:].view(fr.shape)):
+        for offset in (0, 1, 2):
+            for noalloc in (False, True):
+                slab = torch.full((4, 2 * h * w + 4), -7.0, device="cuda")
+                maps = [m[offset:offset + 2 * h * w].view(2, h, w) for m in slab]
+                run.plan.estimate(src, [maps[0], maps[1], None, maps[3]], noalloc=noalloc)
+                torch.cuda.synchronize()
+                assert torch.all(maps[2] == -7.0)
+                got = [maps[k].cpu().numpy() for k in (0, 1, 3)]
+                want = got if want is None else want
+                for x, y in zip(got, want):
+                    assert np.array_equal(x, y, equal_nan=True), (offset, noalloc)
+    maps = run(fr)
+    hbtest.assert_maps_close(maps, hbtest.run_oracle(fr, "f32", s, lowpass=1, sp=sp), f"linear {h}x{w} L{levels} {camera}")
+    B = 1 << levels
+    est, det = run.debug(hb.HB_DEBUG_LOWPASS_EST, 1), run.debug(hb.HB_DEBUG_DETAILS, 1)
+    up = est.reshape(h // B, 1, w // B, 1, 2).repeat(B, 1).repeat(B, 3).reshape(h, w, 2)
+    assert np.array_equal(maps[1, 0], up[..., 0] + det[..., 0]) and np.array_equal(maps[1, 1], up[..., 1] + det[..., 1])
+    run.close()
+
+
 @pytest.mark.parametrize("h,w,levels,split,offset", [
     (64, 96, 2, 1, 0),      # one split: the posterior kernel writes the maps
     (40, 72, 2, 1, 0),      # ragged wave tiles
