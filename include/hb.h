@@ -94,11 +94,12 @@ typedef struct {
                                    and, up to a per-wave budget of B chunks, below 2^-(T-6) (bound:
                                    2 thb_max (G 2^-T + 16 B S 2^-(T-6)), G grid nodes, S grid splits;
                                    T = ceil(log2(2 G thb_max / tolerance)) + 1; T, B and the bound
-                                   are reported by hb_plan_get_info).  The MFMA kernel with one split
-                                   also skips chunks above 2^-T whose summed weight bounds are at
+                                   are reported by hb_plan_get_info).  With one split the kernels
+                                   also skip chunks above 2^-T whose summed weight bounds are at
                                    most that bound / thb_max of the weight the pixel's kept chunks
-                                   sum to, which moves the mean by at most the same bound (it has
-                                   no use for the budget B).
+                                   sum to, which moves the mean by at most the same bound (they
+                                   have no use for the budget B, nor have those of a split grid,
+                                   which skip below 2^-T only).
                                    0: skip only chunks whose float32 weights are all exactly
                                    zero (T = 160; results equal those of no skipping, bit
                                    for bit).  < 0: skip nothing (every chunk that holds a
@@ -145,9 +146,8 @@ typedef struct {
     double direct_index;  /* max over neighbouring grid nodes of their squared scaled distance times their
                              largest Hb/HbO2 difference (uM); float32 logits can move a posterior mean by
                              about 8e-9 times this                                                        */
-    double band_log2;     /* direct kernels: chunks whose logit bound lies between band_log2 and
-                             skip_log2 below the reference are skipped too, up to band_chunks of them
-                             per wave (of 64 pixels); band_log2 = skip_log2: no such budget            */
+    double band_log2;     /* threshold T - 6 and budget B of the a-priori rule that skip_bound is stated
+                             for (posterior_tolerance above); band_log2 = skip_log2: no such budget       */
     int64_t band_chunks;
     double far_room;      /* how far (scaled units) an observation may lie from the grid's nodes
                              before the posterior kernel's float32 logits exceed its precision budget;

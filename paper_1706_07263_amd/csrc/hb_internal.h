@@ -120,14 +120,13 @@ constexpr int kLoFloats = 48;
 // thb_max for G grid nodes.
 constexpr float kExactSkipLog2 = 160.0f;
 constexpr float kMinSkipLog2 = 16.0f;
-// Budgeted skipping below a tolerance-derived threshold.  The hard threshold
-// is T + 1, which spends at most half of the tolerance on G 2^-(T+1); a wave
-// may also leave out chunks bounded between kBandLog2 and T + 1 below its
-// reference, each of whose weights sum to at most 16 2^-(T+1-kBandLog2), as
-// long as its count of such chunks stays within the budget the rest of the
-// tolerance buys (every pixel of the wave then loses at most that mass).
+// A-priori bound at a tolerance-derived threshold.  The hard threshold is
+// T + 1, which spends at most half of the tolerance on G 2^-(T+1); the bound
+// stated for the plan also allows each wave a budget of chunks bounded between
+// kBandLog2 and T + 1 below its reference, whose weights sum to at most 16
+// 2^-(T+1-kBandLog2) each, as many as the rest of the tolerance buys.
 constexpr float kBandLog2 = 6.0f;
-// Certified depth (MFMA kernel).  The stated bound E on the posterior mean
+// Certified depth (one split).  The stated bound E on the posterior mean
 // holds for a pixel as soon as its skipped weight is at most E / thb_max of
 // its kept weight (the mean moves by at most thb_max times their ratio).  A
 // wave sums the bounds of the chunks it leaves out, so it may stop at a far
@@ -175,7 +174,7 @@ inline int super_floats(int side) {
 constexpr int kStripPixels = 2048;
 constexpr int kBlockThreads = 256;
 
-// Tables of the MFMA kernel's tests, derived from the super-tile table:
+// Tables of the skip tests and of the MFMA kernel's probes, derived from the super-tile table:
 //   axes     3 x 3 rotation (rows: unit vectors) along which the boxes lie:
 //            the principal directions of the differences between neighbouring
 //            nodes, the strongest last.  The nodes form a surface, so boxes
@@ -262,20 +261,18 @@ struct PosteriorArgs {
     int split;
     float scale;             // sqrt(log2(e) / (2 sigma^2))
     float skip_log2;         // chunks bounded more than this below the reference are skipped
-    float depth0;            // MFMA kernel: depth of the first pass (skip_log2: the only one)
-    float cert_log2;         // MFMA kernel: largest certified log2 of skipped over kept weight
-    float band_log2;         // chunks bounded more than this below it are skipped while the budget lasts
-    int band_chunks;         // budget: chunks a wave may skip between band_log2 and skip_log2
+    float depth0;            // depth of the first pass (skip_log2: the only one)
+    float cert_log2;         // largest certified log2 of skipped over kept weight
     float *gref;             // [n][LL] best probe logit over the whole grid, or null (one split)
     float *part;             // [n][split][kPartFields][LL]
-    float axes[9];           // MFMA kernel: axes and tables of its tests (see kHdrFloats)
+    float axes[9];           // axes and tables of the skip tests (see kHdrFloats)
     const float *headers;
     const float *boxes;
     const void *probes;
     int probe_shift;         // log2 of the probe slots of a super-tile
     int supers_per_test;     // 64 / chunks_per_super
     int inv_chunks;          // ceil(65536 / chunks_per_super): lane / chunks_per_super = lane * this >> 16
-    int list_across;         // MFMA kernel: list kept super-tiles across groups of 64 (else group by group)
+    int list_across;         // list kept super-tiles across groups of 64 (else group by group)
     const float *lo;         // [chunk][kLoFloats] coordinate low parts (double-float logits)
     int precise;             // direct kernel: every logit from double-float differences
     unsigned long long *work;  // optional: [0] pairs evaluated (pixel x node), added per wave,

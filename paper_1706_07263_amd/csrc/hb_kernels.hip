@@ -824,6 +824,13 @@ __device__ __forceinline__ float max_rows(float x) {
     swap_rows32(x, y);
     return fmaxf(x, y);
 }
+// Minimum / maximum over the wave (uniform).
+__device__ __forceinline__ float lane_value(float x, int lane);
+template <bool MAX>
+__device__ __forceinline__ float wave_reduce(float x) {
+    x = row_reduce<MAX>(x);
+    return pick<MAX>(pick<MAX>(lane_value(x, 0), lane_value(x, 16)), pick<MAX>(lane_value(x, 32), lane_value(x, 48)));
+}
 __device__ __forceinline__ float lane_value(float x, int lane) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
 }
@@ -864,12 +871,6 @@ constexpr int kXcds = 8;   // accelerator complex dies of an MI355X, each with i
 // Waves resident at once: 256 CUs x 4 SIMDs x 6 waves.
 constexpr int kResidentWaves = 256 * 4 * 6;
 constexpr int kOrderSquare = 8;
-
-// A wave of the direct kernel takes a compact 8-wide tile of LL pixels
-// (PW / 8 rows), four waves of a workgroup stack vertically; compact tiles
-// keep the wave's observations close together, which is what the skipping
-// test below relies on.
-constexpr int kWaveTileW = 8;
 
 struct WaveWork {
     int f, split, s0, s1;
@@ -931,17 +932,10 @@ __device__ __forceinline__ WaveWork block_work(const PosteriorArgs &a, int idx) 
     return w;
 }
 
-// LL index of the wave's i-th pixel (clamped into the image) and whether it exists.
-__device__ __forceinline__ bool wave_pixel(const PosteriorArgs &a, const WaveWork &w, int i, long long &p) {
-    const int r = w.r0 + i / kWaveTileW, c = w.c0 + i % kWaveTileW;
-    const bool valid = r < a.hl && c < a.wl;
-    p = (long long)min(r, a.hl - 1) * a.wl + min(c, a.wl - 1);
-    return valid;
-}
-
-// LL index of pixel i of the workgroup's region.
+// LL index of pixel i of the workgroup's region, RW pixels wide.
+template <int RW>
 __device__ __forceinline__ long long region_pixel(const PosteriorArgs &a, const WaveWork &w, int i) {
-    return (long long)(w.r0 + i / kRegionW) * a.wl + w.c0 + i % kRegionW;
+    return (long long)(w.r0 + i / RW) * a.wl + w.c0 + i % RW;
 }
 
 // Scaled double-float observation of LL pixel p, channel k.
@@ -952,7 +946,14 @@ __device__ __forceinline__ void load_obs(const float *zf, long long LL, long lon
     l = fmaf(sc, zh, -h) + sc * zl;
 }
 
-__device__ __forceinline__ void recentre(const float *T, const float ph[3], const float pl[3], float r[3]) {
+// A table that no kernel writes, in the constant address space: reads at a
+// wave-uniform index are scalar loads wherever they stand (behind a fence or
+// a store the compiler would make vector loads of them).
+typedef const __attribute__((address_space(4))) float ConstFloat;
+__device__ __forceinline__ ConstFloat *constant(const float *p) { return (ConstFloat *)(uintptr_t)p; }
+
+template <typename Table>
+__device__ __forceinline__ void recentre(Table T, const float ph[3], const float pl[3], float r[3]) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) r[k] = (ph[k] - T[k]) + (pl[k] - T[3 + k]);
 }
@@ -973,24 +974,6 @@ __device__ __forceinline__ float box_box_bound(const float *box, const float r[6
     return -fmaf(e0, e0, fmaf(e1, e1, e2 * e2));
 }
 
-// Chunks a wave evaluates, from v = its logit bound minus the wave's
-// reference (one chunk per lane, the lanes of real chunks set in
-// lane_mask): every chunk with v > nband, and those with nskip < v <= nband
-// unless the wave's remaining budget band_left (wave-uniform) covers all of
-// them, which it then shrinks by their count.  With nband == nskip no budget
-// is in use.
-__device__ __forceinline__ unsigned long long kept_chunks(unsigned long long lane_mask, float v, float nskip,
-                                                          float nband, int &band_left) {
-    const unsigned long long keep = __builtin_amdgcn_ballot_w64(v > nband) & lane_mask;
-    const unsigned long long any = __builtin_amdgcn_ballot_w64(v > nskip) & lane_mask;
-    const int nb = __popcll(any & ~keep);
-    if (nb <= band_left) {
-        band_left -= nb;
-        return keep;
-    }
-    return any;
-}
-
 // Skipped weight of a node whose logit lies at most v above the wave's
 // reference, rounded up, in units of 2^-kMassLog2.
 __device__ __forceinline__ unsigned mass_units(float v) {
@@ -1000,18 +983,29 @@ __device__ __forceinline__ unsigned mass_units(float v) {
 // Widening of the wave's observation box for rounding (scaled units).
 constexpr float kBoxSlack = 1.0e-3f;
 
-struct PixelRef {
-    float m, ahb, aox;
-    float mup;  // wave-level upper bound of every logit of the split
-};
+// Coordinate of an observation along one of the boxes' axes.
+__device__ __forceinline__ float axis_coordinate(const float axis[3], float x0, float x1, float x2) {
+    return fmaf(axis[0], x0, fmaf(axis[1], x1, axis[2] * x2));
+}
+
+// Widens an observation box for rounding (of the rotation too, at the scale
+// of the observation: far2 its squared distance from the origin).
+__device__ __forceinline__ void widen_box(float zbox[6], float far2) {
+    const float slack = kBoxSlack + sqrtf(far2) * 0x1p-20f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        zbox[k] -= slack;
+        zbox[3 + k] += slack;
+    }
+}
 
 // Best probe of super-tile T for observation r (recentred on T): updates the
 // running best logit and its anchor node.
-__device__ __forceinline__ void probe_supertile(const float *__restrict__ T, const float r[3], float &mlo,
-                                                float &ahb, float &aox) {
+template <typename Table>
+__device__ __forceinline__ void probe_supertile(Table T, const float r[3], float &mlo, float &ahb, float &aox) {
     const int np = __float_as_int(T[14]);
     for (int i = 0; i < np; ++i) {
-        const float *P = T + kSupHdr + i * kProbeFloats;
+        const auto P = T + kSupHdr + i * kProbeFloats;
         const float d0 = r[0] - P[0], d1 = r[1] - P[1], d2 = r[2] - P[2];
         const float tp = -fmaf(d0, d0, fmaf(d1, d1, d2 * d2));
         if (tp > mlo) {
@@ -1020,137 +1014,6 @@ __device__ __forceinline__ void probe_supertile(const float *__restrict__ T, con
             aox = P[4];
         }
     }
-}
-
-// Observation box of the wave (every lane's pixel), for bounds that hold for
-// all of its pixels at once; widened by kBoxSlack once here, which covers the
-// rounding of high + low parts, of the super-tile centre and of the
-// recentring subtractions below.
-__device__ __forceinline__ void wave_obs_box(const float ph[3], const float pl[3], float zlo[3], float zhi[3]) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) zlo[k] = zhi[k] = ph[k] + pl[k];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            zlo[k] = fminf(zlo[k], __shfl_xor(zlo[k], o));
-            zhi[k] = fmaxf(zhi[k], __shfl_xor(zhi[k], o));
-        }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        zlo[k] -= kBoxSlack;
-        zhi[k] += kBoxSlack;
-    }
-}
-
-// Upper bound of the logit between the wave's (widened) observation box and
-// the node box of super-tile si; rbox is the observation box relative to the
-// super-tile's centre.
-__device__ __forceinline__ float wave_super_bound(const PosteriorArgs &a, int si, const float zlo[3],
-                                                  const float zhi[3], float rbox[6]) {
-    const float *__restrict__ T = a.supers + (size_t)si * a.super_stride;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const float c = T[k] + T[3 + k];
-        rbox[k] = zlo[k] - c;
-        rbox[3 + k] = zhi[k] - c;
-    }
-    return box_box_bound(T + 8, rbox);
-}
-
-// Probes i = part, part + LPP, ... of super-tile T for observation r.
-template <int LPP>
-__device__ __forceinline__ void probe_part(const float *__restrict__ T, const float r[3], int part, float &mlo,
-                                           float &ahb, float &aox) {
-    const int np = __float_as_int(T[14]);
-    for (int i = part; i < np; i += LPP) {
-        const float *P = T + kSupHdr + i * kProbeFloats;
-        const float d0 = r[0] - P[0], d1 = r[1] - P[1], d2 = r[2] - P[2];
-        const float tp = -fmaf(d0, d0, fmaf(d1, d1, d2 * d2));
-        if (tp > mlo) {
-            mlo = tp;
-            ahb = P[3];
-            aox = P[4];
-        }
-    }
-}
-
-// Per-pixel reference logit and anchor: the best probe over the split's
-// super-tiles.  Each pixel is handled by LPP lanes (lane / PW selects the
-// part), which split every super-tile's probes between them.  The wave first
-// bounds all super-tiles at once (one per lane, against its observation box),
-// probes the one with the highest bound, then only super-tiles whose bound
-// exceeds the lowest best probe of the wave: the result equals a full probe
-// scan (a super-tile bounded below a pixel's best probe cannot improve it).
-// The caller refines the reference with far_gap_max when some weight could
-// exceed 2^kFarGap relative to it.
-template <int PW, int LPP>
-__device__ PixelRef pixel_reference(const PosteriorArgs &a, const WaveWork &w, const float ph[3],
-                                    const float pl[3], int part, const float zlo[3], const float zhi[3]) {
-    const int lane = threadIdx.x & 63;
-    float mup = -INFINITY;
-    int best = w.s0;
-    for (int g = w.s0; g < w.s1; g += 64) {
-        const int si = g + lane;
-        float rbox[6];
-        float bm = si < w.s1 ? wave_super_bound(a, si, zlo, zhi, rbox) : -INFINITY;
-        int bi = si;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {  // wave arg-max, lowest index on ties
-            const float ob = __shfl_xor(bm, o);
-            const int oi = __shfl_xor(bi, o);
-            if (ob > bm || (ob == bm && oi < bi)) {
-                bm = ob;
-                bi = oi;
-            }
-        }
-        if (bm > mup) {
-            mup = bm;
-            best = bi;
-        }
-    }
-    best = __builtin_amdgcn_readfirstlane(best);
-    float mlo = -INFINITY, ahb = 0.0f, aox = 0.0f;
-    auto combine = [&]() {  // the LPP lanes of a pixel agree (the lower part wins ties)
-#pragma unroll
-        for (int o = PW; o < 64; o <<= 1) {
-            const float om = __shfl_xor(mlo, o), oh = __shfl_xor(ahb, o), oo = __shfl_xor(aox, o);
-            const bool take = (lane & o) == 0 ? (om > mlo) : !(mlo > om);
-            if (take) {
-                mlo = om;
-                ahb = oh;
-                aox = oo;
-            }
-        }
-    };
-    {
-        const float *__restrict__ T = a.supers + (size_t)best * a.super_stride;
-        float r[3];
-        recentre(T, ph, pl, r);
-        probe_part<LPP>(T, r, part, mlo, ahb, aox);
-        combine();
-    }
-    float mwave = mlo;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) mwave = fminf(mwave, __shfl_xor(mwave, o));
-    for (int g = w.s0; g < w.s1; g += 64) {
-        const int sl = g + lane;
-        float rbox[6];
-        const bool cand = sl < w.s1 && sl != best && !(wave_super_bound(a, sl, zlo, zhi, rbox) <= mwave);
-        unsigned long long mask = __ballot(cand);
-        while (mask) {
-            const int si = g + __builtin_ctzll(mask);
-            mask &= mask - 1;
-            const float *__restrict__ T = a.supers + (size_t)si * a.super_stride;
-            float r[3];
-            recentre(T, ph, pl, r);
-            if (!__any(box_bound(T + 8, r) > mlo)) continue;
-            probe_part<LPP>(T, r, part, mlo, ahb, aox);
-        }
-    }
-    combine();
-    PixelRef ref{mlo, ahb, aox, mup};
-    return ref;
 }
 
 // Global reference for split grids: one lane per LL pixel, the best probe
@@ -1235,34 +1098,44 @@ __device__ float far_gap_max(const PosteriorArgs &a, const WaveWork &w, const fl
 }
 
 // Fused recomposition for one split and n <= 3, in units of V pixels along a
-// row, from the estimates of the region's pixels: the maps of the whole region,
-// (8 x 2^n) x (16 x 2^n) pixels, or (RT == 1) those of the 32 pixels of one tile.
-template <int RT, int V>
+// row, from the estimates of the region's pixels: the maps of the whole region
+// of RW x RH LL pixels, or (LIST) those of `count` listed ones.
+template <int RW, int RH, bool LIST, int V>
 __device__ __forceinline__ void fused_maps(const PosteriorArgs &a, const WaveWork &w, const float2 *est,
-                                           const int *tile_slot, int tile_valid) {
+                                           const int *list, int count) {
     constexpr int kLogV = V == 4 ? 2 : (V == 2 ? 1 : 0);
     const int n = a.levels, B = 1 << n;
-    const int n_units = ((RT == 1 ? tile_valid : kRegionPixels) << 2 * n) >> kLogV;
+    const int n_units = ((LIST ? count : RW * RH) << 2 * n) >> kLogV;
     for (int u = threadIdx.x; u < n_units; u += blockDim.x) {
         int i, y, x;   // pixel of the region, offset in its block
-        if constexpr (RT == 1) {
+        if constexpr (LIST) {
             const int o = u & ((1 << (2 * n - kLogV)) - 1);
-            i = tile_slot[u >> (2 * n - kLogV)];
+            i = list[u >> (2 * n - kLogV)];
             y = o >> (n - kLogV);
             x = (o << kLogV) & (B - 1);
         } else {
             const int row_shift = 4 + n - kLogV;   // log2 of the units of a region row
-            const int Y = u >> row_shift, X = (u << kLogV) & ((kRegionW << n) - 1);
-            i = (Y >> n) * kRegionW + (X >> n);
+            static_assert(RW == 16, "row_shift");
+            const int Y = u >> row_shift, X = (u << kLogV) & ((RW << n) - 1);
+            i = (Y >> n) * RW + (X >> n);
             y = Y & (B - 1);
             x = X & (B - 1);
         }
-        const int gr = w.r0 + i / kRegionW, gc = w.c0 + i % kRegionW;
+        const int gr = w.r0 + i / RW, gc = w.c0 + i % RW;
         if (gr >= a.hl || gc >= a.wl) continue;
         const size_t o = ((size_t)w.f * a.H + ((size_t)gr << n) + y) * a.W + ((size_t)gc << n) + x;
         float2 dp[V];
         load_detail<V>(a.det, o, dp);
         write_maps<V>(a.hb, a.hbo2, a.thb, a.so2, a.thb_eps, o, est[i], dp);
+    }
+}
+template <int RW, int RH, bool LIST>
+__device__ __forceinline__ void fused_maps(const PosteriorArgs &a, const WaveWork &w, const float2 *est,
+                                           const int *list = nullptr, int count = 0) {
+    switch (a.vec) {
+        case 4: fused_maps<RW, RH, LIST, 4>(a, w, est, list, count); break;
+        case 2: fused_maps<RW, RH, LIST, 2>(a, w, est, list, count); break;
+        default: fused_maps<RW, RH, LIST, 1>(a, w, est, list, count); break;
     }
 }
 
@@ -1297,8 +1170,9 @@ __device__ __forceinline__ float df_logit_v(const float rh[3], const float rl[3]
     return th;
 }
 
-__device__ __forceinline__ float df_logit(const float rh[3], const float rl[3], const float *__restrict__ C,
-                                          const float *__restrict__ LO, int j, float nm, float &tl) {
+template <typename Table>
+__device__ __forceinline__ float df_logit(const float rh[3], const float rl[3], Table C, Table LO, int j, float nm,
+                                          float &tl) {
     const float vh[3] = {C[j], C[16 + j], C[32 + j]}, vl[3] = {LO[j], LO[16 + j], LO[32 + j]};
     return df_logit_v(rh, rl, vh, vl, nm, tl);
 }
@@ -1329,6 +1203,9 @@ __device__ __forceinline__ PosteriorArgs far_args(KernArgs *k) {
     f.super_stride = k->super_stride;
     f.chunks_per_super = k->chunks_per_super;
     f.lo = k->lo;
+    f.headers = k->headers;
+    f.boxes = k->boxes;
+    for (int i = 0; i < 9; ++i) f.axes[i] = k->axes[i];
     return f;
 }
 
@@ -1352,16 +1229,18 @@ __device__ __forceinline__ void far_pixel_sums(const PosteriorArgs &a, const Wav
     const int lane = threadIdx.x & 63;
     const int j = lane & 15;
     const float nskip = -a.skip_log2;
-    float zbox[6];
+    // The boxes and slack of the main loop's tests: what is evaluated here is
+    // then among the chunks that the pixel's reference was refined over.
+    float zbox[6], far2 = 0.0f;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        zbox[k] = (qh[k] + ql[k]) - kBoxSlack;
-        zbox[3 + k] = (qh[k] + ql[k]) + kBoxSlack;
+        zbox[k] = zbox[3 + k] = axis_coordinate(a.axes + 3 * k, qh[0] + ql[0], qh[1] + ql[1], qh[2] + ql[2]);
+        far2 = fmaf(zbox[k], zbox[k], far2);
     }
+    widen_box(zbox, far2);
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, c0 = 0.f, c1 = 0.f, c2 = 0.f;
     for (int si = w.s0; si < w.s1; ++si) {
-        float rbox[6];
-        if (!(wave_super_bound(a, si, zbox, zbox + 3, rbox) - m_skip > nskip)) continue;
+        if (!(box_box_bound(a.headers + (size_t)si * kHdrFloats, zbox) - m_skip > nskip)) continue;
         const float *__restrict__ T = a.supers + (size_t)si * a.super_stride;
         float rh[3], rl[3];
 #pragma unroll
@@ -1375,7 +1254,7 @@ __device__ __forceinline__ void far_pixel_sums(const PosteriorArgs &a, const Wav
         float L0 = 0.f, L1 = 0.f, L2 = 0.f;
         for (int ci = lane >> 4; ci < a.chunks_per_super; ci += 4) {
             const float *__restrict__ C = C0 + (size_t)ci * kChunkFloats;
-            if (box_box_bound(C + 96, zbox) - m_skip > nskip) {
+            if (box_box_bound(a.boxes + ((size_t)si * a.chunks_per_super + ci) * kBoxFloats, zbox) - m_skip > nskip) {
                 float tl;
                 const float th = df_logit(rh, rl, C, LO0 + (size_t)ci * kLoFloats, j, nm, tl);
                 const float e = __builtin_amdgcn_exp2f(th);
@@ -1431,10 +1310,76 @@ __device__ __forceinline__ void far_pixel_sums(const PosteriorArgs &a, const Wav
 // pair on a 512 x 512 grid 2794 -> 2470, 1280x1024 frame at level 0 with the
 // illumination term 1198 -> 1049, sixteen 320x240 frames 205 -> 165, one
 // 640x480 frame 85 -> 72.
+// Order between the lanes of a tile: of its only wave, or of the workgroup.
+template <int NW>
+__device__ __forceinline__ void tile_sync() {
+    if constexpr (NW == 1) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
+    }
+}
+
 struct KeptSuper {
     unsigned lo, hi;   // kept chunks of the super-tile, one bit each
     int si, segment;
 };
+
+// Lists up to 64 super-tiles from *g on whose bound (relative to mmin) exceeds
+// svlo, and the chunks of each whose bound v has vlo < v <= vhi; what lies
+// below counts into `mass`.  The NW waves of a tile share the chunk tests:
+// 64 / chunks_per_super super-tiles at once, lane sub * cps + ci chunk ci of
+// the sub-th.  Returns the length of the list.  The caller orders the waves
+// before the list is read.
+struct ChunkTest {
+    float vlo, vhi, svlo, mmin;
+    bool last;   // nothing below counts
+};
+template <int NW>
+__device__ __forceinline__ int list_chunks(const PosteriorArgs &a, const WaveWork &w, KeptSuper *kept, int wave,
+                                           const float (&zbox)[6], const ChunkTest &t, int &g, unsigned &mass) {
+    const int lane = threadIdx.x & 63;
+    const int cps = a.chunks_per_super, per_test = a.supers_per_test;
+    const int sub = (int)((unsigned)lane * (unsigned)a.inv_chunks >> 16), ci = lane - sub * cps;   // lane / cps
+    const unsigned long long chunk_bits = cps >= 64 ? ~0ull : (1ull << cps) - 1;
+    // Super-tiles, one per lane; the kept ones are listed.
+    int K = 0;
+    while (g < w.s1) {
+        const int sl = g + lane;
+        const float sv = (sl < w.s1 ? box_box_bound(a.headers + (size_t)sl * kHdrFloats, zbox) : -INFINITY) - t.mmin;
+        const unsigned long long smask = __builtin_amdgcn_ballot_w64(sv > t.svlo);
+        const int n = __popcll(smask);
+        // the list holds 64; exact and no skipping take the same windows
+        if (K + n > 64 || (K > 0 && !a.list_across)) break;
+        if (!t.last && (NW == 1 || wave == 0) && sl < w.s1 && !(sv > t.svlo))
+            mass = __builtin_elementwise_add_sat(mass, mass_units(sv) * (unsigned)cps);
+        const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(smask >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((unsigned)smask, 0));
+        if (sv > t.svlo) {   // every wave writes the same values
+            kept[K + rank].si = sl;
+            kept[K + rank].segment = __float_as_int(a.headers[(size_t)sl * kHdrFloats + 14]);
+        }
+        K += n;
+        g += 64;
+    }
+    if (K == 0) return 0;
+    tile_sync<1>();   // between the lanes of each wave, which has listed them itself
+    for (int k0 = wave * per_test; k0 < K; k0 += NW * per_test) {
+        const int k = k0 + sub;
+        const bool real = sub < per_test && k < K;
+        const int si = kept[real ? k : 0].si;
+        const float v = box_box_bound(a.boxes + ((size_t)si * cps + ci) * kBoxFloats, zbox) - t.mmin;
+        const unsigned long long in = __builtin_amdgcn_ballot_w64(real && v > t.vlo && v <= t.vhi);
+        if (!t.last) mass = __builtin_elementwise_add_sat(mass, real && !(v > t.vlo) ? mass_units(v) : 0u);
+        if (real && ci == 0) {
+            const unsigned long long bits = in >> (sub * cps) & chunk_bits;
+            kept[k].lo = (unsigned)bits;
+            kept[k].hi = (unsigned)(bits >> 32);
+        }
+    }
+    return K;
+}
 
 template <int NW>
 struct TileShared {
@@ -1457,17 +1402,6 @@ struct RegionShared {
     float2 est[kRegionPixels];
     int more[3];
 };
-
-// Order between the lanes of a tile: of its only wave, or of the workgroup.
-template <int NW>
-__device__ __forceinline__ void tile_sync() {
-    if constexpr (NW == 1) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    } else {
-        __syncthreads();
-    }
-}
 
 // base + n / d with n = nh + nl and d = dh + dl, rounded once.
 __device__ __forceinline__ float plus_quotient(float base, float nh, float nl, float dh, float dl) {
@@ -1519,7 +1453,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
             float q = 0.0f;
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                q = fmaf(a.axes[3 * k], x[0], fmaf(a.axes[3 * k + 1], x[1], a.axes[3 * k + 2] * x[2]));
+                q = axis_coordinate(a.axes + 3 * k, x[0], x[1], x[2]);
                 rsh.rot[k][i] = q;
             }
             // ordered bits, the low seven replaced by the pixel's number; pixels
@@ -1556,8 +1490,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
         ah[b] = rsh.obs[lk < 3 ? lk : 0][ib[b]];
         al[b] = rsh.obs[3 + (lk < 3 ? lk : 0)][ib[b]];
     }
-    // Observation box of the tile along the boxes' axes, widened for rounding
-    // (of the rotation too, at the scale of the observation).
+    // Observation box of the tile along the boxes' axes, widened for rounding.
     float zbox[6], far2 = 0.0f;
     {
         const float x0 = rsh.rot[lk < 3 ? lk : 0][ib[0]], x1 = rsh.rot[lk < 3 ? lk : 0][ib[1]];
@@ -1569,12 +1502,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
             const float e = fmaxf(-zbox[k], zbox[3 + k]);
             far2 = fmaf(e, e, far2);
         }
-        const float slack = kBoxSlack + sqrtf(far2) * 0x1p-20f;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            zbox[k] -= slack;
-            zbox[3 + k] += slack;
-        }
+        widen_box(zbox, far2);
     }
     auto super_bound = [&](int si) {   // -inf past the split's range
         return si < w.s1 ? box_box_bound(a.headers + (size_t)si * kHdrFloats, zbox) : -INFINITY;
@@ -1708,7 +1636,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
 #pragma unroll
     for (int b = 0; b < PB; ++b) {
         float m = am[b];
-        if (a.gref) m = fmaxf(m, a.gref[(size_t)w.f * a.LL + region_pixel(a, w, ib[b])]);
+        if (a.gref) m = fmaxf(m, a.gref[(size_t)w.f * a.LL + region_pixel<kRegionW>(a, w, ib[b])]);
         // A pixel without a finite logit (a NaN observation) gets NaN maps
         // whatever is kept; it must not switch skipping off for its tile.
         mmin = fminf(mmin, m > -INFINITY ? m : INFINITY);
@@ -1736,7 +1664,8 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
     }
     // Anchor of the moments, for the whole tile: the centre of the super-tile
     // with the highest bound.
-    const float anc_hb = a.headers[(size_t)best * kHdrFloats + 6], anc_ox = a.headers[(size_t)best * kHdrFloats + 7];
+    const float anc_hb = constant(a.headers)[(size_t)best * kHdrFloats + 6];
+    const float anc_ox = constant(a.headers)[(size_t)best * kHdrFloats + 7];
 
     unsigned executed = 0;   // chunks evaluated by this wave
     // Split operands through a buffer resource: the lane offset stays in a
@@ -1745,12 +1674,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
         const_cast<void *>(a.split_ops), (short)0, a.n_supers * a.chunks_per_super * kSplitChunkBytes, kBufferWord3);
     const __amdgpu_buffer_rsrc_t super_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(a.supers), (short)0, a.n_supers * a.super_stride * 4, kBufferWord3);
-    // Chunk tests: a super-tile holds cps <= 64 chunks, so 64 lanes test
-    // 64 / cps super-tiles at once, lane sub * cps + ci chunk ci of the sub-th.
-    const int cps = a.chunks_per_super, per_test = a.supers_per_test;
-    const int sub = (int)((unsigned)lane * (unsigned)a.inv_chunks >> 16), ci = lane - sub * cps;   // lane / cps
-    const unsigned long long chunk_bits = cps >= 64 ? ~0ull : (1ull << cps) - 1;
-
+    const int cps = a.chunks_per_super;
     // Several waves per tile: the tiles of the workgroup go through the same
     // barriers, so they learn of each other whether one has more to do.
     int round = 0;
@@ -1774,41 +1698,9 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
         unsigned mass = 0;   // this lane's share of the skipped weight (saturating), 2^-kMassLog2 per chunk
         int g = w.s0;
         for (bool more = true; more;) {
-            // Super-tiles, one per lane; the kept ones are listed.
-            int K = 0;
-            while (active && g < w.s1) {
-                const float sv = super_bound(g + lane) - mmin;
-                const unsigned long long smask = __builtin_amdgcn_ballot_w64(sv > svlo);
-                const int n = __popcll(smask);
-                // the list holds 64; exact and no skipping take the same windows
-                if (K + n > 64 || (K > 0 && !a.list_across)) break;
-                if (!last && (NW == 1 || wave == 0) && g + lane < w.s1 && !(sv > svlo))
-                    mass = __builtin_elementwise_add_sat(mass, mass_units(sv) * (unsigned)cps);
-                const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(smask >> 32),
-                                                           __builtin_amdgcn_mbcnt_lo((unsigned)smask, 0));
-                if (sv > svlo) {   // every wave writes the same values
-                    sh.kept[K + rank].si = g + lane;
-                    sh.kept[K + rank].segment = __float_as_int(a.headers[(size_t)(g + lane) * kHdrFloats + 14]);
-                }
-                K += n;
-                g += 64;
-            }
+            const ChunkTest test{vlo, vhi, svlo, mmin, last};
+            const int K = active ? list_chunks<NW>(a, w, sh.kept, wave, zbox, test, g, mass) : 0;
             if (NW == 1 && K == 0) break;
-            tile_sync<1>();   // between the lanes of each wave, which has listed them itself
-            // Chunk tests of the kept super-tiles, 64 chunks at once.
-            for (int k0 = wave * per_test; k0 < K; k0 += NW * per_test) {
-                const int k = k0 + sub;
-                const bool real = sub < per_test && k < K;
-                const int si = sh.kept[real ? k : 0].si;
-                const float v = box_box_bound(a.boxes + ((size_t)si * cps + ci) * kBoxFloats, zbox) - mmin;
-                const unsigned long long kept = __builtin_amdgcn_ballot_w64(real && v > vlo && v <= vhi);
-                if (!last) mass = __builtin_elementwise_add_sat(mass, real && !(v > vlo) ? mass_units(v) : 0u);
-                if (real && ci == 0) {
-                    const unsigned long long bits = kept >> (sub * cps) & chunk_bits;
-                    sh.kept[k].lo = (unsigned)bits;
-                    sh.kept[k].hi = (unsigned)(bits >> 32);
-                }
-            }
             tile_sync<NW>();
             // Segments in turn (which wave sums a segment changes no bit).
             const KeptSuper own = sh.kept[lane];
@@ -1855,7 +1747,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
                     f32x3 qA, qB;
                     take(bA, qA);   // the mask holds at least one chunk
                     bool next = take(bB, qB);
-                    const float *__restrict__ H = a.headers + (size_t)si * kHdrFloats;
+                    ConstFloat *H = constant(a.headers) + (size_t)si * kHdrFloats;
                     const float ch = lk == 0 ? H[8] : (lk == 1 ? H[9] : H[10]);
                     const float cl = lk == 0 ? H[11] : (lk == 1 ? H[12] : H[13]);
                     bf16x8 av[PB];
@@ -2018,7 +1910,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
             const float mq = __shfl(m, q);
             float m_skip = mq;
             if (fa.gref) {
-                const float g = fa.gref[(size_t)w.f * fa.LL + region_pixel(fa, w, i)];
+                const float g = fa.gref[(size_t)w.f * fa.LL + region_pixel<kRegionW>(fa, w, i)];
                 if (!(g < -fa.far_rho2)) continue;
                 m_skip = fmaxf(m_skip, g);
             }
@@ -2036,7 +1928,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
         if (far_pixels) atomicAdd(a.work + 1, (unsigned long long)far_pixels);
     }
     const bool writer = wave == 0 && lane_e < 32 && valid;
-    const long long pe = region_pixel(a, w, pixel);
+    const long long pe = region_pixel<kRegionW>(a, w, pixel);
     if (a.fuse) {
         // one split: the estimate is anchor + S1 / S0
         if (writer) {
@@ -2046,11 +1938,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
             a.est[(size_t)w.f * a.LL + pe] = rsh.est[pixel];
         }
         __syncthreads();
-        switch (a.vec) {
-            case 4: fused_maps<RT, 4>(a, w, rsh.est, rsh.slot + base, min(kTilePixels, n_valid - base)); break;
-            case 2: fused_maps<RT, 2>(a, w, rsh.est, rsh.slot + base, min(kTilePixels, n_valid - base)); break;
-            default: fused_maps<RT, 1>(a, w, rsh.est, rsh.slot + base, min(kTilePixels, n_valid - base)); break;
-        }
+        fused_maps<kRegionW, kRegionH, RT == 1>(a, w, rsh.est, rsh.slot + base, min(kTilePixels, n_valid - base));
         return;
     }
     if (writer) {
@@ -2068,152 +1956,232 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
 // Direct kernel: one LL pixel per lane, logits in the difference form
 // t - m = -(r - v_g)^2 - m on the VALU with wave-uniform (scalar) node loads;
 // PRECISE: from double-float differences (df_logit), for grids whose nodes
-// are too far apart for float32 logits.  Skipping, the global reference, the
-// exact maximum over kept chunks and (float32 logits) the double-float pass
-// for far observations are as in the MFMA kernel.
+// are too far apart for float32 logits.  A wave takes a compact tile of 8 x 8
+// pixels (its observations then lie close together, which the skip tests rely
+// on), a workgroup 2 x 2 of them, whose maps it writes.  The reference search,
+// skipping with its certificate, the exact maximum over kept chunks and
+// (float32 logits) the double-float pass for far observations are as in the
+// MFMA kernel.  Bound by VALU issue, about 8 operations and one exponential
+// per (pixel, node).  Three 1006x758 frames at one level on a 24 x 20 grid: 89
+// us a call with sums over single nodes, the a-priori skip threshold and a
+// kernel of its own for the maps, 67 with the rows' affine moments, the
+// certificate and the maps written here.
+constexpr int kDirectSide = 16;   // LL pixels of a workgroup's region along each axis
 template <bool PRECISE>
-__global__ __launch_bounds__(kBlockThreads) void k_posterior_direct(PosteriorArgs a) {
-    constexpr int PW = 64;
+__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5))) void k_posterior_direct(PosteriorArgs a) {
+    __shared__ KeptSuper s_kept[kBlockThreads / 64][64];
+    __shared__ float2 s_est[kDirectSide * kDirectSide];
     const int lane = threadIdx.x & 63;
-    WaveWork w = block_work<kWaveTileW, 4 * PW / kWaveTileW>(a, xcd_order(blockIdx.x, gridDim.x, kResidentWaves / 4));
-    w.r0 += (threadIdx.x >> 6) * (PW / kWaveTileW);
-    if (w.r0 >= a.hl) return;   // a tile below the frame's last row holds no pixel
-    const float *zf = a.z + (size_t)w.f * 6 * a.LL;
-    long long p;
-    const bool valid = wave_pixel(a, w, lane, p);
-    float ph[3], pl[3];
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const WaveWork w =
+        block_work<kDirectSide, kDirectSide>(a, xcd_order(blockIdx.x, gridDim.x, kResidentWaves / 4));
+    const int tr = (wave >> 1) * 8 + (lane >> 3), tc = (wave & 1) * 8 + (lane & 7);   // pixel of the region
+    const bool valid = w.r0 + tr < a.hl && w.c0 + tc < a.wl;
+    const long long p = (long long)min(w.r0 + tr, a.hl - 1) * a.wl + min(w.c0 + tc, a.wl - 1);
+    // A tile outside the frame has no pixel (but its wave helps with the maps).
+    if (w.r0 + (wave >> 1) * 8 < a.hl && w.c0 + (wave & 1) * 8 < a.wl) {
+        const float *zf = a.z + (size_t)w.f * 6 * a.LL;
+        float ph[3], pl[3];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) load_obs(zf, a.LL, p, k, a.scale, ph[k], pl[k]);
-    float zlo[3], zhi[3];
-    wave_obs_box(ph, pl, zlo, zhi);
-    PixelRef ref = pixel_reference<PW, 1>(a, w, ph, pl, 0, zlo, zhi);
-    const float nskip = -a.skip_log2, nband = -a.band_log2;
-    int band_left = a.band_chunks;
-    float mmin = ref.m;
-    if (a.gref) mmin = fmaxf(mmin, a.gref[(size_t)w.f * a.LL + p]);
-    if (!(mmin > -INFINITY)) mmin = INFINITY;  // NaN observation: see the MFMA kernel
+        for (int k = 0; k < 3; ++k) load_obs(zf, a.LL, p, k, a.scale, ph[k], pl[k]);
+        // Observation box of the tile along the boxes' axes (see the MFMA kernel).
+        float zbox[6], far2 = 0.0f;
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) mmin = fminf(mmin, __shfl_xor(mmin, o));
-    const float zbox[6] = {zlo[0], zlo[1], zlo[2], zhi[0], zhi[1], zhi[2]};
-    if (__any(!(ref.mup - ref.m <= kFarGap))) {
-        auto super_test = [&](int si) {
-            float rbox[6];
-            return wave_super_bound(a, si, zlo, zhi, rbox);
+        for (int k = 0; k < 3; ++k) {
+            const float q = axis_coordinate(a.axes + 3 * k, ph[0] + pl[0], ph[1] + pl[1], ph[2] + pl[2]);
+            zbox[k] = wave_reduce<false>(q);
+            zbox[3 + k] = wave_reduce<true>(q);
+            const float e = fmaxf(-zbox[k], zbox[3 + k]);
+            far2 = fmaf(e, e, far2);
+        }
+        widen_box(zbox, far2);
+        auto super_bound = [&](int si) {   // -inf past the split's range
+            return si < w.s1 ? box_box_bound(a.headers + (size_t)si * kHdrFloats, zbox) : -INFINITY;
         };
-        auto chunk_test = [&](int si, int c) {
-            return box_box_bound(a.supers + (size_t)si * a.super_stride + kSupHdr + kMaxProbes * kProbeFloats +
-                                     (size_t)c * kChunkFloats + 96, zbox);
+        auto chunk_bound = [&](int si, int c) {
+            return box_box_bound(a.boxes + ((size_t)si * a.chunks_per_super + c) * kBoxFloats, zbox);
         };
-        ref.m = far_gap_max<PW, 1>(a, w, ph, pl, 0, super_test, chunk_test, mmin, ref.m);
-    }
-    const float nm = -ref.m;
-    float R0 = 0.f, R1 = 0.f, R2 = 0.f, K0 = 0.f, K1 = 0.f, K2 = 0.f;
-    unsigned executed = 0;
-    for (int g = w.s0; g < w.s1; g += 64) {
-        float rbox[6];
-        const int sl = g + lane;
-        unsigned long long smask = __ballot(sl < w.s1 && wave_super_bound(a, sl, zlo, zhi, rbox) - mmin > nskip);
-        while (smask) {
-            const int si = g + __builtin_ctzll(smask);
-            smask &= smask - 1;
-            const float *__restrict__ T = a.supers + (size_t)si * a.super_stride;
-            float r[3], rh[3], rl[3];
-            if (PRECISE) {
+
+        // Reference logit and anchor: the best probe of the split's super-tiles,
+        // the one with the highest bound first, then those bounded above the
+        // tile's lowest best probe.
+        float mup = -INFINITY, m = -INFINITY, anc_hb = 0.0f, anc_ox = 0.0f;
+        int best = w.s0;
+        for (int g = w.s0; g < w.s1; g += 64) {
+            const float b = super_bound(g + lane), top = wave_reduce<true>(b);
+            if (top > mup) {
+                mup = top;
+                best = g + __builtin_ctzll(__builtin_amdgcn_ballot_w64(b == top) | (1ull << 63));
+            }
+        }
+        best = __builtin_amdgcn_readfirstlane(best);
+        auto probe = [&](int si) {
+            ConstFloat *T = constant(a.supers) + (size_t)si * a.super_stride;
+            float r[3];
+            recentre(T, ph, pl, r);
+            probe_supertile(T, r, m, anc_hb, anc_ox);
+        };
+        probe(best);
+        const float lowest = wave_reduce<false>(m > -INFINITY ? m : INFINITY);
+        for (int g = w.s0; g < w.s1; g += 64) {
+            const int sl = g + lane;
+            unsigned long long cand = __builtin_amdgcn_ballot_w64(sl != best && super_bound(sl) > lowest);
+            while (cand) {
+                probe(g + __builtin_ctzll(cand));
+                cand &= cand - 1;
+            }
+        }
+        float mmin = m;
+        if (a.gref) mmin = fmaxf(mmin, a.gref[(size_t)w.f * a.LL + p]);
+        mmin = wave_reduce<false>(mmin > -INFINITY ? mmin : INFINITY);   // NaN observation: see the MFMA kernel
+        if (__any(!(mup - m <= kFarGap))) m = far_gap_max<64, 1>(a, w, ph, pl, 0, super_bound, chunk_bound, mmin, m);
+        const float nm = -m;
+
+        float R0 = 0.f, R1 = 0.f, R2 = 0.f, K0 = 0.f, K1 = 0.f, K2 = 0.f;
+        unsigned executed = 0;
+        KeptSuper *kept = s_kept[wave];
+        const float nskip = -a.skip_log2;
+        float vhi = INFINITY, vlo = -a.depth0;
+        for (;;) {
+            const bool last = !(vlo > nskip);
+            unsigned mass = 0;
+            const ChunkTest test{vlo, vhi, fmaxf(nskip, vlo - kSuperMargin), mmin, last};
+            for (int g = w.s0;;) {
+                const int K = list_chunks<1>(a, w, kept, 0, zbox, test, g, mass);
+                if (K == 0) break;
+                tile_sync<1>();
+                const KeptSuper own = kept[lane];
+                unsigned long long list = __builtin_amdgcn_ballot_w64(lane < K && (own.lo | own.hi) != 0);
+                for (; list; list &= list - 1) {
+                    const int k = __builtin_ctzll(list);
+                    unsigned long long mask = (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)own.hi, k) << 32 |
+                                              (unsigned)__builtin_amdgcn_readlane((int)own.lo, k);
+                    const int si = __builtin_amdgcn_readlane(own.si, k);
+                    executed += __popcll(mask);
+                    ConstFloat *T = constant(a.supers) + (size_t)si * a.super_stride;
+                    float r[3], rh[3], rl[3];
+                    if (PRECISE) {
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) {
+                            float sk, e;
+                            two_sum(ph[c], -T[c], sk, e);
+                            fast_two_sum(sk, e + (pl[c] - T[3 + c]), rh[c], rl[c]);
+                        }
+                    } else {
+                        recentre(T, ph, pl, r);
+                    }
+                    float L0 = 0.f, L1 = 0.f, L2 = 0.f;
+                    ConstFloat *C0 = T + kSupHdr + kMaxProbes * kProbeFloats;
+                    for (; mask; mask &= mask - 1) {
+                        const int ci = __builtin_ctzll(mask);
+                        ConstFloat *C = C0 + (size_t)ci * kChunkFloats;
+                        ConstFloat *LO =
+                            PRECISE ? constant(a.lo) + ((size_t)si * a.chunks_per_super + ci) * kLoFloats : nullptr;
+#pragma unroll
+                        for (int row = 0; row < 4; ++row) {
+                            float x[4];   // weights of the row's nodes
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) {
+                                const int j = 4 * row + c;
+                                if (PRECISE) {
+                                    float tl;
+                                    const float th = df_logit(rh, rl, C, LO, j, nm, tl);
+                                    const float e = __builtin_amdgcn_exp2f(th);
+                                    x[c] = fmaf(e, tl * 0.6931471805599453f, e);
+                                    L0 += x[c];
+                                    L1 = fmaf(x[c], C[64 + j], L1);
+                                    L2 = fmaf(x[c], C[80 + j], L2);
+                                } else {
+                                    const float d0 = r[0] - C[j], d1 = r[1] - C[16 + j], d2 = r[2] - C[32 + j];
+                                    float t = fmaf(-d0, d0, nm);
+                                    t = fmaf(-d1, d1, t);
+                                    t = fmaf(-d2, d2, t);
+                                    x[c] = __builtin_amdgcn_exp2f(t);
+                                }
+                            }
+                            if (!PRECISE) {
+                                // the row's affine moments, as in the MFMA kernel; L2 the THb moment
+                                const float W0 = (x[0] + x[1]) + (x[2] + x[3]);
+                                const float W1 = fmaf(3.0f, x[3], fmaf(2.0f, x[2], x[1]));
+                                L0 += W0;
+                                L1 = fmaf(C[104 + 4 * row], W0, fmaf(C[105 + 4 * row], W1, L1));
+                                L2 = fmaf(C[106 + 4 * row], W0, L2);
+                            }
+                        }
+                    }
+                    if (!PRECISE) L2 -= L1;   // HbO2 = THb - Hb
+                    kahan_add(R0, K0, L0);
+                    kahan_add(R1, K1, fmaf(T[6] - anc_hb, L0, L1));
+                    kahan_add(R2, K2, fmaf(T[7] - anc_ox, L0, L2));
+                }
+                tile_sync<1>();   // the list is free again
+                if (g >= w.s1) break;
+            }
+            if (last) break;
+            // certificate, as in the MFMA kernel
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1)
+                mass = __builtin_elementwise_add_sat(mass, (unsigned)__shfl_xor((int)mass, o));
+            const float skipped = __log2f((float)mass) - kMassLog2;
+            if (!__any(skipped > a.cert_log2 + ((m + __log2f(R0)) - mmin))) break;
+            vhi = vlo;
+            vlo = fmaxf(nskip, vlo - kDepthStep);
+        }
+        if (a.work && lane == 0) atomicAdd(a.work, (unsigned long long)executed * 64 * kChunkNodes);
+        if constexpr (!PRECISE) {
+            // Pixels whose observation lies far from the grid's nodes: the float32
+            // differences round at the scale of that distance, so their sums are
+            // formed again with double-float logits, as in the MFMA kernel (the
+            // plan sets far_rho2 from this kernel's precision budget).
+            unsigned long long far = __ballot(valid && m + __log2f(R0) < -a.far_rho2);
+            unsigned far_pixels = 0;
+            while (__builtin_expect(far != 0, 0)) {
+                const int q = __builtin_ctzll(far);   // the pixel of lane q
+                far &= far - 1;
+                float qh[3], ql[3];
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
-                    float sk, e;
-                    two_sum(ph[k], -T[k], sk, e);
-                    fast_two_sum(sk, e + (pl[k] - T[3 + k]), rh[k], rl[k]);
+                    qh[k] = __shfl(ph[k], q);
+                    ql[k] = __shfl(pl[k], q);
                 }
-            } else {
-                recentre(T, ph, pl, r);
-            }
-            float L0 = 0.f, L1 = 0.f, L2 = 0.f;
-            const float *__restrict__ C0 = T + kSupHdr + kMaxProbes * kProbeFloats;
-            for (int cg = 0; cg < a.chunks_per_super; cg += 64) {
-                const int ct = min(cg + lane, a.chunks_per_super - 1);
-                const int nc = a.chunks_per_super - cg;
-                unsigned long long mask =
-                    kept_chunks(nc >= 64 ? ~0ull : (1ull << nc) - 1,
-                                box_box_bound(C0 + (size_t)ct * kChunkFloats + 96, zbox) - mmin, nskip, nband, band_left);
-                while (mask) {
-                    const int ci = cg + __builtin_ctzll(mask);
-                    const float *__restrict__ C = C0 + (size_t)ci * kChunkFloats;
-                    const float *__restrict__ LO = PRECISE ? a.lo + ((size_t)si * a.chunks_per_super + ci) * kLoFloats
-                                                           : nullptr;
-                    mask &= mask - 1;
-                    ++executed;
-#pragma unroll
-                    for (int j = 0; j < kChunkNodes; ++j) {
-                        float wt;
-                        if (PRECISE) {
-                            float tl;
-                            const float th = df_logit(rh, rl, C, LO, j, nm, tl);
-                            const float w = __builtin_amdgcn_exp2f(th);
-                            wt = fmaf(w, tl * 0.6931471805599453f, w);
-                        } else {
-                            const float d0 = r[0] - C[j], d1 = r[1] - C[16 + j], d2 = r[2] - C[32 + j];
-                            float t = fmaf(-d0, d0, nm);
-                            t = fmaf(-d1, d1, t);
-                            t = fmaf(-d2, d2, t);
-                            wt = __builtin_amdgcn_exp2f(t);
-                        }
-                        L0 += wt;
-                        L1 = fmaf(wt, C[64 + j], L1);
-                        L2 = fmaf(wt, C[80 + j], L2);
-                    }
+                const float mq = __shfl(m, q);
+                float m_skip = mq;
+                if (a.gref) {
+                    const float g = a.gref[(size_t)w.f * a.LL + __shfl(p, q)];
+                    if (!(g < -a.far_rho2)) continue;
+                    m_skip = fmaxf(m_skip, g);
+                }
+                ++far_pixels;
+                float S[3];
+                far_pixel_sums(a, w, qh, ql, m_skip, -mq, __shfl(anc_hb, q), __shfl(anc_ox, q), S);
+                if (lane == q) {
+                    R0 = S[0];
+                    R1 = S[1];
+                    R2 = S[2];
+                    K0 = K1 = K2 = 0.0f;
                 }
             }
-            kahan_add(R0, K0, L0);
-            kahan_add(R1, K1, fmaf(T[6] - ref.ahb, L0, L1));
-            kahan_add(R2, K2, fmaf(T[7] - ref.aox, L0, L2));
+            if (a.work && lane == 0 && far_pixels) atomicAdd(a.work + 1, (unsigned long long)far_pixels);
+        }
+        if (a.fuse) {
+            // one split: the estimate is anchor + S1 / S0 (the Kahan terms hold
+            // minus what the sums lack)
+            const float2 e = make_float2(plus_quotient(anc_hb, R1, -K1, R0, -K0), plus_quotient(anc_ox, R2, -K2, R0, -K0));
+            s_est[tr * kDirectSide + tc] = e;
+            if (valid) a.est[(size_t)w.f * a.LL + p] = e;
+        } else if (valid) {
+            float *out = a.part + ((size_t)w.f * a.split + w.split) * kPartFields * a.LL;
+            out[p] = m;
+            out[a.LL + p] = R0;
+            out[2 * a.LL + p] = R1;
+            out[3 * a.LL + p] = R2;
+            out[4 * a.LL + p] = anc_hb;
+            out[5 * a.LL + p] = anc_ox;
         }
     }
-    if (a.work && lane == 0) atomicAdd(a.work, (unsigned long long)executed * PW * kChunkNodes);
-    if constexpr (!PRECISE) {
-        // Pixels whose observation lies far from the grid's nodes: the float32
-        // differences round at the scale of that distance, so their sums are
-        // formed again with double-float logits, as in the MFMA kernel (the
-        // plan sets far_rho2 from this kernel's precision budget).
-        unsigned long long far = __ballot(valid && ref.m + __log2f(R0) < -a.far_rho2);
-        unsigned far_pixels = 0;
-        while (__builtin_expect(far != 0, 0)) {
-            const int q = __builtin_ctzll(far);   // the pixel of lane q
-            far &= far - 1;
-            float qh[3], ql[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                qh[k] = __shfl(ph[k], q);
-                ql[k] = __shfl(pl[k], q);
-            }
-            const float mq = __shfl(ref.m, q);
-            float m_skip = mq;
-            if (a.gref) {
-                long long pq;
-                wave_pixel(a, w, q, pq);
-                const float g = a.gref[(size_t)w.f * a.LL + pq];
-                if (!(g < -a.far_rho2)) continue;
-                m_skip = fmaxf(m_skip, g);
-            }
-            ++far_pixels;
-            float S[3];
-            far_pixel_sums(a, w, qh, ql, m_skip, -mq, __shfl(ref.ahb, q), __shfl(ref.aox, q), S);
-            if (lane == q) {
-                R0 = S[0];
-                R1 = S[1];
-                R2 = S[2];
-            }
-        }
-        if (a.work && lane == 0 && far_pixels) atomicAdd(a.work + 1, (unsigned long long)far_pixels);
-    }
-    if (valid) {
-        float *out = a.part + ((size_t)w.f * a.split + w.split) * kPartFields * a.LL;
-        out[p] = ref.m;
-        out[a.LL + p] = R0;
-        out[2 * a.LL + p] = R1;
-        out[3 * a.LL + p] = R2;
-        out[4 * a.LL + p] = ref.ahb;
-        out[5 * a.LL + p] = ref.aox;
+    if (a.fuse) {
+        __syncthreads();
+        fused_maps<kDirectSide, kDirectSide, false>(a, w, s_est);
     }
 }
 
@@ -2358,7 +2326,7 @@ void launch_mfma(const PosteriorArgs &a, long long regions, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_posterior(const PosteriorArgs &a, bool mfma, hipStream_t s) {
-    const int bw = mfma ? kRegionW : kWaveTileW, bh = mfma ? kRegionH : 4 * 64 / kWaveTileW;
+    const int bw = mfma ? kRegionW : kDirectSide, bh = mfma ? kRegionH : kDirectSide;
     const long long blocks = (long long)((a.wl + bw - 1) / bw) * ((a.hl + bh - 1) / bh) * a.n_frames * a.split;
     if (blocks <= 0) return hipSuccess;
     if (mfma) {

@@ -67,8 +67,6 @@ struct hb_plan_s {
     float skip_log2 = kExactSkipLog2;
     float depth0 = kExactSkipLog2;      // = skip_log2 when nothing is certified
     float cert_log2 = 0.0f;
-    float band_log2 = kExactSkipLog2;   // = skip_log2 when no budget is in use
-    int band_chunks = 0;
 
     hipEvent_t done = nullptr;       // recorded after each uncaptured hb_estimate_frames
     bool timing = false;
@@ -125,12 +123,12 @@ Dims make_dims(const hb_plan_desc_t &d) {
     return m;
 }
 
-// Skip thresholds and band budget for a posterior tolerance tol (uM) on a
-// grid of G nodes with THb up to thb_max, seen by `split` grid splits.
+// Skip threshold, band budget and stated bound for a posterior tolerance tol
+// (uM) on a grid of G nodes with THb up to thb_max, seen by `split` grid splits.
 // tol > 0: T = the smallest threshold with 2 G 2^-T thb_max <= tol; skip hard
-// at T + 1 (at most half of tol) and spend the rest on a per-wave budget of
-// chunks bounded between T + 1 and T + 1 - kBandLog2 (each at most 16 nodes
-// of weight 2^-(T + 1 - kBandLog2)), shared out between the splits.  At the
+// at T + 1 (at most half of tol); the bound spends the rest on a per-wave
+// budget of chunks bounded between T + 1 and T + 1 - kBandLog2 (each at most 16
+// nodes of weight 2^-(T + 1 - kBandLog2)), shared out between the splits.  At the
 // exact threshold (T reaching kExactSkipLog2) there is no band and no error.
 // tol == 0: exact skipping.  tol < 0: no skipping.
 SkipRule skip_rule(double G, double thb_max, double tol, int split) {
@@ -210,8 +208,6 @@ void set_split(hb_plan_s *p, int split) {
     p->info.grid_split = split;
     const SkipRule rule = skip_rule((double)p->n_nodes, d.thb_max, d.posterior_tolerance, split);
     p->skip_log2 = rule.skip_log2;
-    p->band_log2 = rule.band_log2;
-    p->band_chunks = rule.band_chunks;
     p->depth0 = p->skip_log2;
     if (rule.bound > 0.0 && split == 1) {
         // skipped over kept weight that moves a mean by at most the stated
@@ -223,8 +219,8 @@ void set_split(hb_plan_s *p, int split) {
     }
     p->info.skip_bound = rule.bound;
     p->info.skip_log2 = p->skip_log2;
-    p->info.band_log2 = p->band_log2;
-    p->info.band_chunks = p->band_chunks;
+    p->info.band_log2 = rule.band_log2;
+    p->info.band_chunks = rule.band_chunks;
 }
 
 hb_status_t set_device(int dev) {
@@ -508,7 +504,7 @@ void split_block(const float *C, uint16_t *O) {
 // Threads for tables of n_sup super-tiles: one per 512 chunks or so (a thread
 // costs about as much to start as it takes to fill those).
 unsigned table_threads(int n_sup, int side) {
-    return (unsigned)std::max(1LL, std::min(32LL, (long long)n_sup * (side / 4) * (side / 4) / 512));
+    return (unsigned)std::max(1LL, std::min(16LL, (long long)n_sup * (side / 4) * (side / 4) / 512));
 }
 
 // Split bf16 A operands of every chunk of the super-tile table.
@@ -523,13 +519,14 @@ void build_split_ops(const std::vector<float> &table, int n_sup, int side, std::
     });
 }
 
-// Principal axes of the node differences across each chunk (both grid
-// directions), rows of `axes` in ascending order of their spread: the
-// eigenvectors of the summed outer products, by Jacobi rotations.
+// Principal axes of the node differences across the chunks (both grid
+// directions) of up to 64 super-tiles spread over the grid, rows of `axes` in
+// ascending order of their spread: the eigenvectors of the summed outer
+// products, by Jacobi rotations.
 void principal_axes(const std::vector<float> &table, int n_sup, int side, float axes[9]) {
     const int stride = super_floats(side), cps = (side / 4) * (side / 4);
     double A[3][3] = {}, V[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
-    for (int si = 0; si < n_sup; ++si)
+    for (int si = 0; si < n_sup; si += (n_sup + 63) / 64)
         for (int c = 0; c < cps; ++c) {
             const float *C = &table[(size_t)si * stride + kSupHdr + kMaxProbes * kProbeFloats + (size_t)c * kChunkFloats];
             for (int q : {3, 12}) {   // along SO2, along THb
@@ -769,8 +766,6 @@ hb_status_t estimate(hb_plan_s *p, const void *d_frames, int32_t n_frames, const
         pa.skip_log2 = p->skip_log2;
         pa.depth0 = p->depth0;
         pa.cert_log2 = p->cert_log2;
-        pa.band_log2 = p->band_log2;
-        pa.band_chunks = p->band_chunks;
         pa.part = cb.part;
         pa.lo = p->d_lo;
         pa.precise = p->precise ? 1 : 0;
@@ -782,9 +777,9 @@ hb_status_t estimate(hb_plan_s *p, const void *d_frames, int32_t n_frames, const
             pa.gref = cb.gref;
             if (launch_reference(pa, s) != hipSuccess) return HB_ERR_DEVICE;
         }
-        // One split, MFMA kernel, n <= 3: the posterior writes the maps (from
-        // four levels on its few workgroups would write large regions).
-        fused = p->use_mfma && p->split == 1 && p->dims.levels <= 3;
+        // One split, n <= 3: the posterior writes the maps (from four levels
+        // on its few workgroups would write large regions).
+        fused = p->split == 1 && p->dims.levels <= 3;
         if (fused) {
             pa.fuse = 1;
             pa.vec = vec;
