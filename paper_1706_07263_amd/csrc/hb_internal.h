@@ -54,6 +54,14 @@ namespace hb {
 // of chunk row l / 16.
 constexpr int kSplitLaneBytes = 16;
 constexpr int kSplitChunkBytes = 64 * kSplitLaneBytes;
+// Chunk record of the MFMA kernel: the operand followed by the four rows'
+// affine coefficients (A_h, B_h, A_t, 0; a copy of the super-tile table's).
+// One scalar offset then addresses both loads, where two tables take a
+// product and a sum more per chunk: with the mask of the chunks walked by
+// s_ff1 and s_bitset0, 12 instead of 20 scalar instructions beside the 28
+// vector ones.  Sixteen 1920x1080 frames 1978 -> 1945 us a call, one such frame
+// 183 -> 177, a 640x480 frame 71 -> 67, a pair on a 512 x 512 grid 2480 -> 2380.
+constexpr int kChunkRecordBytes = kSplitChunkBytes + 64;
 // Precision rule for the MFMA kernel.  Its expanded logit rounds at the scale
 // of the squared super-tile radius R^2 (scaled units), and a coarse grid
 // (node spacing h in uM of Hb/HbO2) turns a logit error into an estimate error
@@ -254,7 +262,7 @@ struct PosteriorArgs {
     int n_frames;
     const float *z;          // [n][6][LL]
     const float *supers;     // [n_supers][super_floats(side)]
-    const void *split_ops;   // [n_supers][chunks_per_super][kSplitChunkBytes] bf16 A operands
+    const void *split_ops;   // [n_supers][chunks_per_super][kChunkRecordBytes] chunk records
     int n_supers;
     int super_stride;        // floats
     int chunks_per_super;

@@ -872,6 +872,18 @@ constexpr int kXcds = 8;   // accelerator complex dies of an MI355X, each with i
 constexpr int kResidentWaves = 256 * 4 * 6;
 constexpr int kOrderSquare = 8;
 
+// Lowest set bit (-1: none) and the mask without bit c, one scalar
+// instruction each.
+__device__ __forceinline__ int lowest_bit(unsigned long long m) {
+    int c;
+    asm("s_ff1_i32_b64 %0, %1" : "=s"(c) : "s"(m));
+    return c;
+}
+__device__ __forceinline__ unsigned long long clear_bit(unsigned long long m, int c) {
+    asm("s_bitset0_b64 %0, %1" : "+s"(m) : "s"(c));
+    return m;
+}
+
 struct WaveWork {
     int f, split, s0, s1;
     int r0, c0;  // origin of the wave's tile (of the workgroup's region) in LL pixels
@@ -1668,12 +1680,10 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
     const float anc_ox = constant(a.headers)[(size_t)best * kHdrFloats + 7];
 
     unsigned executed = 0;   // chunks evaluated by this wave
-    // Split operands through a buffer resource: the lane offset stays in a
-    // register and the chunk offset is scalar; loads past the table return 0.
-    const __amdgpu_buffer_rsrc_t split_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<void *>(a.split_ops), (short)0, a.n_supers * a.chunks_per_super * kSplitChunkBytes, kBufferWord3);
-    const __amdgpu_buffer_rsrc_t super_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(a.supers), (short)0, a.n_supers * a.super_stride * 4, kBufferWord3);
+    // Chunk records through a buffer resource: the lane offset stays in a
+    // register and the record's offset is scalar; loads past the table return 0.
+    const __amdgpu_buffer_rsrc_t ops = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<void *>(a.split_ops), (short)0, a.n_supers * a.chunks_per_super * kChunkRecordBytes, kBufferWord3);
     const int cps = a.chunks_per_super;
     // Several waves per tile: the tiles of the workgroup go through the same
     // barriers, so they learn of each other whether one has more to do.
@@ -1721,32 +1731,28 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
                                               (unsigned)__builtin_amdgcn_readlane((int)own.lo, k);
                     const int si = __builtin_amdgcn_readlane(own.si, k);
                     executed += __popcll(walk);
-                    const int s_first = si * cps;   // first chunk of the super-tile in the split table
-                    // byte offset of the first chunk's row coefficients in the super-tile table
-                    const int c_first = (si * a.super_stride + kSupHdr + kMaxProbes * kProbeFloats + 104) * 4;
+                    const int s_first = si * cps * kChunkRecordBytes;   // records of the super-tile
                     // Walk the kept chunks with two operand buffers: the next chunk's
                     // operands are in flight while the current one is evaluated.  The
-                    // loads are issued unconditionally (the last chunk is simply loaded
-                    // again), so the wait counts match on every path and a wait for the
-                    // current chunk never waits for the next one.
-                    int tail = 0;
-                    auto take = [&](bf16x8 &bv, f32x3 &qm) -> bool {
-                        const bool got = walk != 0;
-                        tail = got ? __builtin_ctzll(walk | (1ull << 63)) : tail;
-                        walk &= walk - 1;
-                        bv = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
-                                                            split_rsrc, lane * kSplitLaneBytes,
-                                                            (s_first + tail) * kSplitChunkBytes, 0));
-                        qm = __builtin_bit_cast(f32x3, __builtin_amdgcn_raw_buffer_load_b96(
-                                                           super_rsrc, lk * 16, c_first + tail * (kChunkFloats * 4), 0));
+                    // loads are issued unconditionally (past the last chunk they fetch
+                    // the super-tile's first), so the wait counts match on every path
+                    // and a wait for the current chunk never waits for the next one.
+                    int left = __popcll(walk);
+                    auto take = [&](bf16x8 &bv, f32x3 &qm) {
+                        const int c = max(lowest_bit(walk), 0);
+                        walk = clear_bit(walk, c);
+                        const int at = s_first + c * kChunkRecordBytes;
+                        bv = __builtin_bit_cast(
+                            bf16x8, __builtin_amdgcn_raw_buffer_load_b128(ops, lane * kSplitLaneBytes, at, 0));
+                        qm = __builtin_bit_cast(
+                            f32x3, __builtin_amdgcn_raw_buffer_load_b96(ops, kSplitChunkBytes + lk * 16, at, 0));
                         // keep these loads ahead of the evaluation that follows
                         __builtin_amdgcn_sched_barrier(0);
-                        return got;
                     };
                     bf16x8 bA, bB;
                     f32x3 qA, qB;
-                    take(bA, qA);   // the mask holds at least one chunk
-                    bool next = take(bB, qB);
+                    take(bA, qA);
+                    take(bB, qB);
                     ConstFloat *H = constant(a.headers) + (size_t)si * kHdrFloats;
                     const float ch = lk == 0 ? H[8] : (lk == 1 ? H[9] : H[10]);
                     const float cl = lk == 0 ? H[11] : (lk == 1 ? H[12] : H[13]);
@@ -1781,11 +1787,11 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
                     using First = std::true_type;
                     using Next = std::false_type;
                     eval(bA, qA, First{});
-                    while (next) {
-                        const bool got = take(bA, qA);
+                    while (--left) {
+                        take(bA, qA);
                         eval(bB, qB, Next{});
-                        if (!got) break;
-                        next = take(bB, qB);
+                        if (--left == 0) break;
+                        take(bB, qB);
                         eval(bA, qA, Next{});
                     }
                     const float from_hb = H[6] - anc_hb, from_ox = H[7] - anc_ox;

@@ -507,15 +507,20 @@ unsigned table_threads(int n_sup, int side) {
     return (unsigned)std::max(1LL, std::min(16LL, (long long)n_sup * (side / 4) * (side / 4) / 512));
 }
 
-// Split bf16 A operands of every chunk of the super-tile table.
-void build_split_ops(const std::vector<float> &table, int n_sup, int side, std::vector<uint16_t> &ops) {
+// Split bf16 A operands of every chunk of the super-tile table, `record` bytes
+// apart; records longer than the operand also get the rows' coefficients.
+void build_split_ops(const std::vector<float> &table, int n_sup, int side, std::vector<uint16_t> &ops,
+                     size_t record = kSplitChunkBytes) {
     const int stride = super_floats(side), n_chunks = (side / 4) * (side / 4);
-    ops.assign((size_t)n_sup * n_chunks * kSplitChunkBytes / 2, 0);
+    ops.assign((size_t)n_sup * n_chunks * record / 2, 0);
     for_supers(n_sup, table_threads(n_sup, side), [&](int s_begin, int s_end) {
         for (int si = s_begin; si < s_end; ++si)
-            for (int c = 0; c < n_chunks; ++c)
-                split_block(&table[(size_t)si * stride + kSupHdr + kMaxProbes * kProbeFloats + (size_t)c * kChunkFloats],
-                            &ops[((size_t)si * n_chunks + c) * kSplitChunkBytes / 2]);
+            for (int c = 0; c < n_chunks; ++c) {
+                const float *C = &table[(size_t)si * stride + kSupHdr + kMaxProbes * kProbeFloats + (size_t)c * kChunkFloats];
+                uint16_t *O = &ops[((size_t)si * n_chunks + c) * record / 2];
+                split_block(C, O);
+                if (record > kSplitChunkBytes) std::memcpy(O + kSplitChunkBytes / 2, C + 104, 64);
+            }
     });
 }
 
@@ -903,7 +908,7 @@ hb_status_t hb_plan_create(const hb_plan_desc_t *desc, int device, hb_plan_t *ou
     if (st == HB_OK) st = dev_alloc(p, (void **)&p->d_mf, sizeof(float) * 16);
     if (st == HB_OK) st = dev_alloc(p, (void **)&p->d_tiles, sizeof(float) * (size_t)p->n_tiles * super_floats(p->side));
     if (st == HB_OK)
-        st = dev_alloc(p, &p->d_split, (size_t)kSplitChunkBytes * p->n_tiles * (p->side / 4) * (p->side / 4));
+        st = dev_alloc(p, &p->d_split, (size_t)kChunkRecordBytes * p->n_tiles * (p->side / 4) * (p->side / 4));
     {
         const size_t n = (size_t)p->n_tiles, cps = (size_t)(p->side / 4) * (p->side / 4);
         p->boxes_at = n * kHdrFloats;
@@ -1060,7 +1065,7 @@ hb_status_t hb_set_forward_model(hb_plan_t p, const hb_forward_model_t *fm) {
         return HB_ERR_DEVICE;
     std::vector<float> tests;
     std::vector<uint16_t> probes, split_ops;
-    build_split_ops(tiles, p->n_tiles, p->side, split_ops);
+    build_split_ops(tiles, p->n_tiles, p->side, split_ops, kChunkRecordBytes);
     principal_axes(tiles, p->n_tiles, p->side, p->axes);
     build_test_tables(tiles, p->n_tiles, (d.grid_so2 + p->side - 1) / p->side, p->side, p->boxes_at, p->axes, tests,
                       probes);
@@ -1209,9 +1214,19 @@ hb_status_t hb_debug_copy(hb_plan_t p, int32_t which, int32_t frame, void *host_
             const int cps = (p->side / 4) * (p->side / 4);
             const size_t n_chunks = (size_t)p->n_tiles * cps;
             if (which == HB_DEBUG_SPLIT_OPERANDS) {
-                src = p->d_split;
-                avail = n_chunks * kSplitChunkBytes;
-                break;
+                // whole operands out of their records, then the rest of the last one
+                if (bytes > n_chunks * kSplitChunkBytes) return HB_ERR_INVALID_ARG;
+                if (set_device(p->device) != HB_OK) return HB_ERR_DEVICE;
+                if (hipDeviceSynchronize() != hipSuccess) return HB_ERR_DEVICE;
+                const size_t whole = bytes / kSplitChunkBytes, rest = bytes % kSplitChunkBytes;
+                if (whole && hipMemcpy2D(host_dst, kSplitChunkBytes, p->d_split, kChunkRecordBytes, kSplitChunkBytes, whole,
+                                         hipMemcpyDeviceToHost) != hipSuccess)
+                    return HB_ERR_DEVICE;
+                if (rest && hipMemcpy((char *)host_dst + whole * kSplitChunkBytes,
+                                      (const char *)p->d_split + whole * kChunkRecordBytes, rest,
+                                      hipMemcpyDeviceToHost) != hipSuccess)
+                    return HB_ERR_DEVICE;
+                return HB_OK;
             }
             // gather the first 64 floats of every chunk from a host copy of the table
             if (bytes > n_chunks * 64 * sizeof(float)) return HB_ERR_INVALID_ARG;
