@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 #include <vector>
@@ -256,7 +257,42 @@ struct HaarArgs {
     int df;                  // double-float logs, means and Tikhonov (always from three levels on)
 };
 
+// Division of 0 <= n < 2^31 by a fixed d >= 1 as a product: with
+// mul = floor(2^32 / d) + 1 the high word of n mul is n / d or one more (n mul
+// exceeds 2^32 n / d by less than 2^31), which the remainder shows.
+struct FastDivide {
+    int d = 1;
+    unsigned mul = 0;
+    FastDivide() = default;
+    explicit FastDivide(int by) : d(by), mul(by > 1 ? (unsigned)((1ull << 32) / (unsigned)by) + 1 : 0) {}
+    __host__ __device__ int divide(int n) const {
+        if (d == 1) return n;
+        const unsigned q = (unsigned)((unsigned long long)(unsigned)n * mul >> 32);
+        return (int)(q * (unsigned)d > (unsigned)n ? q - 1 : q);
+    }
+};
+
+// Order in which the posterior's workgroups go through the blocks of a frame.
+constexpr int kOrderSquare = 8;
+struct BlockOrder {
+    FastDivide split, frame, band;   // by the splits, the blocks of a frame and of a band
+    FastDivide low_square, rest;     // by the blocks of a square of the last band, the columns past the squares
+    int full = 0;                    // full-width squares of a band
+    int low_band = 0, low_rows = 0;  // the last band, if it has fewer rows (else past the end), and its rows
+    BlockOrder() = default;
+    BlockOrder(int cols, int rows, int splits)
+        : split(splits),
+          frame(cols * rows),
+          band(kOrderSquare * cols),
+          low_square(kOrderSquare * std::max(rows % kOrderSquare, 1)),
+          rest(std::max(cols % kOrderSquare, 1)),
+          full(cols / kOrderSquare),
+          low_band(rows / kOrderSquare),
+          low_rows(rows % kOrderSquare) {}
+};
+
 struct PosteriorArgs {
+    BlockOrder order;   // set by the launcher
     long long LL;
     int hl, wl;              // low-pass band size (LL = hl * wl)
     int n_frames;

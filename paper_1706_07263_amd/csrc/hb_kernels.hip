@@ -870,7 +870,6 @@ __device__ __forceinline__ bf16x8 split_pixel_operand(float u, float c, bool coo
 constexpr int kXcds = 8;   // accelerator complex dies of an MI355X, each with its own L2
 // Waves resident at once: 256 CUs x 4 SIMDs x 6 waves.
 constexpr int kResidentWaves = 256 * 4 * 6;
-constexpr int kOrderSquare = 8;
 
 // Lowest set bit (-1: none) and the mask without bit c, one scalar
 // instruction each.
@@ -909,38 +908,46 @@ __device__ __forceinline__ int xcd_order(int bid, int n, int resident) {
     return n > resident && bid < per_xcd * kXcds ? (bid % kXcds) * per_xcd + bid / kXcds : bid;
 }
 
-// Block number idx of BW x BH LL pixels (and its grid split).
+// Block number idx of BW x BH LL pixels (and its grid split).  Blocks go in
+// squares of kOrderSquare x kOrderSquare (bands of that many block rows,
+// squares left to right, row-major inside a square): the workgroups an XCD runs
+// at once then cover a compact part of the frame.  Divisions by the launch's
+// numbers are products: as divisions they took some 500 scalar instructions at
+// the start of every wave, where it has no load in flight yet.
 template <int BW, int BH>
 __device__ __forceinline__ WaveWork block_work(const PosteriorArgs &a, int idx) {
     WaveWork w;
-    const int S = a.split;
-    w.split = idx % S;
-    const int chunk = idx / S;
-    const int bcols = (a.wl + BW - 1) / BW;
-    const int brows = (a.hl + BH - 1) / BH;
-    const int per_frame = bcols * brows;
-    w.f = chunk / per_frame;
-    const int t = chunk % per_frame;
-    // Blocks in squares of kOrderSquare x kOrderSquare (bands of that many
-    // block rows, squares left to right, row-major inside a square): the
-    // workgroups an XCD runs at once then cover a compact part of the frame.
-    const int band = t / (kOrderSquare * bcols), in_band = t % (kOrderSquare * bcols);
-    const int R = min(kOrderSquare, brows - band * kOrderSquare);
-    const int full = bcols / kOrderSquare;          // full-width squares in the band
+    const BlockOrder &o = a.order;
+    int chunk = idx;
+    w.split = 0;
+    if (a.split > 1) {
+        chunk = o.split.divide(idx);
+        w.split = idx - chunk * a.split;
+    }
+    w.f = o.frame.divide(chunk);
+    const int t = chunk - w.f * o.frame.d;
+    const int band = o.band.divide(t), in_band = t - band * o.band.d;
+    const bool low = band == o.low_band;            // the last band, with fewer rows
+    const int square = kOrderSquare * (low ? o.low_rows : kOrderSquare);
     int br, bc;
-    if (in_band < full * R * kOrderSquare) {
-        const int sq = in_band / (R * kOrderSquare), o = in_band % (R * kOrderSquare);
-        br = o / kOrderSquare;
-        bc = sq * kOrderSquare + o % kOrderSquare;
+    if (in_band < o.full * square) {
+        const int sq = low ? o.low_square.divide(in_band) : in_band / (kOrderSquare * kOrderSquare);
+        const int in = in_band - sq * square;
+        br = in / kOrderSquare;
+        bc = sq * kOrderSquare + in % kOrderSquare;
     } else {
-        const int wl = bcols - full * kOrderSquare, o = in_band - full * R * kOrderSquare;
-        br = o / wl;
-        bc = full * kOrderSquare + o % wl;
+        const int in = in_band - o.full * square;
+        br = o.rest.divide(in);
+        bc = o.full * kOrderSquare + in - br * o.rest.d;
     }
     w.r0 = (band * kOrderSquare + br) * BH;
     w.c0 = bc * BW;
-    w.s0 = S == 1 ? 0 : (int)((long long)a.n_supers * w.split / S);
-    w.s1 = S == 1 ? a.n_supers : (int)((long long)a.n_supers * (w.split + 1) / S);
+    w.s0 = 0;
+    w.s1 = a.n_supers;
+    if (a.split > 1) {
+        w.s0 = (int)((long long)a.n_supers * w.split / a.split);
+        w.s1 = (int)((long long)a.n_supers * (w.split + 1) / a.split);
+    }
     return w;
 }
 
@@ -1321,7 +1328,12 @@ __device__ __forceinline__ void far_pixel_sums(const PosteriorArgs &a, const Wav
 // boxes along the nodes' axes: sixteen 1080p frames 2274 -> 1976 us, 1280x1024
 // pair on a 512 x 512 grid 2794 -> 2470, 1280x1024 frame at level 0 with the
 // illumination term 1198 -> 1049, sixteen 320x240 frames 205 -> 165, one
-// 640x480 frame 85 -> 72.
+// 640x480 frame 85 -> 72.  What a wave does before its first chunk is a chain
+// of latencies: the bounds of the first 64 super-tiles are formed once and kept
+// in LDS, the next probe operand is fetched while one is evaluated and the
+// block's place takes no division: a 64x64 frame 25.0 -> 24.3 us a call, one
+// 1080p frame 180 -> 178, a 3840x2160 frame 223 -> 221.
+
 // Order between the lanes of a tile: of its only wave, or of the workgroup.
 template <int NW>
 __device__ __forceinline__ void tile_sync() {
@@ -1342,15 +1354,17 @@ struct KeptSuper {
 // svlo, and the chunks of each whose bound v has vlo < v <= vhi; what lies
 // below counts into `mass`.  The NW waves of a tile share the chunk tests:
 // 64 / chunks_per_super super-tiles at once, lane sub * cps + ci chunk ci of
-// the sub-th.  Returns the length of the list.  The caller orders the waves
-// before the list is read.
+// the sub-th.  `bound` holds the bounds of the split's first 64 super-tiles.
+// Returns the length of the list.  The caller orders the waves before the list
+// is read.
 struct ChunkTest {
     float vlo, vhi, svlo, mmin;
     bool last;   // nothing below counts
 };
 template <int NW>
-__device__ __forceinline__ int list_chunks(const PosteriorArgs &a, const WaveWork &w, KeptSuper *kept, int wave,
-                                           const float (&zbox)[6], const ChunkTest &t, int &g, unsigned &mass) {
+__device__ __forceinline__ int list_chunks(const PosteriorArgs &a, const WaveWork &w, KeptSuper *kept,
+                                           const float *bound, int wave, const float (&zbox)[6], const ChunkTest &t,
+                                           int &g, unsigned &mass) {
     const int lane = threadIdx.x & 63;
     const int cps = a.chunks_per_super, per_test = a.supers_per_test;
     const int sub = (int)((unsigned)lane * (unsigned)a.inv_chunks >> 16), ci = lane - sub * cps;   // lane / cps
@@ -1359,7 +1373,12 @@ __device__ __forceinline__ int list_chunks(const PosteriorArgs &a, const WaveWor
     int K = 0;
     while (g < w.s1) {
         const int sl = g + lane;
-        const float sv = (sl < w.s1 ? box_box_bound(a.headers + (size_t)sl * kHdrFloats, zbox) : -INFINITY) - t.mmin;
+        float sv = -INFINITY;
+        if (g == w.s0)
+            sv = bound[lane];
+        else if (sl < w.s1)
+            sv = box_box_bound(a.headers + (size_t)sl * kHdrFloats, zbox);
+        sv -= t.mmin;
         const unsigned long long smask = __builtin_amdgcn_ballot_w64(sv > t.svlo);
         const int n = __popcll(smask);
         // the list holds 64; exact and no skipping take the same windows
@@ -1396,6 +1415,7 @@ __device__ __forceinline__ int list_chunks(const PosteriorArgs &a, const WaveWor
 template <int NW>
 struct TileShared {
     KeptSuper kept[64];
+    float bound[64];               // of the split's first 64 super-tiles
     float total[6][kTilePixels];   // S0, S1, S2 and their compensation, per pixel
     // several waves: sums of the segments, best probes, skipped weights
     float part[NW > 1 ? kSegments : 1][6][kTilePixels];
@@ -1568,6 +1588,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
     int best = w.s0;
     for (int g = w.s0; g < w.s1; g += 64) {
         const float b = super_bound(g + lane);
+        if (g == w.s0) sh.bound[lane] = b;   // every wave writes the same values
         const float r = row_reduce<true>(b);
         const float top = fmaxf(fmaxf(lane_value(r, 0), lane_value(r, 16)), fmaxf(lane_value(r, 32), lane_value(r, 48)));
         if (top > mup) {
@@ -1576,14 +1597,16 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
         }
     }
     best = __builtin_amdgcn_readfirstlane(best);
+    tile_sync<1>();   // each wave reads what it has written itself
+    auto super_bound_of = [&](int g) { return g == w.s0 ? sh.bound[lane] : super_bound(g + lane); };
     float am[PB] = {-INFINITY, -INFINITY};   // reference of pixel b*16 + lp
     {
         bf16x8 pv[PB];
         const float x[PB] = {ah[0] + al[0], ah[1] + al[1]}, none[PB] = {0.0f, 0.0f};
         pixel_operands(x, none, std::false_type{}, pv);
         const int shift = 4 - a.probe_shift;   // log2 of the super-tiles of one probe operand
-        auto probe = [&](int blk) {
-            const bf16x8 v = reinterpret_cast<const bf16x8 *>(a.probes)[(size_t)blk * 64 + lane];
+        auto operand = [&](int blk) { return reinterpret_cast<const bf16x8 *>(a.probes)[(size_t)blk * 64 + lane]; };
+        auto probe = [&](int blk, const bf16x8 &v) {
 #pragma unroll
             for (int b = 0; b < PB; ++b) {
                 f32x4 d = mfma_16x16x32_bf16(v, pv[b], zero4);
@@ -1599,24 +1622,32 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
             }
         };
         const int first = best >> shift;
-        probe(first);   // every wave
+        probe(first, operand(first));   // every wave
 #pragma unroll
         for (int b = 0; b < PB; ++b) am[b] = max_rows(am[b]);
         float lowest = INFINITY;
 #pragma unroll
         for (int b = 0; b < PB; ++b) lowest = fminf(lowest, am[b] > -INFINITY ? am[b] : INFINITY);
         lowest = lane_value(row_reduce<false>(lowest), 0);
+        // The next operand is in flight while one is evaluated.
         int done = first, turn = 0;
+        int held = -1;
+        bf16x8 ahead = {};
         for (int g = w.s0; g < w.s1; g += 64) {
-            unsigned long long cand = __builtin_amdgcn_ballot_w64(super_bound(g + lane) > lowest);
+            unsigned long long cand = __builtin_amdgcn_ballot_w64(super_bound_of(g) > lowest);
             while (cand) {
                 const int blk = (g + __builtin_ctzll(cand)) >> shift;
                 cand &= cand - 1;
                 if (blk == first || blk == done) continue;
                 done = blk;
-                if (NW == 1 || turn++ % NW == wave) probe(blk);
+                if (NW > 1 && turn++ % NW != wave) continue;
+                const bf16x8 v = ahead;
+                ahead = operand(blk);
+                if (held >= 0) probe(held, v);
+                held = blk;
             }
         }
+        if (held >= 0) probe(held, ahead);
         // over the pixel's lanes and the waves
 #pragma unroll
         for (int b = 0; b < PB; ++b) am[b] = max_rows(am[b]);
@@ -1709,7 +1740,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
         int g = w.s0;
         for (bool more = true; more;) {
             const ChunkTest test{vlo, vhi, svlo, mmin, last};
-            const int K = active ? list_chunks<NW>(a, w, sh.kept, wave, zbox, test, g, mass) : 0;
+            const int K = active ? list_chunks<NW>(a, w, sh.kept, sh.bound, wave, zbox, test, g, mass) : 0;
             if (NW == 1 && K == 0) break;
             tile_sync<NW>();
             // Segments in turn (which wave sums a segment changes no bit).
@@ -1732,6 +1763,9 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
                     const int si = __builtin_amdgcn_readlane(own.si, k);
                     executed += __popcll(walk);
                     const int s_first = si * cps * kChunkRecordBytes;   // records of the super-tile
+                    ConstFloat *H = constant(a.headers) + (size_t)si * kHdrFloats;
+                    const float ch = lk == 0 ? H[8] : (lk == 1 ? H[9] : H[10]);
+                    const float cl = lk == 0 ? H[11] : (lk == 1 ? H[12] : H[13]);
                     // Walk the kept chunks with two operand buffers: the next chunk's
                     // operands are in flight while the current one is evaluated.  The
                     // loads are issued unconditionally (past the last chunk they fetch
@@ -1753,9 +1787,6 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
                     f32x3 qA, qB;
                     take(bA, qA);
                     take(bB, qB);
-                    ConstFloat *H = constant(a.headers) + (size_t)si * kHdrFloats;
-                    const float ch = lk == 0 ? H[8] : (lk == 1 ? H[9] : H[10]);
-                    const float cl = lk == 0 ? H[11] : (lk == 1 ? H[12] : H[13]);
                     bf16x8 av[PB];
                     const float r[PB] = {(ah[0] - ch) + (al[0] - cl), (ah[1] - ch) + (al[1] - cl)};
                     pixel_operands(r, am, std::integral_constant<bool, DFC>{}, av);
@@ -1971,11 +2002,13 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
 // per (pixel, node).  Three 1006x758 frames at one level on a 24 x 20 grid: 89
 // us a call with sums over single nodes, the a-priori skip threshold and a
 // kernel of its own for the maps, 67 with the rows' affine moments, the
-// certificate and the maps written here.
+// certificate and the maps written here, 65 with the super-tiles' bounds kept in
+// LDS and the block's place found without divisions.
 constexpr int kDirectSide = 16;   // LL pixels of a workgroup's region along each axis
 template <bool PRECISE>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5))) void k_posterior_direct(PosteriorArgs a) {
     __shared__ KeptSuper s_kept[kBlockThreads / 64][64];
+    __shared__ float s_bound[kBlockThreads / 64][64];
     __shared__ float2 s_est[kDirectSide * kDirectSide];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -2015,6 +2048,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5
         int best = w.s0;
         for (int g = w.s0; g < w.s1; g += 64) {
             const float b = super_bound(g + lane), top = wave_reduce<true>(b);
+            if (g == w.s0) s_bound[wave][lane] = b;
             if (top > mup) {
                 mup = top;
                 best = g + __builtin_ctzll(__builtin_amdgcn_ballot_w64(b == top) | (1ull << 63));
@@ -2031,7 +2065,8 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5
         const float lowest = wave_reduce<false>(m > -INFINITY ? m : INFINITY);
         for (int g = w.s0; g < w.s1; g += 64) {
             const int sl = g + lane;
-            unsigned long long cand = __builtin_amdgcn_ballot_w64(sl != best && super_bound(sl) > lowest);
+            const float b = g == w.s0 ? s_bound[wave][lane] : super_bound(sl);
+            unsigned long long cand = __builtin_amdgcn_ballot_w64(sl != best && b > lowest);
             while (cand) {
                 probe(g + __builtin_ctzll(cand));
                 cand &= cand - 1;
@@ -2053,7 +2088,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5
             unsigned mass = 0;
             const ChunkTest test{vlo, vhi, fmaxf(nskip, vlo - kSuperMargin), mmin, last};
             for (int g = w.s0;;) {
-                const int K = list_chunks<1>(a, w, kept, 0, zbox, test, g, mass);
+                const int K = list_chunks<1>(a, w, kept, s_bound[wave], 0, zbox, test, g, mass);
                 if (K == 0) break;
                 tile_sync<1>();
                 const KeptSuper own = kept[lane];
@@ -2331,10 +2366,13 @@ void launch_mfma(const PosteriorArgs &a, long long regions, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_posterior(const PosteriorArgs &a, bool mfma, hipStream_t s) {
+hipError_t launch_posterior(const PosteriorArgs &args, bool mfma, hipStream_t s) {
     const int bw = mfma ? kRegionW : kDirectSide, bh = mfma ? kRegionH : kDirectSide;
-    const long long blocks = (long long)((a.wl + bw - 1) / bw) * ((a.hl + bh - 1) / bh) * a.n_frames * a.split;
+    const int cols = (args.wl + bw - 1) / bw, rows = (args.hl + bh - 1) / bh;
+    const long long blocks = (long long)cols * rows * args.n_frames * args.split;
     if (blocks <= 0) return hipSuccess;
+    PosteriorArgs a = args;
+    a.order = BlockOrder(cols, rows, a.split);
     if (mfma) {
         // Tiles that would all be resident at once with one wave each: the
         // launch would last as long as its busiest tile (2.3 times the mean on

@@ -564,6 +564,23 @@ def test_ragged_regions_agree_in_small_and_large_launches(torch_cuda, h, w, leve
     hbtest.assert_maps_close(got[:, :, r:, c:], ora, f"{h}x{w} L{levels}")
 
 
+@pytest.mark.parametrize("w,h,grid,split,kernel", [
+    (128, 64, 72, 1, "mfma"), (147, 73, 72, 1, "mfma"), (147, 73, 72, 3, "mfma"), (19, 131, 72, 1, "mfma"),
+    (147, 147, 20, 1, "direct"), (128, 128, 20, 1, "direct"), (147, 147, 64, 2, None)])
+def test_every_block_of_the_frame_order(torch_cuda, w, h, grid, split, kernel):
+    """The posterior's workgroups go through a frame in squares of 8 x 8
+    blocks (16 x 8 or 16 x 16 pixels): frames of whole squares, with columns
+    and a band of fewer rows left over, of one block column, with grid splits,
+    two frames a call."""
+    s = _settings(levels=0, grid=grid)
+    frames = np.stack([synth.single_frame(h, w, config=91, stream=i)[0] for i in range(2)])
+    run = hbtest.GpuRun(w, h, s, max_batch=2, grid_split=split)
+    if kernel:
+        assert run.plan.info()["posterior_kernel"] == kernel
+    hbtest.assert_maps_close(run(frames), hbtest.run_oracle(frames, "f32", s), f"{w}x{h} grid {grid} split {split}")
+    run.close()
+
+
 @pytest.mark.parametrize("levels", [0, 1, 2])
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("camera", ["default", "shifted"])
