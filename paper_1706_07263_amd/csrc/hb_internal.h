@@ -292,7 +292,8 @@ struct BlockOrder {
 };
 
 struct PosteriorArgs {
-    BlockOrder order;   // set by the launcher
+    BlockOrder order;   // set by the launcher, as is
+    int run_log2 = 0;   // the run of blocks an XCD takes at once (0: an eighth of the launch)
     long long LL;
     int hl, wl;              // low-pass band size (LL = hl * wl)
     int n_frames;

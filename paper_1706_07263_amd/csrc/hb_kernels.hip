@@ -897,15 +897,21 @@ __device__ __forceinline__ void square_or(float r, float m, bool sq, float &p, f
 }
 
 // Renumbered workgroup.  Workgroups are dealt to the 8 XCDs in turn; each XCD
-// takes a contiguous run of tiles (neighbouring pixels keep overlapping
-// chunks, which then stay in that XCD's L2).  The last n % 8 workgroups keep
-// their numbers.  A launch whose workgroups are all resident at once keeps the
-// plain numbering: its time is that of the slowest XCD, and interleaved tiles
-// spread the frame's costly regions over all eight (measured 1.5% faster for
-// one 1080p frame, slower from two frames on).
-__device__ __forceinline__ int xcd_order(int bid, int n, int resident) {
-    const int per_xcd = n / kXcds;
-    return n > resident && bid < per_xcd * kXcds ? (bid % kXcds) * per_xcd + bid / kXcds : bid;
+// takes runs of 2^run_log2 neighbouring blocks in turn (run_log2 = 0: one
+// contiguous eighth of the launch), since neighbouring pixels keep overlapping
+// chunks, which then stay in that XCD's L2.  Workgroups past the last whole
+// round of runs keep their numbers.  A launch whose workgroups are all resident
+// at once keeps the plain numbering: interleaved blocks spread the frame's
+// costly regions over all eight.
+__device__ __forceinline__ int xcd_order(int bid, int n, int resident, int run_log2) {
+    if (n <= resident) return bid;
+    if (run_log2 == 0) {
+        const int per_xcd = n / kXcds;
+        return bid < per_xcd * kXcds ? (bid % kXcds) * per_xcd + bid / kXcds : bid;
+    }
+    if (bid >= n / kXcds >> run_log2 << run_log2 << 3) return bid;
+    const int j = bid / kXcds, run = j >> run_log2;
+    return ((run * kXcds + bid % kXcds) << run_log2) + (j - (run << run_log2));
 }
 
 // Block number idx of BW x BH LL pixels (and its grid split).  Blocks go in
@@ -1451,7 +1457,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
     const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int wave = wid % NW;   // of its tile
     const int lp = lane & 15, lk = lane >> 4;
-    const int bid = xcd_order(blockIdx.x, gridDim.x, kResidentWaves / (NW * RT));
+    const int bid = xcd_order(blockIdx.x, gridDim.x, kResidentWaves / (NW * RT), a.run_log2);
     const int tile = RT == 1 ? bid % kRegionTiles : wid / NW;   // of its region
     const WaveWork w = block_work<kRegionW, kRegionH>(a, RT == 1 ? bid / kRegionTiles : bid);
     TileShared<NW> &sh = rsh.tile[RT == 1 ? 0 : tile];
@@ -2013,7 +2019,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const WaveWork w =
-        block_work<kDirectSide, kDirectSide>(a, xcd_order(blockIdx.x, gridDim.x, kResidentWaves / 4));
+        block_work<kDirectSide, kDirectSide>(a, xcd_order(blockIdx.x, gridDim.x, kResidentWaves / 4, a.run_log2));
     const int tr = (wave >> 1) * 8 + (lane >> 3), tc = (wave & 1) * 8 + (lane & 7);   // pixel of the region
     const bool valid = w.r0 + tr < a.hl && w.c0 + tc < a.wl;
     const long long p = (long long)min(w.r0 + tr, a.hl - 1) * a.wl + min(w.c0 + tc, a.wl - 1);
@@ -2366,6 +2372,19 @@ void launch_mfma(const PosteriorArgs &a, long long regions, hipStream_t s) {
 
 }  // namespace
 
+// Run length (log2, in blocks) in which a launch is dealt to the XCDs.  An XCD's
+// contiguous eighth of a few frames is one part of a picture, and costs differ
+// between the parts by more than short runs lose in L2: us a call with an eighth
+// and with runs of 8, 1080p frames on a 256 x 256 grid: one 179.5 and 175.4, two
+// 303 and 294, four 552 and 542, six 786 and 788, eight 1024 and 1033.  From six
+// on the eighth stays.  Tables past twice an XCD's L2 (4 MB) want longer runs:
+// 1280x1024 pair, eighth, runs of 8 and of 64: 320 x 320 grid (7 MB) 949, 918 and
+// 921; 384 x 384 (10 MB) 1317, 1303 and 1276; 448 x 448 1763, 1820 and 1715.
+static int xcd_run_log2(int n_frames, size_t table_bytes) {
+    if (n_frames >= 6) return 0;
+    return table_bytes <= (size_t)(8 << 20) ? 3 : 6;
+}
+
 hipError_t launch_posterior(const PosteriorArgs &args, bool mfma, hipStream_t s) {
     const int bw = mfma ? kRegionW : kDirectSide, bh = mfma ? kRegionH : kDirectSide;
     const int cols = (args.wl + bw - 1) / bw, rows = (args.hl + bh - 1) / bh;
@@ -2373,6 +2392,7 @@ hipError_t launch_posterior(const PosteriorArgs &args, bool mfma, hipStream_t s)
     if (blocks <= 0) return hipSuccess;
     PosteriorArgs a = args;
     a.order = BlockOrder(cols, rows, a.split);
+    a.run_log2 = xcd_run_log2(a.n_frames, (size_t)a.n_supers * a.chunks_per_super * kChunkRecordBytes);
     if (mfma) {
         // Tiles that would all be resident at once with one wave each: the
         // launch would last as long as its busiest tile (2.3 times the mean on
@@ -2384,10 +2404,12 @@ hipError_t launch_posterior(const PosteriorArgs &args, bool mfma, hipStream_t s)
         // tiles) 193 and 183.  More tiles keep the chip full by themselves, and
         // the waves of a tile repeat its set-up: 9600 tiles (128 x 128 grid)
         // 165 and 187 us, 20480 tiles 256 and 343.
-        if (blocks * kRegionTiles <= kResidentWaves)
+        if (blocks * kRegionTiles <= kResidentWaves) {
+            if (a.run_log2) a.run_log2 += 2;   // four workgroups a region
             launch_mfma<4, 1>(a, blocks, s);
-        else
+        } else {
             launch_mfma<1, kRegionTiles>(a, blocks, s);
+        }
     } else if (a.precise) {
         hipLaunchKernelGGL(k_posterior_direct<true>, dim3((unsigned)blocks), dim3(kBlockThreads), 0, s, a);
     } else {

@@ -581,6 +581,27 @@ def test_every_block_of_the_frame_order(torch_cuda, w, h, grid, split, kernel):
     run.close()
 
 
+@pytest.mark.parametrize("w,h,grid", [(260, 250, 72), (520, 402, 72), (520, 402, 384), (800, 780, 20)])
+def test_runs_of_blocks_cover_the_frame(torch_cuda, w, h, grid):
+    """Launches with more workgroups than are resident at once deal runs of 8
+    or (tables above 8 MB) 64 blocks to the XCDs, the rest in plain order:
+    every block's maps are those of the same block in a launch of its own."""
+    s = _settings(levels=0, grid=grid)
+    frames = synth.single_frame(h, w, config=92)[0][None]
+    whole = hbtest.GpuRun(w, h, s, grid_split=1)
+    out = whole(frames)
+    whole.close()
+    ch, cw = 32 + h % 16, 64 + w % 16   # block-aligned crops; the last ends with the frame
+    part = hbtest.GpuRun(cw, ch, s, grid_split=1)
+    for r in sorted({*range(0, h - ch + 1, 96), h - ch}):
+        for c in sorted({*range(0, w - cw + 1, 128), w - cw}):
+            r0, c0 = r // 16 * 16, c // 16 * 16
+            got = part(np.ascontiguousarray(frames[:, r0:r0 + ch, c0:c0 + cw]))
+            same = np.s_[..., :ch, :cw] if (r0 + ch, c0 + cw) == (h, w) else np.s_[..., :32, :64]
+            assert np.array_equal(got[same], out[:, :, r0:r0 + ch, c0:c0 + cw][same], equal_nan=True), (r0, c0)
+    part.close()
+
+
 @pytest.mark.parametrize("levels", [0, 1, 2])
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("camera", ["default", "shifted"])
