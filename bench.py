@@ -58,8 +58,8 @@ NOMINAL_CEILING_PAIRS_PER_S = 256 * N_SIMD * CLOCK_HZ / CHUNK_BLOCK_CYCLES      
 # rocprofv3 FETCH_SIZE/WRITE_SIZE runs summarised in profiles/, valid for the
 # device sources whose combined sha256 (kernel_source_sha) starts with
 # PROFILED_KERNEL_SHA; reported as null for any other source or workload.
-PROFILED_KERNEL_SHA = "53f13351ed65cd57"
-PROFILED_POSTERIOR_TRAFFIC = 1186.5e6
+PROFILED_KERNEL_SHA = "05bb76e6abbc4aa0"
+PROFILED_POSTERIOR_TRAFFIC = 1387.1e6
 KERNEL_SOURCES = ("hb_kernels.hip", "hb_internal.h", "hb_df.h")
 
 
@@ -620,10 +620,9 @@ def main():
     # double-float low-pass observation (24 B per low-pass pixel) written.
     k1_bytes = B * H * W * ((12 if a.dtype == "f32" else 6) + 8) + B * LL * 24
     stage["log_haar_GBps"] = k1_bytes / (stage["log_haar_ms"] * 1e-3) / 1e9
-    # With one grid split, the MFMA kernel and <= 2 levels the posterior kernel
-    # writes the maps itself and the recomposition kernel is not launched.
-    stage["recompose_fused"] = bool(info["grid_split"] == 1 and info["posterior_kernel"] == "mfma"
-                                    and a.levels <= 2)
+    # With one grid split and <= 3 levels the posterior kernel writes the maps
+    # itself and the recomposition kernel is not launched.
+    stage["recompose_fused"] = bool(info["grid_split"] == 1 and a.levels <= 3)
 
     modes = None
     if "modes" in legs:

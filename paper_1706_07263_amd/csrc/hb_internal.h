@@ -183,7 +183,8 @@ inline int super_floats(int side) {
 constexpr int kStripPixels = 2048;
 constexpr int kBlockThreads = 256;
 
-// Tables of the skip tests and of the MFMA kernel's probes, derived from the super-tile table:
+// Tables of the skip tests and of the MFMA kernel's probes, derived from the
+// super-tile table:
 //   axes     3 x 3 rotation (rows: unit vectors) along which the boxes lie:
 //            the principal directions of the differences between neighbouring
 //            nodes, the strongest last.  The nodes form a surface, so boxes

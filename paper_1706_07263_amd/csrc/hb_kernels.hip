@@ -3,17 +3,22 @@
 //   K0  k_tikhonov_fp64     plan time, FP64: E, (E'E + gamma I)^-1 E'   (Method, Eq. 5)
 //   K1  k_log_haar_reg<n>   log-attenuation, n-level 2D Haar, Tikhonov on the
 //                           directional coefficients and the inverse Haar of
-//                           that detail part, one block per thread (n <= 2)
-//       k_log_haar          the same in LDS-staged strips (unaligned frames)
+//                           that detail part, one block per thread (n <= 2);
+//                           with the linear low-pass estimator also the maps
+//       k_log_haar          the same in LDS-staged strips (unaligned frames of
+//                           n <= 2 levels)
 //       k_log_haar_df       log-attenuation, block means and detail part in
-//                           double-float (any n)          (Eq. 1-2, 4, 5)
+//                           double-float: three levels and more, and operators
+//                           with a large norm at any n    (Eq. 1-2, 4, 5)
 //   K2a k_reference         best probe over the whole grid (split grids only)
 //   K2  k_posterior         posterior mean over the THb x SO2 grid on the
-//                           low-pass band (MFMA logits); with one split it
-//                           also writes the maps                   (Fig. 1)
+//                           low-pass band (MFMA logits); with one split and
+//                           n <= 3 it also writes the maps         (Fig. 1)
 //       k_posterior_direct  the same with VALU logits (coarse grids, small sigma;
 //                           double-float logits for the coarsest)
 //   K3  k_recompose         split merge plus detail part to the THb/SO2 maps
+//                           (split grids, four levels and more, the linear
+//                           low-pass of unaligned frames)
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -1328,7 +1333,7 @@ __device__ __forceinline__ void far_pixel_sums(const PosteriorArgs &a, const Wav
 //
 // Bound by VALU issue: 96% busy on sixteen 1080p frames (256 x 256 grid), 14
 // instructions (one MFMA and four exponentials among them) per 256 pairs and
-// about 3100 per tile around them (12460 in all).  Six waves per SIMD (80
+// about 3100 per tile around them (12500 in all).  Six waves per SIMD (80
 // VGPRs; spills outside the chunk loop only).  Times a call with tiles of 8 x 4
 // neighbours and boxes along the channels -> tiles of like observations and
 // boxes along the nodes' axes: sixteen 1080p frames 2274 -> 1976 us, 1280x1024
