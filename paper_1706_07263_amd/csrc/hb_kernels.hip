@@ -2377,6 +2377,9 @@ void launch_mfma(const PosteriorArgs &a, long long regions, hipStream_t s) {
 
 }  // namespace
 
+// Chunk tables up to twice an XCD's L2 (4 MB).
+constexpr size_t kTableNearL2 = 8 << 20;
+
 // Run length (log2, in blocks) in which a launch is dealt to the XCDs.  An XCD's
 // contiguous eighth of a few frames is one part of a picture, and costs differ
 // between the parts by more than short runs lose in L2: us a call with an eighth
@@ -2387,7 +2390,7 @@ void launch_mfma(const PosteriorArgs &a, long long regions, hipStream_t s) {
 // 921; 384 x 384 (10 MB) 1317, 1303 and 1276; 448 x 448 1763, 1820 and 1715.
 static int xcd_run_log2(int n_frames, size_t table_bytes) {
     if (n_frames >= 6) return 0;
-    return table_bytes <= (size_t)(8 << 20) ? 3 : 6;
+    return table_bytes <= kTableNearL2 ? 3 : 6;
 }
 
 hipError_t launch_posterior(const PosteriorArgs &args, bool mfma, hipStream_t s) {
@@ -2397,23 +2400,34 @@ hipError_t launch_posterior(const PosteriorArgs &args, bool mfma, hipStream_t s)
     if (blocks <= 0) return hipSuccess;
     PosteriorArgs a = args;
     a.order = BlockOrder(cols, rows, a.split);
-    a.run_log2 = xcd_run_log2(a.n_frames, (size_t)a.n_supers * a.chunks_per_super * kChunkRecordBytes);
+    const size_t table = (size_t)a.n_supers * a.chunks_per_super * kChunkRecordBytes;
+    a.run_log2 = xcd_run_log2(a.n_frames, table);
     if (mfma) {
         // Tiles that would all be resident at once with one wave each: the
         // launch would last as long as its busiest tile (2.3 times the mean on
-        // 1080p frames); four waves a tile share that out, in a workgroup of
+        // 1080p frames).  Few of them take four waves each, in a workgroup of
         // their own so that few regions still reach every CU (the region is
         // then ranked by each of its four tiles' workgroups).  One 640x480
         // frame (600 tiles, 256 x 256 grid): 155 us a call with one wave per
-        // tile and four tiles per workgroup, 72 this way; one 1080p frame (4080
-        // tiles) 193 and 183.  More tiles keep the chip full by themselves, and
-        // the waves of a tile repeat its set-up: 9600 tiles (128 x 128 grid)
-        // 165 and 187 us, 20480 tiles 256 and 343.
-        if (blocks * kRegionTiles <= kResidentWaves) {
+        // tile and four tiles per workgroup, 72 this way.  With more of them
+        // what the waves of a tile repeat weighs more than balance, and two
+        // waves a tile in a region's workgroup are faster: us a call with four
+        // and with two waves, one 1080p frame (4080 tiles) 181 and 175.5, on a
+        // 128 x 128 grid 97 and 87, 5904 tiles 242 and 227; but 3800 tiles 171
+        // and 172, 2560 tiles 131 and 139.  Small super-tiles repeat more per
+        // chunk and change over earlier (2560 tiles on a 128 x 128 grid 72.2 and
+        // 68.4, 3200 on 96 x 96 50.1 and 48.4), large tables never do (4080
+        // tiles on 384 x 384 319 and 334).  Past the residents one wave a tile:
+        // 7680 tiles 303 and 305.5 with two, 9600 (128 x 128 grid) 159 and 168.
+        const long long tiles = blocks * kRegionTiles;
+        const long long pairs_from = a.chunks_per_super <= 16 ? 2048 : 4000;
+        if (tiles > kResidentWaves) {
+            launch_mfma<1, kRegionTiles>(a, blocks, s);
+        } else if (tiles > pairs_from && table <= kTableNearL2) {
+            launch_mfma<2, kRegionTiles>(a, blocks, s);
+        } else {
             if (a.run_log2) a.run_log2 += 2;   // four workgroups a region
             launch_mfma<4, 1>(a, blocks, s);
-        } else {
-            launch_mfma<1, kRegionTiles>(a, blocks, s);
         }
     } else if (a.precise) {
         hipLaunchKernelGGL(k_posterior_direct<true>, dim3((unsigned)blocks), dim3(kBlockThreads), 0, s, a);

@@ -581,11 +581,13 @@ def test_every_block_of_the_frame_order(torch_cuda, w, h, grid, split, kernel):
     run.close()
 
 
-@pytest.mark.parametrize("w,h,grid", [(260, 250, 72), (520, 402, 72), (520, 402, 384), (800, 780, 20)])
+@pytest.mark.parametrize("w,h,grid", [
+    (260, 250, 72), (400, 390, 72), (520, 402, 72), (260, 250, 384), (520, 402, 384), (800, 780, 20)])
 def test_runs_of_blocks_cover_the_frame(torch_cuda, w, h, grid):
     """Launches with more workgroups than are resident at once deal runs of 8
-    or (tables above 8 MB) 64 blocks to the XCDs, the rest in plain order:
-    every block's maps are those of the same block in a launch of its own."""
+    or (tables above 8 MB) 64 blocks to the XCDs, the rest in plain order, and
+    take one, two or four waves a tile: every block's maps are those of the
+    same block in a launch of its own (four waves a tile, plain order)."""
     s = _settings(levels=0, grid=grid)
     frames = synth.single_frame(h, w, config=92)[0][None]
     whole = hbtest.GpuRun(w, h, s, grid_split=1)
