@@ -1917,7 +1917,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
         vhi = vlo;
         vlo = fmaxf(nskip, vlo - kDepthStep);
     }
-    tile_sync<NW>();
+    tile_sync<1>();   // several waves: the passes end with a barrier behind the last sums
     float S0 = sh.total[0][px] + sh.total[3][px];
     const float m = (px < 16 ? am[0] : am[1]);
 
@@ -1938,6 +1938,9 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
     const bool valid = base + px_e < n_valid;
     const int pixel = rsh.slot[valid ? base + px_e : 0];
     unsigned long long far = __builtin_amdgcn_ballot_w64(lane_e < 32 && valid && m + __log2f(S0) < -a.far_rho2);
+    // Every wave of the tile has formed its mask from the passes' sums before
+    // one of them replaces a pixel's: the waves then deal the same pixels.
+    tile_sync<NW>();
     if (__builtin_expect(far != 0, 0)) {
         // The pass reads the kernel's arguments again from the argument segment
         // (PosteriorArgs is the kernel's only argument): keeping the values it

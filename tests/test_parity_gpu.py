@@ -222,6 +222,31 @@ def test_far_observations_in_small_and_large_launches(torch_cuda):
     print("far pixels", far1, far8)
 
 
+def test_far_observations_around_the_room(torch_cuda):
+    """The waves of a tile share out its far pixels by a mask that each forms
+    from the tile's sums, which the pass then replaces: with observations
+    spread over both sides of the room (the green channel dimmed by a ramp)
+    the same pixels take the pass, and every map has the same bits, whether
+    one, two or four waves share a tile (13, 10 and 1 frames a call)."""
+    frames = []
+    for i in range(13):
+        fr = synth.single_frame(128, 128, config=64, stream=60 + i)[0].copy()
+        fr[:, :, 1] *= np.linspace(0.85, 1.0, 128, dtype=fr.dtype)[None, :]
+        frames.append(fr)
+    frames = np.stack(frames)
+    run = hbtest.GpuRun(128, 128, _settings(levels=0, grid=256, sigma=0.005), max_batch=13)
+    alone = [_far_run(run, frames[k:k + 1]) for k in range(13)]
+    counts = [c for _, c in alone]
+    print("far pixels", counts)
+    assert all(0.05 * 128 * 128 < c < 0.95 * 128 * 128 for c in counts), counts
+    for n in (10, 13):
+        maps, far = _far_run(run, frames[:n])
+        assert far == sum(counts[:n]), (n, far, counts[:n])
+        for k in range(n):
+            assert np.array_equal(maps[k], alone[k][0][0], equal_nan=True), (n, k)
+    run.close()
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_half_storage_matches_oracle_on_quantised_input(torch_cuda, dtype):
     w = synth.config1(dtype)
