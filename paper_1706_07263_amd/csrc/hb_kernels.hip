@@ -1929,15 +1929,18 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
     // = -(m + log2 S0), at most the nearest node's; with a split grid, also
     // that of the best probe of the whole grid (-gref): a split whose nodes
     // all lie far from an observation that lies close to others carries a
-    // negligible part of the posterior.  The tile's waves take the pixels in
-    // turn.
+    // negligible part of the posterior.  A pixel without a finite logit (a NaN
+    // or infinite observation) gets NaN maps from its sums as they are: where a
+    // tile holds nothing else they are all zero, which is no distance.  The
+    // tile's waves take the pixels in turn.
     unsigned far_pixels = 0;
     // Lane indices for what follows, formed here again rather than kept
     // across the main loop.
     const int lane_e = opaque_v((int)threadIdx.x) & 63, px_e = lane_e & 31;
     const bool valid = base + px_e < n_valid;
     const int pixel = rsh.slot[valid ? base + px_e : 0];
-    unsigned long long far = __builtin_amdgcn_ballot_w64(lane_e < 32 && valid && m + __log2f(S0) < -a.far_rho2);
+    unsigned long long far =
+        __builtin_amdgcn_ballot_w64(lane_e < 32 && valid && m > -INFINITY && m + __log2f(S0) < -a.far_rho2);
     // Every wave of the tile has formed its mask from the passes' sums before
     // one of them replaces a pixel's: the waves then deal the same pixels.
     tile_sync<NW>();
@@ -2188,7 +2191,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5
             // differences round at the scale of that distance, so their sums are
             // formed again with double-float logits, as in the MFMA kernel (the
             // plan sets far_rho2 from this kernel's precision budget).
-            unsigned long long far = __ballot(valid && m + __log2f(R0) < -a.far_rho2);
+            unsigned long long far = __ballot(valid && m > -INFINITY && m + __log2f(R0) < -a.far_rho2);
             unsigned far_pixels = 0;
             while (__builtin_expect(far != 0, 0)) {
                 const int q = __builtin_ctzll(far);   // the pixel of lane q

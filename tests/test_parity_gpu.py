@@ -807,6 +807,25 @@ def test_nan_pixels_do_not_switch_skipping_off(torch_cuda):
     run.close()
 
 
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("grid,kernel,split", [(256, "mfma", 1), (256, "mfma", 3), (24, "direct", 1), (24, "direct", 3)])
+def test_pixels_without_an_observation_take_no_far_pass(torch_cuda, value, grid, kernel, split):
+    """A NaN or infinite pixel has no distance to the nodes: scattered ones
+    (gathered into tiles of their own by rank) and a region of them give NaN
+    maps without the double-float pass of far observations, which no other
+    pixel of the frame takes."""
+    fr = synth.single_frame(64, 96, config=64)[0].copy()
+    rng = np.random.default_rng(4)
+    bad = rng.random((64, 96)) < 0.3
+    bad[:, :32] = True
+    fr[bad, rng.integers(0, 3, bad.sum())] = value
+    run = hbtest.GpuRun(96, 64, _settings(levels=0, grid=grid), grid_split=split)
+    room = run.plan.info()["far_room"]
+    maps, far = _far_run(run, fr[None], kernel, room)
+    run.close()
+    assert np.array_equal(np.isnan(maps[0, 0]), bad) and far == 0
+
+
 @pytest.mark.parametrize("gt,gs", [(4096, 3), (3, 4096), (1024, 1024), (1, 4096)])
 def test_maximum_grid_sizes(torch_cuda, gt, gs):
     """Grids at the largest extent the plan accepts along an axis (4096
