@@ -1090,19 +1090,22 @@ __global__ __launch_bounds__(kBlockThreads) void k_reference(PosteriorArgs a) {
 // chunk_test(si, c) are the bounds of the main loop's own tests (one
 // super-tile or chunk per lane): a chunk that the loop evaluates but this scan
 // leaves out could hold weights that overflow relative to the result.
-// Returns max(current, that maximum).
-template <int PW, int LPP, typename SuperTest, typename ChunkTest>
+// The NW waves of a tile take the super-tiles in turn.  Returns the maximum of
+// cur and of the wave's share.
+template <int PW, int LPP, int NW, typename SuperTest, typename ChunkTest>
 __device__ float far_gap_max(const PosteriorArgs &a, const WaveWork &w, const float ph[3], const float pl[3],
-                             int part, SuperTest super_test, ChunkTest chunk_test, float mmin, float cur) {
+                             int part, int wave, SuperTest super_test, ChunkTest chunk_test, float mmin, float cur) {
     const int lane = threadIdx.x & 63;
     const float nskip = -a.skip_log2;
     float mx = cur;
+    int turn = 0;
     for (int g = w.s0; g < w.s1; g += 64) {
         const int sl = g + lane;
         unsigned long long smask = __ballot(sl < w.s1 && super_test(sl) - mmin > nskip);
         while (smask) {
             const int si = g + __builtin_ctzll(smask);
             smask &= smask - 1;
+            if (NW > 1 && turn++ % NW != wave) continue;
             const float *__restrict__ T = a.supers + (size_t)si * a.super_stride;
             float r[3];
             recentre(T, ph, pl, r);
@@ -1431,6 +1434,7 @@ struct TileShared {
     // several waves: sums of the segments, best probes, skipped weights
     float part[NW > 1 ? kSegments : 1][6][kTilePixels];
     float best[NW][kTilePixels];
+    float top[NW][kTilePixels];    // each wave's share of far_gap_max
     unsigned mass[NW];
 };
 
@@ -1699,8 +1703,12 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
     // If some weight could exceed 2^kFarGap relative to the best probe, take
     // the exact maximum over the nodes of the chunks that will be kept (the
     // only weights evaluated); a split far from the posterior usually keeps
-    // none, and then the reference needs no refinement.
-    if (__any(!(mup - am[0] <= kFarGap) || !(mup - am[1] <= kFarGap))) {
+    // none, and then the reference needs no refinement.  Several waves share
+    // the scan and put their maxima together behind the first barrier below
+    // (each scanning it all, a 1920x1080 frame of random intensities, whose
+    // tiles spread over the whole grid, took 11.9 ms with two waves a tile; 7.7).
+    bool refine = active && __any(!(mup - am[0] <= kFarGap) || !(mup - am[1] <= kFarGap));
+    if (refine) {
         const int i = px < 16 ? ib[0] : ib[1];
         float ph[3], pl[3];
 #pragma unroll
@@ -1711,10 +1719,14 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
         auto chunk_test = [&](int si, int c) {
             return box_box_bound(a.boxes + ((size_t)si * a.chunks_per_super + c) * kBoxFloats, zbox);
         };
-        const float m = far_gap_max<kTilePixels, 2>(a, w, ph, pl, lane >> 5, super_bound, chunk_test, mmin,
-                                                    px < 16 ? am[0] : am[1]);
+        const float m = far_gap_max<kTilePixels, 2, NW>(a, w, ph, pl, lane >> 5, wave, super_bound, chunk_test, mmin,
+                                                        px < 16 ? am[0] : am[1]);
+        if constexpr (NW > 1) {
+            if (lane < 32) sh.top[wave][lane] = m;
+        } else {
 #pragma unroll
-        for (int b = 0; b < PB; ++b) am[b] = __shfl(m, b * 16 + lp);
+            for (int b = 0; b < PB; ++b) am[b] = __shfl(m, b * 16 + lp);
+        }
     }
     // Anchor of the moments, for the whole tile: the centre of the super-tile
     // with the highest bound.
@@ -1754,6 +1766,13 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
             const int K = active ? list_chunks<NW>(a, w, sh.kept, sh.bound, wave, zbox, test, g, mass) : 0;
             if (NW == 1 && K == 0) break;
             tile_sync<NW>();
+            if (NW > 1 && refine) {
+#pragma unroll
+                for (int q = 0; q < NW; ++q)
+#pragma unroll
+                    for (int b = 0; b < PB; ++b) am[b] = fmaxf(am[b], sh.top[q][16 * b + lp]);
+                refine = false;
+            }
             // Segments in turn (which wave sums a segment changes no bit).
             const KeptSuper own = sh.kept[lane];
             for (int seg = wave; seg < kSegments; seg += NW) {
@@ -2092,7 +2111,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5
         float mmin = m;
         if (a.gref) mmin = fmaxf(mmin, a.gref[(size_t)w.f * a.LL + p]);
         mmin = wave_reduce<false>(mmin > -INFINITY ? mmin : INFINITY);   // NaN observation: see the MFMA kernel
-        if (__any(!(mup - m <= kFarGap))) m = far_gap_max<64, 1>(a, w, ph, pl, 0, super_bound, chunk_bound, mmin, m);
+        if (__any(!(mup - m <= kFarGap))) m = far_gap_max<64, 1, 1>(a, w, ph, pl, 0, 0, super_bound, chunk_bound, mmin, m);
         const float nm = -m;
 
         float R0 = 0.f, R1 = 0.f, R2 = 0.f, K0 = 0.f, K1 = 0.f, K2 = 0.f;

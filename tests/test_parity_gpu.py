@@ -807,6 +807,26 @@ def test_nan_pixels_do_not_switch_skipping_off(torch_cuda):
     run.close()
 
 
+def test_tiles_spread_over_the_grid(torch_cuda):
+    """Frames of random intensities: a tile's observations spread over the
+    whole grid and beyond it, its best probes lie far below the bound of its
+    box, and the exact maximum over the nodes, which the waves of a tile
+    share, becomes the reference.  The same bits with one, two and four waves
+    a tile (13, 10 and 1 frames a call)."""
+    rng = np.random.default_rng(5)
+    frames = (rng.random((13, 128, 128, 3)) * 1.5).astype(np.float32)
+    s = _settings(levels=0, grid=128)
+    run = hbtest.GpuRun(128, 128, s, max_batch=13)
+    assert run.plan.info()["posterior_kernel"] == "mfma"
+    every = run(frames)
+    two = run(frames[:10])
+    assert np.array_equal(two, every[:10], equal_nan=True)
+    for k in (0, 12):
+        assert np.array_equal(run(frames[k:k + 1])[0], every[k], equal_nan=True), k
+    assert np.all(np.isfinite(every[:, :3]))
+    run.close()
+
+
 @pytest.mark.parametrize("value", [np.nan, np.inf])
 @pytest.mark.parametrize("grid,kernel,split", [(256, "mfma", 1), (256, "mfma", 3), (24, "direct", 1), (24, "direct", 3)])
 def test_pixels_without_an_observation_take_no_far_pass(torch_cuda, value, grid, kernel, split):
