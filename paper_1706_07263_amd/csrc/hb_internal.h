@@ -150,7 +150,14 @@ constexpr float kBandLog2 = 6.0f;
 // chunks' depth (their bound counts for all of their nodes).
 constexpr float kDepthStep = 4.0f;
 constexpr float kSuperMargin = 12.0f;
-constexpr float kMassLog2 = 42.0f;     // unit of the skipped weight: 2^-42
+// Unit of the skipped weight, in log2 below the first depth.  Every skipped
+// bound lies below that depth: a chunk counts at most 2^16 + 1 units, so that a
+// 32-bit sum holds all the 2^14 chunks of a 512 x 512 grid at their largest and
+// larger grids unless the very most of their chunks lie just at the depth (the
+// count then saturates and certifies nothing).  Rounding up to whole units adds
+// 2^-12 of a node's weight at that depth per chunk, under a hundredth of what
+// the kept weight allows at any node density and tolerance.
+constexpr float kMassDepthLog2 = 12.0f;
 constexpr float kChunkNodesLog2 = 4.0f;
 struct SkipRule {
     float skip_log2 = kExactSkipLog2, band_log2 = kExactSkipLog2;
@@ -309,6 +316,7 @@ struct PosteriorArgs {
     float skip_log2;         // chunks bounded more than this below the reference are skipped
     float depth0;            // depth of the first pass (skip_log2: the only one)
     float cert_log2;         // largest certified log2 of skipped over kept weight
+    float mass_log2;         // the skipped weight is counted in units of 2^-mass_log2
     float *gref;             // [n][LL] best probe logit over the whole grid, or null (one split)
     float *part;             // [n][split][kPartFields][LL]
     float axes[9];           // axes and tables of the skip tests (see kHdrFloats)

@@ -1004,10 +1004,17 @@ __device__ __forceinline__ float box_box_bound(const float *box, const float r[6
     return -fmaf(e0, e0, fmaf(e1, e1, e2 * e2));
 }
 
-// Skipped weight of a node whose logit lies at most v above the wave's
-// reference, rounded up, in units of 2^-kMassLog2.
-__device__ __forceinline__ unsigned mass_units(float v) {
-    return (unsigned)__builtin_amdgcn_exp2f(fminf(v + (kMassLog2 + kChunkNodesLog2), 31.0f)) + 1u;
+// Skipped weight of a chunk whose logits lie at most v above the wave's
+// reference, rounded up, in units of 2^-mass_log2.  What is skipped lies below
+// the first depth: at most 2^(kMassDepthLog2 + kChunkNodesLog2) + 1 units.
+__device__ __forceinline__ unsigned mass_units(float v, float mass_log2) {
+    constexpr float kMost = kMassDepthLog2 + kChunkNodesLog2;
+    return (unsigned)__builtin_amdgcn_exp2f(fminf(v + (mass_log2 + kChunkNodesLog2), kMost)) + 1u;
+}
+// Whether the skipped weight `mass` (relative to mmin) is too large for a pixel
+// whose sums hold 2^held; a count that has saturated is no bound.
+__device__ __forceinline__ bool certificate_fails(const PosteriorArgs &a, unsigned mass, float held, float mmin) {
+    return mass == ~0u || __log2f((float)mass) - a.mass_log2 > a.cert_log2 + (held - mmin);
 }
 
 // Widening of the wave's observation box for rounding (scaled units).
@@ -1398,7 +1405,7 @@ __device__ __forceinline__ int list_chunks(const PosteriorArgs &a, const WaveWor
         // the list holds 64; exact and no skipping take the same windows
         if (K + n > 64 || (K > 0 && !a.list_across)) break;
         if (!t.last && (NW == 1 || wave == 0) && sl < w.s1 && !(sv > t.svlo))
-            mass = __builtin_elementwise_add_sat(mass, mass_units(sv) * (unsigned)cps);
+            mass = __builtin_elementwise_add_sat(mass, mass_units(sv, a.mass_log2) * (unsigned)cps);
         const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(smask >> 32),
                                                    __builtin_amdgcn_mbcnt_lo((unsigned)smask, 0));
         if (sv > t.svlo) {   // every wave writes the same values
@@ -1416,7 +1423,7 @@ __device__ __forceinline__ int list_chunks(const PosteriorArgs &a, const WaveWor
         const int si = kept[real ? k : 0].si;
         const float v = box_box_bound(a.boxes + ((size_t)si * cps + ci) * kBoxFloats, zbox) - t.mmin;
         const unsigned long long in = __builtin_amdgcn_ballot_w64(real && v > t.vlo && v <= t.vhi);
-        if (!t.last) mass = __builtin_elementwise_add_sat(mass, real && !(v > t.vlo) ? mass_units(v) : 0u);
+        if (!t.last) mass = __builtin_elementwise_add_sat(mass, real && !(v > t.vlo) ? mass_units(v, a.mass_log2) : 0u);
         if (real && ci == 0) {
             const unsigned long long bits = in >> (sub * cps) & chunk_bits;
             kept[k].lo = (unsigned)bits;
@@ -1759,7 +1766,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
     for (;;) {
         const bool last = !(vlo > nskip);
         const float svlo = fmaxf(nskip, vlo - kSuperMargin);
-        unsigned mass = 0;   // this lane's share of the skipped weight (saturating), 2^-kMassLog2 per chunk
+        unsigned mass = 0;   // this lane's share of the skipped weight (saturating), in units of 2^-mass_log2
         int g = w.s0;
         for (bool more = true; more;) {
             const ChunkTest test{vlo, vhi, svlo, mmin, last};
@@ -1908,7 +1915,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
         }
         bool fails = false;
         if (active && !last) {
-            // Certificate: the skipped weight, at most 2^skipped relative to mmin for
+            // Certificate: the skipped weight, which is at most `mass` relative to mmin for
             // every pixel of the tile, against the pixel's sum.  A NaN sum certifies
             // itself: its maps are NaN whatever is kept.
 #pragma unroll
@@ -1923,9 +1930,8 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
             for (int q = 1; q < NW; ++q) mass = __builtin_elementwise_add_sat(mass, sh.mass[q]);
         }
         if (active && !last) {
-            const float skipped = __log2f((float)mass) - kMassLog2;
             const float held = (px < 16 ? am[0] : am[1]) + __log2f(sh.total[0][px] + sh.total[3][px]);
-            fails = __any(skipped > a.cert_log2 + (held - mmin));
+            fails = __any(certificate_fails(a, mass, held, mmin));
         }
         active = fails;
         if constexpr (NW > 1) {
@@ -2199,8 +2205,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5
 #pragma unroll
             for (int o = 32; o >= 1; o >>= 1)
                 mass = __builtin_elementwise_add_sat(mass, (unsigned)__shfl_xor((int)mass, o));
-            const float skipped = __log2f((float)mass) - kMassLog2;
-            if (!__any(skipped > a.cert_log2 + ((m + __log2f(R0)) - mmin))) break;
+            if (!__any(certificate_fails(a, mass, m + __log2f(R0), mmin))) break;
             vhi = vlo;
             vlo = fmaxf(nskip, vlo - kDepthStep);
         }

@@ -771,6 +771,7 @@ hb_status_t estimate(hb_plan_s *p, const void *d_frames, int32_t n_frames, const
         pa.skip_log2 = p->skip_log2;
         pa.depth0 = p->depth0;
         pa.cert_log2 = p->cert_log2;
+        pa.mass_log2 = p->depth0 + kMassDepthLog2;
         pa.part = cb.part;
         pa.lo = p->d_lo;
         pa.precise = p->precise ? 1 : 0;
