@@ -212,6 +212,11 @@ constexpr int kBoxFloats = 8;
 inline int probe_shift(int side) { return side <= 8 ? 0 : (side <= 16 ? 2 : 4); }
 inline int probe_slots(int side) { return 1 << probe_shift(side); }   // ceil(side / 8)^2 and more
 
+// A tile whose observations' extent stands for at most this share of thb_max by
+// the linear estimate sums its moments about one anchor in plain float32
+// (an error of about 2^-25 of the distance from the anchor).
+constexpr double kNarrowTile = 0.25;
+
 // LL pixels of one tile of the MFMA kernel (two MFMA blocks of 16).
 // Each chunk's 1 KB split operand is loaded once and used for both blocks;
 // larger tiles would share it further but keep more chunks.
@@ -319,6 +324,8 @@ struct PosteriorArgs {
     float mass_log2;         // the skipped weight is counted in units of 2^-mass_log2
     float *gref;             // [n][LL] best probe logit over the whole grid, or null (one split)
     float *part;             // [n][split][kPartFields][LL]
+    float spread[2];         // MFMA kernel: extents along the boxes' second and third axis, per unit of
+                             // which the linear estimate moves by one kNarrowTile
     float axes[9];           // axes and tables of the skip tests (see kHdrFloats)
     const float *headers;
     const float *boxes;

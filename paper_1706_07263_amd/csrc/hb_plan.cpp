@@ -63,6 +63,7 @@ struct hb_plan_s {
     hb_plan_info_t info{};
     float iref[3] = {1, 1, 1};
     float axes[9] = {1, 0, 0, 0, 1, 0, 0, 0, 1};
+    float spread[2] = {0, 0};   // of a tile's observations (PosteriorArgs)
     float scale = 1.0f;
     float skip_log2 = kExactSkipLog2;
     float depth0 = kExactSkipLog2;      // = skip_log2 when nothing is certified
@@ -303,6 +304,9 @@ double build_supers(const hb_plan_desc_t &d, const ForwardModel &fm, const doubl
     table.assign((size_t)n_sup * stride, 0.0f);
     lo.assign((size_t)n_sup * cps * cps * kLoFloats, 0.0f);
     std::vector<double> radius(n_sup, 0.0), index(n_sup, 0.0);
+    // Centres on the multiples of thb_max's last bit: their differences are exact.
+    const double quantum = d.thb_max > 0 ? std::ldexp(1.0, std::ilogb((float)d.thb_max) - 23) : 0.0;
+    auto on_quantum = [&](double x) { return (float)(quantum > 0 ? std::round(x / quantum) * quantum : x); };
     auto work = [&](int s_begin, int s_end) {
         std::vector<double> mu((size_t)side * side * 3), chb((size_t)side * side), cox((size_t)side * side);
         std::vector<char> real((size_t)side * side);
@@ -346,7 +350,7 @@ double build_supers(const hb_plan_desc_t &d, const ForwardModel &fm, const doubl
                 cen_lo[k] = (float)(c - (double)cen_hi[k]);
                 cen_d[k] = (double)cen_hi[k] + (double)cen_lo[k];
             }
-            const float chb_c = (float)(mhb / nreal), cox_c = (float)(mox / nreal);
+            const float chb_c = on_quantum(mhb / nreal), cox_c = on_quantum(mox / nreal);
             auto rel = [&](int n, int k) { return mu[3 * n + k] - cen_d[k]; };
             // neighbouring nodes inside the super-tile (both grid directions)
             for (int i = 0; i < side; ++i)
@@ -758,6 +762,7 @@ hb_status_t estimate(hb_plan_s *p, const void *d_frames, int32_t n_frames, const
         pa.super_stride = super_floats(p->side);
         pa.chunks_per_super = (p->side / 4) * (p->side / 4);
         for (int k = 0; k < 9; ++k) pa.axes[k] = p->axes[k];
+        for (int k = 0; k < 2; ++k) pa.spread[k] = p->spread[k];
         pa.headers = p->d_tests;
         pa.boxes = p->d_tests + p->boxes_at;
         pa.probes = p->d_probes;
@@ -1068,6 +1073,15 @@ hb_status_t hb_set_forward_model(hb_plan_t p, const hb_forward_model_t *fm) {
     std::vector<uint16_t> probes, split_ops;
     build_split_ops(tiles, p->n_tiles, p->side, split_ops, kChunkRecordBytes);
     principal_axes(tiles, p->n_tiles, p->side, p->axes);
+    for (int r = 1; r < 3; ++r) {
+        double most = 0.0;   // uM per scaled unit along the axis
+        for (int i = 0; i < 2; ++i) {
+            double g = 0.0;
+            for (int k = 0; k < 3; ++k) g += k0_out[6 + 3 * i + k] * (double)p->axes[3 * r + k];
+            most = std::max(most, std::fabs(g) / (double)p->scale);
+        }
+        p->spread[r - 1] = (float)(most / (kNarrowTile * std::max(d.thb_max, 1e-30)));
+    }
     build_test_tables(tiles, p->n_tiles, (d.grid_so2 + p->side - 1) / p->side, p->side, p->boxes_at, p->axes, tests,
                       probes);
     if (hipMemcpy(p->d_tests, tests.data(), sizeof(float) * tests.size(), hipMemcpyHostToDevice) != hipSuccess ||

@@ -827,6 +827,27 @@ def test_tiles_spread_over_the_grid(torch_cuda):
     run.close()
 
 
+@pytest.mark.parametrize("grid,split", [(128, 1), (256, 1), (128, 3)])
+def test_wide_tiles_round_like_narrow_ones(torch_cuda, grid, split):
+    """Random intensities: the estimates of a tile lie up to the width of the
+    grid from its one anchor.  The sums must not round at that distance: all
+    but one pixel in a hundred (whose posterior lies between distant nodes,
+    where the observation's own rounding shows) come within one and a half
+    times the error of rounding the oracle's maps to float32, twice that with
+    a split (whose partial moments are merged once more)."""
+    fr = (np.random.default_rng(6).random((64, 64, 3)) * 1.5).astype(np.float32)
+    s = _settings(levels=0, grid=grid)
+    run = hbtest.GpuRun(64, 64, s, grid_split=split)
+    assert run.plan.info()["posterior_kernel"] == "mfma"
+    gpu = run(fr[None])[0, :2].astype(np.float64)
+    run.close()
+    ora = hbtest.run_oracle(fr[None], "f32", s)[0, :2]
+    rounding = np.quantile(np.abs(ora.astype(np.float32) - ora), 0.99)
+    err = np.quantile(np.abs(gpu - ora), 0.99)
+    print(f"grid {grid} split {split}: 99% of the errors below {err:.2e}, of the roundings {rounding:.2e}")
+    assert err <= (1.5 if split == 1 else 3.0) * rounding
+
+
 @pytest.mark.parametrize("value", [np.nan, np.inf])
 @pytest.mark.parametrize("grid,kernel,split", [(256, "mfma", 1), (256, "mfma", 3), (24, "direct", 1), (24, "direct", 3)])
 def test_pixels_without_an_observation_take_no_far_pass(torch_cuda, value, grid, kernel, split):
