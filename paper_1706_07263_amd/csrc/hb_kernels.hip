@@ -1152,14 +1152,15 @@ __device__ float far_gap_max(const PosteriorArgs &a, const WaveWork &w, const fl
 
 // Fused recomposition for one split and n <= 3, in units of V pixels along a
 // row, from the estimates of the region's pixels: the maps of the whole region
-// of RW x RH LL pixels, or (LIST) those of `count` listed ones.
+// of RW x RH LL pixels, or (LIST) those of `count` listed ones, by thread `thread`
+// of `threads`.
 template <int RW, int RH, bool LIST, int V>
-__device__ __forceinline__ void fused_maps(const PosteriorArgs &a, const WaveWork &w, const float2 *est,
-                                           const int *list, int count) {
+__device__ __forceinline__ void fused_maps(const PosteriorArgs &a, const WaveWork &w, const float2 *est, int thread,
+                                           int threads, const int *list, int count) {
     constexpr int kLogV = V == 4 ? 2 : (V == 2 ? 1 : 0);
     const int n = a.levels, B = 1 << n;
     const int n_units = ((LIST ? count : RW * RH) << 2 * n) >> kLogV;
-    for (int u = threadIdx.x; u < n_units; u += blockDim.x) {
+    for (int u = thread; u < n_units; u += threads) {
         int i, y, x;   // pixel of the region, offset in its block
         if constexpr (LIST) {
             const int o = u & ((1 << (2 * n - kLogV)) - 1);
@@ -1183,12 +1184,12 @@ __device__ __forceinline__ void fused_maps(const PosteriorArgs &a, const WaveWor
     }
 }
 template <int RW, int RH, bool LIST>
-__device__ __forceinline__ void fused_maps(const PosteriorArgs &a, const WaveWork &w, const float2 *est,
-                                           const int *list = nullptr, int count = 0) {
+__device__ __forceinline__ void fused_maps(const PosteriorArgs &a, const WaveWork &w, const float2 *est, int thread,
+                                           int threads, const int *list = nullptr, int count = 0) {
     switch (a.vec) {
-        case 4: fused_maps<RW, RH, LIST, 4>(a, w, est, list, count); break;
-        case 2: fused_maps<RW, RH, LIST, 2>(a, w, est, list, count); break;
-        default: fused_maps<RW, RH, LIST, 1>(a, w, est, list, count); break;
+        case 4: fused_maps<RW, RH, LIST, 4>(a, w, est, thread, threads, list, count); break;
+        case 2: fused_maps<RW, RH, LIST, 2>(a, w, est, thread, threads, list, count); break;
+        default: fused_maps<RW, RH, LIST, 1>(a, w, est, thread, threads, list, count); break;
     }
 }
 
@@ -1455,9 +1456,9 @@ struct TileShared {
     float bound[64];               // of the split's first 64 super-tiles
     float total[6][kTilePixels];   // S0, S1, S2 and their compensation, per pixel
     // several waves: sums of the segments, best probes, skipped weights
-    float part[NW > 1 ? kSegments : 1][6][kTilePixels];
-    float best[NW][kTilePixels];
-    float top[NW][kTilePixels];    // each wave's share of far_gap_max
+    float part[NW > 1 ? kSegments : 1][6][NW > 1 ? kTilePixels : 1];
+    float best[NW][NW > 1 ? kTilePixels : 1];
+    float top[NW][NW > 1 ? kTilePixels : 1];   // each wave's share of far_gap_max
     unsigned mass[NW];
 };
 
@@ -1503,10 +1504,18 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
     // threads share the comparisons.
     const int rows = min(kRegionH, a.hl - w.r0), cols = min(kRegionW, a.wl - w.c0);
     const int n_valid = rows * cols;
+    // A region of one tile (small low-pass bands) has nothing to rank: its pixels
+    // in order, by the tile's own waves.  Waves that end here or below are not
+    // counted by the workgroup's later barriers.  While they stayed, three
+    // quarters of the waves of 4096 frames of 8 x 4 pixels idled: 163 us a call.
+    const bool single = n_valid <= kTilePixels;
+    if (single && tile > 0 && (RT == 1 || NW == 1)) return;
     {
-        const int i = threadIdx.x % kRegionPixels, part = threadIdx.x / kRegionPixels;
+        int i = threadIdx.x % kRegionPixels;
+        const int part = threadIdx.x / kRegionPixels;
         constexpr int kParts = 64 * NW * RT / kRegionPixels, kKeys = kRegionPixels / kParts;
-        if (part == 0) {
+        if (single) i = i / cols * kRegionW + i % cols;
+        if (single ? (int)threadIdx.x < n_valid : part == 0) {
             const int r = i / kRegionW, c = i % kRegionW;
             const bool inside = r < rows && c < cols;
             const long long p = (long long)(w.r0 + min(r, rows - 1)) * a.wl + w.c0 + min(c, cols - 1);
@@ -1532,25 +1541,27 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
             const unsigned ordered = u & 0x80000000u ? ~u : u | 0x80000000u;
             rsh.key[i] = (inside ? ordered & ~127u : 0xffffff80u) | (unsigned)i;
             rsh.rank[i] = 0;
+            if (single) rsh.slot[threadIdx.x] = i;
         }
-        for (int t = threadIdx.x; t < 6 * kTilePixels * RT; t += 64 * NW * RT)
-            (&rsh.tile[t / (6 * kTilePixels)].total[0][0])[t % (6 * kTilePixels)] = 0.0f;
+        for (int t = 64 * wave + lane; t < 6 * kTilePixels; t += 64 * NW) (&sh.total[0][0])[t] = 0.0f;
         if (threadIdx.x < 3) rsh.more[threadIdx.x] = 0;
         __syncthreads();
-        const unsigned own = rsh.key[i];
-        int rank = 0;
+        if (!single) {
+            const unsigned own = rsh.key[i];
+            int rank = 0;
 #pragma unroll 4
-        for (int t = 0; t < kKeys; ++t) rank += rsh.key[part * kKeys + t] < own ? 1 : 0;
-        atomicAdd(&rsh.rank[i], rank);
-        __syncthreads();
-        if (part == 0) rsh.slot[rsh.rank[i]] = i;
-        __syncthreads();
+            for (int t = 0; t < kKeys; ++t) rank += rsh.key[part * kKeys + t] < own ? 1 : 0;
+            atomicAdd(&rsh.rank[i], rank);
+            __syncthreads();
+            if (part == 0) rsh.slot[rsh.rank[i]] = i;
+            __syncthreads();
+        }
     }
     // A tile past the frame's pixels has nothing to do; a partial one repeats
     // its first pixel.
     const int base = tile * kTilePixels;
     bool active = base < n_valid;
-    if (RT == 1 && !active) return;
+    if ((RT == 1 || NW == 1) && !active) return;
     int ib[PB];   // region pixel b*16 + lp of the tile
     float ah[PB], al[PB];   // lane (lp, lk) holds its coordinate lk (lk == 3 repeats coordinate 0)
 #pragma unroll
@@ -1795,12 +1806,14 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
             const int K = active ? list_chunks<NW>(a, w, sh.kept, sh.bound, wave, zbox, test, g, mass) : 0;
             if (NW == 1 && K == 0) break;
             tile_sync<NW>();
-            if (NW > 1 && refine) {
+            if constexpr (NW > 1) {
+                if (refine) {
 #pragma unroll
-                for (int q = 0; q < NW; ++q)
+                    for (int q = 0; q < NW; ++q)
 #pragma unroll
-                    for (int b = 0; b < PB; ++b) am[b] = fmaxf(am[b], sh.top[q][16 * b + lp]);
-                refine = false;
+                        for (int b = 0; b < PB; ++b) am[b] = fmaxf(am[b], sh.top[q][16 * b + lp]);
+                    refine = false;
+                }
             }
             // Segments in turn (which wave sums a segment changes no bit).
             const KeptSuper own = sh.kept[lane];
@@ -2053,7 +2066,9 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
             a.est[(size_t)w.f * a.LL + pe] = rsh.est[pixel];
         }
         __syncthreads();
-        fused_maps<kRegionW, kRegionH, RT == 1>(a, w, rsh.est, rsh.slot + base, min(kTilePixels, n_valid - base));
+        const int live = NW == 1 ? 64 * min(RT, (n_valid + kTilePixels - 1) / kTilePixels) : 64 * NW * RT;
+        fused_maps<kRegionW, kRegionH, RT == 1>(a, w, rsh.est, threadIdx.x, live, rsh.slot + base,
+                                                min(kTilePixels, n_valid - base));
         return;
     }
     if (writer) {
@@ -2106,8 +2121,10 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5
     const int tr = (wave >> 1) * 8 + (lane >> 3), tc = (wave & 1) * 8 + (lane & 7);   // pixel of the region
     const bool valid = w.r0 + tr < a.hl && w.c0 + tc < a.wl;
     const long long p = (long long)min(w.r0 + tr, a.hl - 1) * a.wl + min(w.c0 + tc, a.wl - 1);
-    // A tile outside the frame has no pixel (but its wave helps with the maps).
-    if (w.r0 + (wave >> 1) * 8 < a.hl && w.c0 + (wave & 1) * 8 < a.wl) {
+    // The wave of a tile outside the frame has nothing to do (see the MFMA kernel).
+    const int wave_rows = w.r0 + 8 < a.hl ? 2 : 1, wave_cols = w.c0 + 8 < a.wl ? 2 : 1;
+    if ((wave >> 1) >= wave_rows || (wave & 1) >= wave_cols) return;
+    {
         const float *zf = a.z + (size_t)w.f * 6 * a.LL;
         float ph[3], pl[3];
 #pragma unroll
@@ -2312,7 +2329,8 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5
     }
     if (a.fuse) {
         __syncthreads();
-        fused_maps<kDirectSide, kDirectSide, false>(a, w, s_est);
+        const int thread = 64 * ((wave >> 1) * wave_cols + (wave & 1)) + lane;
+        fused_maps<kDirectSide, kDirectSide, false>(a, w, s_est, thread, 64 * wave_rows * wave_cols);
     }
 }
 

@@ -589,6 +589,33 @@ def test_ragged_regions_agree_in_small_and_large_launches(torch_cuda, h, w, leve
     hbtest.assert_maps_close(got[:, :, r:, c:], ora, f"{h}x{w} L{levels}")
 
 
+@pytest.mark.parametrize("w,h,levels,n", [(8, 4, 0, 1600), (1, 1, 0, 1600), (10, 6, 1, 1600), (16, 2, 0, 1600),
+                                          (20, 12, 0, 420), (33, 9, 0, 300)])
+@pytest.mark.parametrize("grid,kernel", [(72, "mfma"), (20, "direct")])
+def test_batches_of_small_bands(torch_cuda, w, h, levels, n, grid, kernel):
+    """Low-pass bands that fill one tile of a region, or leave some of its
+    tiles empty, in batches of more workgroups than are resident at once: the
+    waves of the empty tiles end early and the others write the maps.  A frame
+    gives the same bits alone (four waves a tile), and the maps match the
+    oracle."""
+    rng = np.random.default_rng(w * h)
+    some = np.stack([synth.noisy_frame(*synth.hb_hbo2(rng.uniform(60, 160) + rng.normal(0, 5, (h, w)),
+                                                      np.clip(rng.uniform(0.5, 0.9) + rng.normal(0, 0.01, (h, w)), 0, 1)),
+                                       synth.spectra(), 200 + i) for i in range(7)])
+    frames = np.concatenate([some] * (n // 7 + 1))[:n]
+    s = _settings(levels=levels, grid=grid)
+    run = hbtest.GpuRun(w, h, s, max_batch=n, grid_split=1)
+    assert run.plan.info()["posterior_kernel"] == kernel
+    every = run(frames)
+    for k in range(7):
+        alone = run(frames[k:k + 1])[0]
+        for j in (k, n // 7 * 7 - 7 + k):
+            assert np.array_equal(every[j], alone, equal_nan=True), j
+    assert np.array_equal(every[7:n // 7 * 7], np.concatenate([every[:7]] * (n // 7 - 1)), equal_nan=True)
+    run.close()
+    hbtest.assert_maps_close(every[:7], hbtest.run_oracle(some, "f32", s), f"{w}x{h} L{levels}")
+
+
 @pytest.mark.parametrize("w,h,grid,split,kernel", [
     (128, 64, 72, 1, "mfma"), (147, 73, 72, 1, "mfma"), (147, 73, 72, 3, "mfma"), (19, 131, 72, 1, "mfma"),
     (147, 147, 20, 1, "direct"), (128, 128, 20, 1, "direct"), (147, 147, 64, 2, None)])
