@@ -192,18 +192,21 @@ constexpr int kBlockThreads = 256;
 
 // Tables of the skip tests and of the MFMA kernel's probes, derived from the
 // super-tile table:
+//   origin   middle of the box of all nodes (float32 values): the tests' and the
+//            probes' coordinates are relative to it, since float32 rounds them,
+//            and the probes' expanded logits, at the scale of the distance from
+//            the origin, which mu_ref may lie any distance from the nodes
 //   axes     3 x 3 rotation (rows: unit vectors) along which the boxes lie:
 //            the principal directions of the differences between neighbouring
 //            nodes, the strongest last.  The nodes form a surface, so boxes
 //            along these axes are thin in one direction (kept chunks 3% fewer
 //            on 1080p frames than with boxes along the channels)
-//   headers  [super][kHdrFloats]: absolute box lower corner (3), upper corner
-//            (3) along the axes, Hb and HbO2 of the centre, centre high parts (3), low parts
+//   headers  [super][kHdrFloats]: box lower corner (3), upper corner (3) about
+//            the origin along the axes, Hb and HbO2 of the centre, centre high parts (3), low parts
 //            (3), segment (int bits)
-//   boxes    [chunk][kBoxFloats]: the chunk's absolute box along the axes,
-//            lower corner (3) and upper corner (3), rounded outward
-//   probes   split operands (as the chunks') of 16 probes each in absolute
-//            coordinates, probe_slots(side) per super-tile; slots without a
+//   boxes    [chunk][kBoxFloats]: the chunk's box about the origin along the
+//            axes, lower corner (3) and upper corner (3), rounded outward
+//   probes   split operands (as the chunks') of 16 probes each about the origin, probe_slots(side) per super-tile; slots without a
 //            probe have the logit kPadLogit
 // One lane tests one super-tile or chunk, and 64 consecutive entries are one
 // contiguous read.
@@ -326,7 +329,8 @@ struct PosteriorArgs {
     float *part;             // [n][split][kPartFields][LL]
     float spread[2];         // MFMA kernel: extents along the boxes' second and third axis, per unit of
                              // which the linear estimate moves by one kNarrowTile
-    float axes[9];           // axes and tables of the skip tests (see kHdrFloats)
+    float origin[3];         // origin, axes and tables of the skip tests (see kHdrFloats)
+    float axes[9];
     const float *headers;
     const float *boxes;
     const void *probes;

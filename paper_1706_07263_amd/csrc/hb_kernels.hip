@@ -1260,6 +1260,7 @@ __device__ __forceinline__ PosteriorArgs far_args(KernArgs *k) {
     f.headers = k->headers;
     f.boxes = k->boxes;
     for (int i = 0; i < 9; ++i) f.axes[i] = k->axes[i];
+    for (int i = 0; i < 3; ++i) f.origin[i] = k->origin[i];
     return f;
 }
 
@@ -1288,7 +1289,8 @@ __device__ __forceinline__ void far_pixel_sums(const PosteriorArgs &a, const Wav
     float zbox[6], far2 = 0.0f;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        zbox[k] = zbox[3 + k] = axis_coordinate(a.axes + 3 * k, qh[0] + ql[0], qh[1] + ql[1], qh[2] + ql[2]);
+        zbox[k] = zbox[3 + k] = axis_coordinate(a.axes + 3 * k, (qh[0] - a.origin[0]) + ql[0],
+                                                (qh[1] - a.origin[1]) + ql[1], (qh[2] - a.origin[2]) + ql[2]);
         far2 = fmaf(zbox[k], zbox[k], far2);
     }
     widen_box(zbox, far2);
@@ -1527,7 +1529,7 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
                 load_obs(zf, a.LL, p, k, a.scale, h, l);
                 rsh.obs[k][i] = h;
                 rsh.obs[3 + k][i] = l;
-                x[k] = h + l;
+                x[k] = (h - a.origin[k]) + l;
             }
             float q = 0.0f;
 #pragma unroll
@@ -1630,9 +1632,10 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
     // split's super-tiles.  The super-tile with the highest bound is probed
     // first, then those bounded above the tile's lowest best probe: the
     // result equals a scan of every probe.  The probes' logits come from MFMAs
-    // on split operands in absolute coordinates, 16 probes at once: they round
-    // at the scale of |z|^2 2^-22, which the reference may (every weight is
-    // formed relative to the same m, and the skip tests allow for far2 2^-20).
+    // on split operands, 16 probes at once, in coordinates about the grid's
+    // middle: they round at the scale of 2^-22 of the squared distance from it,
+    // which the reference may (every weight is formed relative to the same m, and
+    // the skip tests allow for far2 2^-20).
     float mup = -INFINITY;   // upper bound of every logit of the split
     int best = w.s0;
     for (int g = w.s0; g < w.s1; g += 64) {
@@ -1651,7 +1654,8 @@ __global__ __launch_bounds__(64 * NW * RT) __attribute__((amdgpu_waves_per_eu(6)
     float am[PB] = {-INFINITY, -INFINITY};   // reference of pixel b*16 + lp
     {
         bf16x8 pv[PB];
-        const float x[PB] = {ah[0] + al[0], ah[1] + al[1]}, none[PB] = {0.0f, 0.0f};
+        const float o = lk == 1 ? a.origin[1] : (lk == 2 ? a.origin[2] : a.origin[0]);
+        const float x[PB] = {(ah[0] - o) + al[0], (ah[1] - o) + al[1]}, none[PB] = {0.0f, 0.0f};
         pixel_operands(x, none, std::false_type{}, pv);
         const int shift = 4 - a.probe_shift;   // log2 of the super-tiles of one probe operand
         auto operand = [&](int blk) { return reinterpret_cast<const bf16x8 *>(a.probes)[(size_t)blk * 64 + lane]; };
@@ -2133,7 +2137,8 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5
         float zbox[6], far2 = 0.0f;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const float q = axis_coordinate(a.axes + 3 * k, ph[0] + pl[0], ph[1] + pl[1], ph[2] + pl[2]);
+            const float q = axis_coordinate(a.axes + 3 * k, (ph[0] - a.origin[0]) + pl[0],
+                                            (ph[1] - a.origin[1]) + pl[1], (ph[2] - a.origin[2]) + pl[2]);
             zbox[k] = wave_reduce<false>(q);
             zbox[3 + k] = wave_reduce<true>(q);
             const float e = fmaxf(-zbox[k], zbox[3 + k]);

@@ -62,6 +62,7 @@ struct hb_plan_s {
 
     hb_plan_info_t info{};
     float iref[3] = {1, 1, 1};
+    float origin[3] = {0, 0, 0};
     float axes[9] = {1, 0, 0, 0, 1, 0, 0, 0, 1};
     float spread[2] = {0, 0};   // of a tile's observations (PosteriorArgs)
     float scale = 1.0f;
@@ -575,10 +576,26 @@ void principal_axes(const std::vector<float> &table, int n_sup, int side, float 
         for (int k = 0; k < 3; ++k) axes[3 * r + k] = (float)V[k][order[r]];
 }
 
-// Test tables of the MFMA kernel (layout in hb_internal.h) from the
-// super-tile table; `out` holds headers and boxes one after the other.
+// Middle of the box of all nodes.
+void grid_middle(const std::vector<float> &table, int n_sup, int side, float origin[3]) {
+    const int stride = super_floats(side);
+    for (int k = 0; k < 3; ++k) {
+        double lo = INFINITY, hi = -INFINITY;
+        for (int si = 0; si < n_sup; ++si) {
+            const float *T = &table[(size_t)si * stride];
+            const double centre = (double)T[k] + (double)T[3 + k];
+            lo = std::min(lo, centre + (double)T[8 + k]);
+            hi = std::max(hi, centre + (double)T[11 + k]);
+        }
+        origin[k] = (float)(0.5 * (lo + hi));
+    }
+}
+
+// Test tables (layout in hb_internal.h) from the super-tile table; `out` holds
+// headers and boxes one after the other.
 void build_test_tables(const std::vector<float> &table, int n_sup, int columns, int side, size_t boxes_at,
-                       const float axes[9], std::vector<float> &out, std::vector<uint16_t> &probes) {
+                       const float origin[3], const float axes[9], std::vector<float> &out,
+                       std::vector<uint16_t> &probes) {
     const int stride = super_floats(side), cps = (side / 4) * (side / 4), slots = probe_slots(side);
     constexpr int kLaneHalves = kSplitLaneBytes / 2;
     out.assign(boxes_at + (size_t)n_sup * cps * kBoxFloats, 0.0f);
@@ -603,7 +620,7 @@ void build_test_tables(const std::vector<float> &table, int n_sup, int columns, 
         double cen[3];   // the centre along the axes
         for (int r = 0; r < 3; ++r) {
             cen[r] = 0.0;
-            for (int k = 0; k < 3; ++k) cen[r] += (double)axes[3 * r + k] * ((double)T[k] + (double)T[3 + k]);
+            for (int k = 0; k < 3; ++k) cen[r] += (double)axes[3 * r + k] * (((double)T[k] - (double)origin[k]) + (double)T[3 + k]);
         }
         for (int c = 0; c < cps; ++c) {
             const float *C = T + kSupHdr + kMaxProbes * kProbeFloats + (size_t)c * kChunkFloats;
@@ -631,7 +648,8 @@ void build_test_tables(const std::vector<float> &table, int n_sup, int columns, 
             const size_t at = (size_t)si * slots + i;
             double sq = 0;
             for (int k = 0; k < 3; ++k) {
-                const float x = (float)((double)T[k] + (double)T[3 + k] + (double)T[kSupHdr + i * kProbeFloats + k]);
+                const float x = (float)(((double)T[k] - (double)origin[k]) + (double)T[3 + k] +
+                                        (double)T[kSupHdr + i * kProbeFloats + k]);
                 v[at / 16 * 64 + 16 * k + at % 16] = x;
                 sq += (double)x * (double)x;
             }
@@ -761,6 +779,7 @@ hb_status_t estimate(hb_plan_s *p, const void *d_frames, int32_t n_frames, const
         pa.n_supers = p->n_tiles;
         pa.super_stride = super_floats(p->side);
         pa.chunks_per_super = (p->side / 4) * (p->side / 4);
+        for (int k = 0; k < 3; ++k) pa.origin[k] = p->origin[k];
         for (int k = 0; k < 9; ++k) pa.axes[k] = p->axes[k];
         for (int k = 0; k < 2; ++k) pa.spread[k] = p->spread[k];
         pa.headers = p->d_tests;
@@ -1072,6 +1091,7 @@ hb_status_t hb_set_forward_model(hb_plan_t p, const hb_forward_model_t *fm) {
     std::vector<float> tests;
     std::vector<uint16_t> probes, split_ops;
     build_split_ops(tiles, p->n_tiles, p->side, split_ops, kChunkRecordBytes);
+    grid_middle(tiles, p->n_tiles, p->side, p->origin);
     principal_axes(tiles, p->n_tiles, p->side, p->axes);
     for (int r = 1; r < 3; ++r) {
         double most = 0.0;   // uM per scaled unit along the axis
@@ -1082,8 +1102,8 @@ hb_status_t hb_set_forward_model(hb_plan_t p, const hb_forward_model_t *fm) {
         }
         p->spread[r - 1] = (float)(most / (kNarrowTile * std::max(d.thb_max, 1e-30)));
     }
-    build_test_tables(tiles, p->n_tiles, (d.grid_so2 + p->side - 1) / p->side, p->side, p->boxes_at, p->axes, tests,
-                      probes);
+    build_test_tables(tiles, p->n_tiles, (d.grid_so2 + p->side - 1) / p->side, p->side, p->boxes_at, p->origin, p->axes,
+                      tests, probes);
     if (hipMemcpy(p->d_tests, tests.data(), sizeof(float) * tests.size(), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(p->d_probes, probes.data(), sizeof(uint16_t) * probes.size(), hipMemcpyHostToDevice) != hipSuccess)
         return HB_ERR_DEVICE;

@@ -875,6 +875,35 @@ def test_wide_tiles_round_like_narrow_ones(torch_cuda, grid, split):
     assert err <= (1.5 if split == 1 else 3.0) * rounding
 
 
+@pytest.mark.parametrize("split", [1, 3])
+@pytest.mark.parametrize("sigma,ref", [(1e-5, (0.0, 0.5)), (1e-5, (150.0, 0.1)), (1e-4, (0.0, 0.5)), (1e-5, None)])
+def test_reference_concentration_far_from_a_narrow_grid(torch_cuda, sigma, ref, split):
+    """A narrow grid at a small sigma, and a reference concentration off it:
+    the observations lie 1e4 to 1e5 scaled units from mu_ref but within a few
+    of the nodes.  Neither the reference logits nor the skip tests may round at
+    the scale of the former."""
+    from paper_1706_07263_amd import hb
+    s = dict(_settings(levels=1, grid=64, sigma=sigma), thb_min=100.0, thb_max=100.2, so2_min=0.6, so2_max=0.602)
+    rng = np.random.default_rng(8)
+    thb, so2 = rng.uniform(100.0, 100.2, (32, 48)), rng.uniform(0.6, 0.602, (32, 48))
+    fr = synth.noisy_frame(*synth.hb_hbo2(thb, so2), synth.spectra(), 9, noise_sigma=0.3 * sigma)[None]
+    desc = hb.make_desc(48, 32, levels=1, grid_thb=64, grid_so2=64, thb_min=100.0, thb_max=100.2, so2_min=0.6,
+                        so2_max=0.602, sigma=sigma, grid_split=split,
+                        **({} if ref is None else dict(ref_thb=ref[0], ref_so2=ref[1])))
+    with hb.Plan(desc, 0) as plan:
+        plan.set_forward_model(synth.spectra())
+        assert plan.info()["posterior_kernel"] == "mfma"
+        maps = [torch_cuda.zeros((1, 32, 48), device="cuda") for _ in range(4)]
+        hb.hb_plan_set_timing(plan.handle, True)
+        plan.estimate(torch_cuda.from_numpy(fr).cuda(), maps)
+        got = np.stack([m.cpu().numpy() for m in maps], axis=1)
+        evaluated = hb.hb_plan_get_work(plan.handle)[0]
+    conc = None if ref is None else (ref[0] * (1.0 - ref[1]), ref[0] * ref[1])
+    want = orc.estimate(hbtest.oracle_params(48, 32, s, ref=conc), hbtest.oracle_model(synth.spectra()),
+                        fr.astype(np.float64))
+    print(f"sigma {sigma} ref {ref}: evaluated {evaluated / (24 * 16 * 64 * 64):.3f}", hbtest.assert_maps_close(got, want, "narrow grid"))
+
+
 @pytest.mark.parametrize("value", [np.nan, np.inf])
 @pytest.mark.parametrize("grid,kernel,split", [(256, "mfma", 1), (256, "mfma", 3), (24, "direct", 1), (24, "direct", 3)])
 def test_pixels_without_an_observation_take_no_far_pass(torch_cuda, value, grid, kernel, split):
