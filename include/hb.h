@@ -160,7 +160,7 @@ typedef struct {
     int32_t mfma_df_constant; /* 1: the MFMA kernel sums its pixel operand's constant |r|^2 + m as a
                              double-float (mfma_index > 350)                                           */
     double m_norm;        /* |M|inf, uM per unit log-attenuation                                         */
-    int32_t k1_double_float; /* 1: the log + Haar kernel forms log-ratios, Haar coefficients and the
+    int32_t k1_double_float; /* 1: the log + Haar kernel forms logs, block means and the
                              Tikhonov apply as double-floats (|M|inf > 1100 or three or more levels:
                              float32 log-ratios would reach the maps at up to ~1e-4 uM)               */
 } hb_plan_info_t;
@@ -251,7 +251,8 @@ hb_status_t hb_plan_get_work(hb_plan_t plan, int64_t *evaluated, int64_t *full);
  * distances, -log2 of the sum of 2^-d^2 over the nodes) and, with a split
  * grid, from the best probe node of the whole grid (the expanded logit
  * would round at the scale of that distance; the posterior of step 4 is
- * unchanged, only its precision).  Their pairs are not counted by
+ * unchanged, only its precision).  Pixels without a finite observation
+ * (their maps are NaN) are not among them.  Their pairs are not counted by
  * hb_plan_get_work.  Synchronises the device, then writes the count to the
  * host pointer `pixels`; HB_ERR_INVALID_ARG for a NULL plan or pointer,
  * HB_ERR_DEVICE if the device cannot be read. */

@@ -18,7 +18,8 @@ namespace hb {
 // stored relative to the super-tile centre.  One super-tile is
 //   header (kSupHdr floats)
 //     [0..2]  centre, high parts        [3..5] centre, low parts (double-float)
-//     [6] Hb of the centre node set     [7] HbO2 of it (moments are relative to these)
+//     [6] Hb of the centre node set     [7] HbO2 of it (moments are relative to these;
+//         multiples of the last bit of thb_max, so that their differences are exact)
 //     [8..10] box lower corner          [11..13] box upper corner (relative)
 //     [14] number of probes (int bits)
 //   probes (kMaxProbes x kProbeFloats): relative coordinates (3), Hb, HbO2
@@ -28,7 +29,8 @@ namespace hb {
 //     Slots outside the grid hold kPadCoord coordinates and kPadLogit here.
 //     [64 + j]: Hb of node j minus header[6]     [80 + j]: HbO2 minus header[7]
 //     [96..98] chunk box lower corner, [99..101] upper corner (absolute:
-//       centre plus the stored coordinates, rounded outward)
+//       centre plus the stored coordinates, rounded outward; the kernels test
+//       the boxes along the axes below, not these)
 //     [104 + 4 a + (0..3)], a = 0..3: for the chunk row of THb offset a,
 //       Hb = A_h + B_h s at SO2 offset s = 0..3 relative to header[6] (exact
 //       on a product grid: THb is constant along the row and SO2 is linear
@@ -131,9 +133,12 @@ constexpr float kExactSkipLog2 = 160.0f;
 constexpr float kMinSkipLog2 = 16.0f;
 // A-priori bound at a tolerance-derived threshold.  The hard threshold is
 // T + 1, which spends at most half of the tolerance on G 2^-(T+1); the bound
-// stated for the plan also allows each wave a budget of chunks bounded between
-// kBandLog2 and T + 1 below its reference, whose weights sum to at most 16
-// 2^-(T+1-kBandLog2) each, as many as the rest of the tolerance buys.
+// stated for the plan also allows each wave a budget of chunks bounded up to
+// kBandLog2 above T + 1 below its reference, whose weights sum to at most 16
+// 2^-(T+1-kBandLog2) each, as many as the rest of the tolerance buys.  No kernel
+// spends that budget: with one split the certificate below skips far more on the
+// same bound, and split grids evaluate 0.69 to 1.00 of the pairs that boxes along
+// the channels and the budget left them (1.03 on a 16 x 16 grid).
 constexpr float kBandLog2 = 6.0f;
 // Certified depth (one split).  The stated bound E on the posterior mean
 // holds for a pixel as soon as its skipped weight is at most E / thb_max of
@@ -346,8 +351,8 @@ struct PosteriorArgs {
                              // this take double-float logits (INFINITY: none)
     int dfc;                 // MFMA kernel: form the pixel operand's constant |r|^2 + m as a
                              // double-float (plans with R^2 h > kMfmaDfcIndex)
-    // Fused recomposition (one split, MFMA kernel, levels <= 2): the kernel
-    // writes the low-pass estimate and the maps itself instead of partials.
+    // Fused recomposition (one split, levels <= 3): the kernel writes the
+    // low-pass estimate and the maps itself instead of partials.
     int fuse;
     int levels, H, W;
     int vec;                 // pixels per map store: 1, 2 or 4 (pointer alignment)

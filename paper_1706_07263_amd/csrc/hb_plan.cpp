@@ -30,7 +30,7 @@ struct hb_plan_s {
     int split = 1;              // grid split in use
     int max_split = 1;          // that the buffers are sized for
     int side = 8;
-    float far_rho2 = INFINITY;  // MFMA kernel: squared room for far observations (scaled units)
+    float far_rho2 = INFINITY;  // squared room for far observations (scaled units)
     double radius = 0;        // largest super-tile radius, scaled units
     double node_h = 0;        // node spacing, uM of Hb/HbO2 (the larger of the two grid directions)
     bool use_mfma = true;
@@ -47,7 +47,7 @@ struct hb_plan_s {
     float *d_tiles = nullptr;   // super-tile table
     float *d_lo = nullptr;      // low parts of the node coordinates (double-float direct logits)
     void *d_split = nullptr;    // split bf16 A operands of the chunks
-    float *d_tests = nullptr;   // MFMA kernel: headers and boxes of its tests
+    float *d_tests = nullptr;   // headers and boxes of the skip tests
     void *d_probes = nullptr;   // MFMA kernel: split bf16 operands of the probes
     size_t boxes_at = 0;        // floats
     float *d_z = nullptr;
