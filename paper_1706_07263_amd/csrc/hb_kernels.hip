@@ -1362,10 +1362,11 @@ __device__ __forceinline__ void far_pixel_sums(const PosteriorArgs &a, const Wav
 // for any NW and RT.  DFC: the pixel operand's constant |r|^2 + m summed as a
 // double-float (plans near the precision budget).
 //
-// Bound by VALU issue: 96% busy on sixteen 1080p frames (256 x 256 grid), 14
-// instructions (one MFMA and four exponentials among them) per 256 pairs and
-// about 3100 per tile around them (12500 in all).  Six waves per SIMD (80
-// VGPRs; spills outside the chunk loop only).  Times a call with tiles of 8 x 4
+// Bound by VALU issue: 94 to 99% busy on sixteen 1080p frames (256 x 256 grid),
+// 14 instructions (one MFMA and four exponentials among them) per 256 pairs and
+// about 3000 per tile around them (12850 in all).  Six waves per SIMD (80
+// VGPRs; ten registers are spilled, outside the chunk loop, which every wave
+// writes once: a quarter of the kernel's HBM writes).  Times a call with tiles of 8 x 4
 // neighbours and boxes along the channels -> tiles of like observations and
 // boxes along the nodes' axes: sixteen 1080p frames 2274 -> 1976 us, 1280x1024
 // pair on a 512 x 512 grid 2794 -> 2470, 1280x1024 frame at level 0 with the
